@@ -19,6 +19,7 @@ LIB = os.path.join(PKG, "libargcsr.so")
 SOURCES = [
     "library.cpp",
     "plan.cpp",
+    "mailbox.cpp",
     "convert.hip",
     "group.hip",
     "spmv.hip",

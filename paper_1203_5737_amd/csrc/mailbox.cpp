@@ -1,0 +1,65 @@
+#include "mailbox.hpp"
+
+#include <hip/hip_runtime.h>
+
+#include <mutex>
+#include <vector>
+
+#include "common.hpp"
+
+namespace argcsr {
+namespace {
+
+constexpr int kSlots = 256;
+constexpr size_t kSlotBytes = sizeof(int64_t) * Mailbox::kWords;
+// visible to every device and written through to the host
+constexpr unsigned kFlags = hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent;
+
+std::mutex g_mu;
+int64_t* g_block = nullptr;           // kSlots slots, guarded by g_mu
+std::vector<int64_t*> g_free;         // guarded by g_mu
+
+}  // namespace
+
+int Mailbox::init() {
+  {
+    std::lock_guard<std::mutex> lock(g_mu);
+    if (!g_block) {
+      void* p = nullptr;
+      if (hipHostMalloc(&p, kSlots * kSlotBytes, kFlags) != hipSuccess)
+        return fail(ARGCSR_ENOMEM, "pinned result slots could not be allocated");
+      g_block = static_cast<int64_t*>(p);
+      g_free.reserve(kSlots);
+      for (int i = kSlots - 1; i >= 0; --i) g_free.push_back(g_block + i * kWords);
+    }
+    if (!g_free.empty()) {
+      host_ = g_free.back();
+      g_free.pop_back();
+    }
+  }
+  if (!host_) {
+    void* p = nullptr;
+    if (hipHostMalloc(&p, kSlotBytes, kFlags) != hipSuccess)
+      return fail(ARGCSR_ENOMEM, "pinned result slot could not be allocated");
+    host_ = static_cast<int64_t*>(p);
+    own_ = true;
+  }
+  void* d = nullptr;
+  if (hipHostGetDevicePointer(&d, host_, 0) != hipSuccess)
+    return fail(ARGCSR_EHIP, "pinned result slot is not mapped on this device");
+  dev_ = static_cast<int64_t*>(d);
+  for (int i = 0; i < kWords; ++i) static_cast<volatile int64_t*>(host_)[i] = 0;
+  return ARGCSR_OK;
+}
+
+Mailbox::~Mailbox() {
+  if (!host_ || lost_) return;
+  if (own_) {
+    (void)hipHostFree(host_);
+    return;
+  }
+  std::lock_guard<std::mutex> lock(g_mu);
+  g_free.push_back(host_);              // reserved above: never allocates
+}
+
+}  // namespace argcsr

@@ -164,6 +164,58 @@ def test_stage_heavy_groups_and_empty_rows(ac):
         assert M.n_heavy > 0
 
 
+def spread(n, distance, width):
+    """Rows i with columns i % width and distance + i % width (two bands
+    `distance` columns apart) and one column in between for odd rows."""
+    i = np.arange(n)
+    cols = [np.unique([k % width, distance // 2 + k % 7, distance + k % width]
+                      if k % 2 else [k % width, distance + k % width]) for k in i]
+    rp = np.zeros(n + 1, dtype=np.int32)
+    rp[1:] = np.cumsum([c.size for c in cols])
+    col = np.concatenate(cols).astype(np.int32)
+    return synth.Csr(n, distance + width, rp, col,
+                     np.random.default_rng(n).uniform(-1.0, 1.0, col.size))
+
+
+# distances around one and several 2^15-column pieces of the marking, with
+# windows that end and begin at their edges, up to the 2^18-column limit
+@pytest.mark.parametrize("distance", [32767 - 300, 32767, 32768, 65536 + 31, (1 << 18) - 300])
+@pytest.mark.parametrize("gap", [0, 40000])
+def test_stage_wide_spans(ac, distance, gap):
+    A = spread(900, distance, 300)
+    x = vec(A.n_cols, 3, 1)
+    for T, D in [(64, 1), (256, 8)]:
+        ref = oracle.convert(A.rp, A.col, A.val, T, D, 1)
+        if oracle.stage(ref, gap, MAX_TILES) == oracle.STAGE_TOO_MANY_TILES:
+            M = ac.convert(ac.to_device_csr(A.rp, A.col, A.val, A.n_cols, DEV), T, D, 1)
+            with pytest.raises(ac.ArgCsrError) as e:
+                ac.stage(M, gap=gap)
+            assert e.value.code == ac._lib.EUNSUPPORTED
+        else:
+            run_case(ac, A, T, D, 1, gap, x)
+
+
+# groups of every length against a workgroup's 1024, 2048 and 4096 held
+# slots, and block sizes whose slots allow no 16-byte loads
+@pytest.mark.parametrize("T,per_row", [(3, 5), (50, 9), (64, 16), (64, 17), (128, 16), (256, 16),
+                                       (256, 17), (250, 40)])
+def test_stage_group_lengths(ac, T, per_row):
+    n = 1000
+    rp = np.arange(0, n * per_row + 1, per_row, dtype=np.int32)
+    col = (np.arange(n)[:, None] + 3 * np.arange(per_row)[None, :]).ravel().astype(np.int32)
+    A = synth.Csr(n, n + 3 * per_row, rp, col, np.random.default_rng(1).uniform(-1, 1, col.size))
+    M = ac.convert(ac.to_device_csr(A.rp, A.col, A.val, A.n_cols, DEV), T, per_row, 1)
+    for cut in (0, 1):                        # the column array at 16 and at 4 bytes
+        M.columns = torch.cat([torch.zeros(cut, dtype=torch.int32, device=DEV), M.columns])[cut:]
+        for gap in (0, 2):
+            ref = oracle.stage(oracle.convert(A.rp, A.col, A.val, T, per_row, 1), gap, MAX_TILES)
+            Ms = ac.stage(M, gap=gap)
+            assert np.array_equal(Ms.tile_ptr.cpu().numpy(), ref.tile_ptr)
+            assert np.array_equal(Ms.tile_start.cpu().numpy(), ref.tile_start)
+            assert np.array_equal(Ms.tile_len.cpu().numpy(), ref.tile_len)
+            assert np.array_equal(Ms.local.cpu().numpy().view(np.uint16), ref.local)
+
+
 def test_stage_limits(ac):
     # 100 random columns over 10^5 per row: every group (one row) needs 100
     # one-column tiles, more than 64
