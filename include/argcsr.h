@@ -199,12 +199,12 @@ int argcsr_choose_region_desired(int32_t n_rows, const int32_t* row_ptr_host,
 /*
  * argcsr_plan_device -- the sizes argcsr_plan computes (same grouping rule,
  * same results), from a row_ptr that lives only in device memory: steps 1-2
- * of Sec. 3 run as HIP kernels on `stream` (step 1 by binary lifting over
- * the next-group-start function of the rows; see argcsr_convert).
+ * of Sec. 3 run as HIP kernels on `stream` (step 1 from the
+ * next-group-start function of the rows; see argcsr_convert).
  *   row_ptr  device int32[n_rows+1]
  *   other arguments as for argcsr_plan (n_heavy may be NULL)
  * Synchronous (reads the counts back).  Uses stream-ordered device scratch
- * of about 4*(log2(n_rows)+2)*n_rows bytes.  Errors: EINVAL (bad sizes,
+ * of about 22 bytes a row.  Errors: EINVAL (bad sizes,
  * row_ptr not starting at 0 or decreasing), EOVERFLOW, ENOMEM, EHIP.
  */
 int argcsr_plan_device(int32_t n_rows, const int32_t* row_ptr, int32_t block_dim,
@@ -220,7 +220,7 @@ typedef struct argcsr_device_plan argcsr_device_plan;
 /*
  * argcsr_plan_device_keep -- argcsr_plan_device that keeps its steps 1-3 in
  * *plan for argcsr_convert_planned (free it with argcsr_device_plan_destroy).
- * The plan holds 16 bytes per group and 4 per row of device memory.
+ * The plan holds 20 bytes per row of device memory (room for a group a row).
  *   arguments as for argcsr_plan_device; plan out (NULL on error)
  * Synchronous.  Errors: as argcsr_plan_device.
  */
@@ -256,8 +256,8 @@ int argcsr_device_plan_destroy(argcsr_device_plan* plan);
  * is given, and otherwise on the device from row_ptr alone: with
  * next(s) = the end of the group that opens at row s (a binary search on
  * row_ptr), the groups are the path 0 -> next(0) -> ... -> n_rows, found by
- * binary lifting (jump tables next^(2^k), then each group's start from the
- * bits of its index).  Either way the result equals, byte for byte, the
+ * composing the maps of 4096-row blocks (from each row the path can enter a
+ * block at to the row it enters the next one at).  Either way the result equals, byte for byte, the
  * sequential conversion the paper describes.
  *   row_ptr_host  host int32[n_rows+1] (same content as row_ptr), or NULL
  *   row_ptr       device int32[n_rows+1]
@@ -287,16 +287,16 @@ int argcsr_convert(int32_t n_rows, int32_t n_cols, const int32_t* row_ptr_host,
  * calls no hipMalloc, hipFree or other allocating routine.  Like
  * argcsr_convert it waits for its stream (it reads back the validation
  * flag), so it cannot itself be recorded into a HIP graph.  Its scratch (status words, scan partials and the
- * fill's long-row list) is a fixed 16 MiB array in device memory, one copy
+ * fill's long-row list) is a fixed array of 16 MiB and 32 KiB in device memory, one copy
  * per GPU, held by the library until the process ends; the caller still
  * passes every input and output, as for argcsr_convert, and the result is
  * byte for byte the same.
  *   arguments as for argcsr_convert, except that row_ptr_host is required
  *   (step 1 runs on the host; device grouping needs scratch proportional to
- *   n_rows*log2(n_rows))
- * A matrix whose scratch would exceed 16 MiB -- 24 + 16*ceil(n_groups/1024)
- * + 8*(n_slots/(4*block_dim) + 1) bytes, i.e. n_slots above about
- * 8*10^6*block_dim -- is rejected with EINVAL before anything is written.
+ *   n_rows)
+ * A matrix for which 24 + 16*ceil(n_groups/1024) + 8*(n_slots/(4*block_dim) + 1)
+ * exceeds 16 MiB, i.e. n_slots above about 8*10^6*block_dim, is rejected
+ * with EINVAL before anything is written.
  * The scratch keeps the last call's contents; each call clears what must
  * start at zero.  Calls are serialised by a process-wide lock and are
  * synchronous, so calls from several host threads never overlap on a GPU.

@@ -164,14 +164,46 @@ def choose_region_desired(row_ptr_host, region_rows: int, max_desired: int = 64)
 def plan_device(row_ptr: torch.Tensor, block_dim: int, desired_chunk_size: int, stream=None,
                 fmt: int = FORMAT_ARG):
     """(n_groups, n_slots, n_heavy) from a device row_ptr (argcsr_plan_device)."""
-    if row_ptr.dtype != torch.int32 or not row_ptr.is_contiguous() or not row_ptr.is_cuda:
-        raise ValueError("row_ptr must be a contiguous int32 device tensor")
+    _check_device_row_ptr(row_ptr)
     g, s, h = ctypes.c_int32(0), ctypes.c_int64(0), ctypes.c_int32(0)
     check(lib().argcsr_plan_device(int(row_ptr.numel() - 1), _ptr(row_ptr), int(block_dim),
                                    int(desired_chunk_size), int(fmt), ctypes.byref(g),
                                    ctypes.byref(s), ctypes.byref(h), _stream(stream)),
           "argcsr_plan_device")
     return g.value, s.value, h.value
+
+
+# Rows from which convert() groups on the device although the host has the
+# row offsets: the host scans them for the sizes and again for the groups, the
+# device takes five launches and one wait.  Whole conversions on MI355X, host /
+# device grouping, us: 8281 rows of a 5-point Laplacian 123 / 122, 16 384 rows
+# 156 / 123, 10^6 rows 1799 / 181; power-law rows 8192 119 / 135, 16 384
+# 153 / 137, 10^6 2781 / 216; 27-point stencil 15 625 rows 118 / 124, 32 768
+# 139 / 124, 10^6 1362 / 264.
+_DEVICE_GROUPING_ROWS = 16384
+
+
+def _groups_on_device(A: DeviceCsr) -> bool:
+    rp = A.row_ptr
+    return (A.n_rows >= _DEVICE_GROUPING_ROWS and rp.is_cuda and rp.dtype == torch.int32
+            and rp.is_contiguous() and rp.numel() == A.n_rows + 1)
+
+
+def _check_device_row_ptr(rp: torch.Tensor) -> None:
+    if rp.dtype != torch.int32 or not rp.is_contiguous() or not rp.is_cuda:
+        raise ValueError("row_ptr must be a contiguous int32 device tensor")
+
+
+def _plan_keep(A: DeviceCsr, block_dim, desired_chunk_size, fmt, stream):
+    """(plan handle, n_groups, n_slots, n_heavy) of argcsr_plan_device_keep."""
+    g, s, h = ctypes.c_int32(0), ctypes.c_int64(0), ctypes.c_int32(0)
+    plan_h = ctypes.c_void_p(0)
+    check(lib().argcsr_plan_device_keep(A.n_rows, _ptr(A.row_ptr), int(block_dim),
+                                        int(desired_chunk_size), int(fmt), ctypes.byref(g),
+                                        ctypes.byref(s), ctypes.byref(h),
+                                        ctypes.byref(plan_h), _stream(stream)),
+          "argcsr_plan_device_keep")
+    return plan_h, g.value, s.value, h.value
 
 
 def convert(A: DeviceCsr, block_dim: int = 64, desired_chunk_size: int = 1,
@@ -181,10 +213,12 @@ def convert(A: DeviceCsr, block_dim: int = 64, desired_chunk_size: int = 1,
     """CSR -> ARG-CSR (or, with fmt=FORMAT_RG, row-grouped CSR) on the GPU
     (argcsr_convert); allocates the result.  `schedule` also builds the
     heavy-group launch schedule.  With `device_grouping` step 1 runs on the
-    device and the host copy of row_ptr is not used: steps 1-3 run twice
-    (argcsr_plan_device, then argcsr_convert with row_ptr_host = NULL), or,
-    with `keep_plan`, once, kept on the device between sizing and conversion
-    (argcsr_plan_device_keep + argcsr_convert_planned).
+    device and the host copy of row_ptr is not used: steps 1-3 run once,
+    kept on the device between sizing and conversion
+    (argcsr_plan_device_keep + argcsr_convert_planned; `keep_plan` is
+    accepted and changes nothing).  Without it step 1 of a large matrix runs
+    there all the same (see _groups_on_device) and that of a small one on the
+    host; the result is the same bytes.
     `region_desired` (with `region_rows`) gives ARG-CSR a desiredChunkSize
     per region of rows (argcsr_plan_regions; the sizes are planned on the
     host).  `noalloc` converts with argcsr_convert_noalloc (the library
@@ -200,21 +234,18 @@ def convert(A: DeviceCsr, block_dim: int = 64, desired_chunk_size: int = 1,
         regions = np.ascontiguousarray(np.asarray(region_desired, dtype=np.int32))
         desired_chunk_size = 0
         G, S, H = plan_regions(A.row_ptr_host, block_dim, region_rows, regions)
-    elif device_grouping and keep_plan:
-        if A.row_ptr.dtype != torch.int32 or not A.row_ptr.is_contiguous():
-            raise ValueError("row_ptr must be a contiguous int32 device tensor")
-        g, s_, h = ctypes.c_int32(0), ctypes.c_int64(0), ctypes.c_int32(0)
-        plan_h = ctypes.c_void_p(0)
-        check(lib().argcsr_plan_device_keep(A.n_rows, _ptr(A.row_ptr), int(block_dim),
-                                            int(desired_chunk_size), int(fmt), ctypes.byref(g),
-                                            ctypes.byref(s_), ctypes.byref(h),
-                                            ctypes.byref(plan_h), _stream(stream)),
-              "argcsr_plan_device_keep")
-        G, S, H = g.value, s_.value, h.value
     elif device_grouping:
-        G, S, H = plan_device(A.row_ptr, block_dim, desired_chunk_size, stream, fmt)
+        _check_device_row_ptr(A.row_ptr)
+        plan_h, G, S, H = _plan_keep(A, block_dim, desired_chunk_size, fmt, stream)
     else:
-        G, S, H = plan(A.row_ptr_host, block_dim, desired_chunk_size, fmt)
+        if not noalloc and _groups_on_device(A):
+            try:
+                plan_h, G, S, H = _plan_keep(A, block_dim, desired_chunk_size, fmt, stream)
+            except ArgCsrError as e:
+                if e.code != _lib_mod.ENOMEM:        # no room for the plan: group on the host
+                    raise
+        if plan_h is None:
+            G, S, H = plan(A.row_ptr_host, block_dim, desired_chunk_size, fmt)
     try:
         dev = A.row_ptr.device
         out = ArgCsrMatrix(

@@ -51,30 +51,47 @@ __device__ __forceinline__ T wave_uniform(T v) {
   return __builtin_amdgcn_readfirstlane(v);
 }
 
-// Inclusive wave-wide prefix sum of an int (Hillis-Steele over 64 lanes).
+// One data-parallel-primitive step: v of the lane that CTRL names, `old` in
+// lanes whose row ROWS leaves out or that have no such lane.  These steps run
+// in the vector ALU (a few cycles each); a shuffle goes through LDS.
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ int dpp_move(int old, int v) {
+  return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xf, false);
+}
+constexpr int kDppRowShr = 0x110;      // + n: the lane n before, within 16 lanes
+constexpr int kDppRowBcast15 = 0x142;  // lane 15 of the 16 lanes before
+constexpr int kDppRowBcast31 = 0x143;  // lane 31
+
+// Inclusive wave-wide prefix sum and maximum.  Every lane must be active.
 __device__ __forceinline__ int wave_inclusive_scan(int v) {
-  const int lane = lane_id();
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int t = __shfl_up(v, d, 64);
-    if (lane >= d) v += t;
-  }
+  v += dpp_move<kDppRowShr + 1>(0, v);
+  v += dpp_move<kDppRowShr + 2>(0, v);
+  v += dpp_move<kDppRowShr + 4>(0, v);
+  v += dpp_move<kDppRowShr + 8>(0, v);
+  v += dpp_move<kDppRowBcast15, 0xa>(0, v);
+  v += dpp_move<kDppRowBcast31, 0xc>(0, v);
   return v;
 }
 
-__device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+__device__ __forceinline__ int wave_inclusive_max(int v) {
+  constexpr int kLow = INT32_MIN;
+  auto up = [](int x, int y) { return x > y ? x : y; };
+  v = up(v, dpp_move<kDppRowShr + 1>(kLow, v));
+  v = up(v, dpp_move<kDppRowShr + 2>(kLow, v));
+  v = up(v, dpp_move<kDppRowShr + 4>(kLow, v));
+  v = up(v, dpp_move<kDppRowShr + 8>(kLow, v));
+  v = up(v, dpp_move<kDppRowBcast15, 0xa>(kLow, v));
+  v = up(v, dpp_move<kDppRowBcast31, 0xc>(kLow, v));
   return v;
+}
+
+// Wave-wide sum (modulo 2^32) and maximum, the same in every lane.
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+  return uint32_t(__builtin_amdgcn_readlane(wave_inclusive_scan(int(v)), 63));
 }
 
 __device__ __forceinline__ int wave_max(int v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    const int t = __shfl_xor(v, d, 64);
-    v = t > v ? t : v;
-  }
-  return v;
+  return __builtin_amdgcn_readlane(wave_inclusive_max(v), 63);
 }
 
 }  // namespace argcsr

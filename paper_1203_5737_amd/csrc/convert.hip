@@ -1,14 +1,15 @@
 // CSR -> ARG-CSR conversion on the GPU (Sec. 3 of the paper).
 //
 // Step 1 (grouping) is a sequential scan; it runs on the host (plan.cpp), or
-// on the device by binary lifting (group.hip) when the caller has row_ptr on
+// on the device (group.hip) when the caller has row_ptr on
 // the device only.  The kernels here run steps 2-4, every group independently:
 //   chunks_kernel   step 2: chunk size c_g = min{c >= 1 : sum_r max(1,ceil(L_r/c)) <= T}
 //                   (row-grouped CSR: c_g = max(1, longest row)) and
 //                   t_r = max(1, ceil(L_r/c_g)) chunks per row;
 //                   step 3: inclusive per-group prefix sum of t_r -> threadsMapping
-//   offsets kernels exclusive scan of c_g*T over the groups -> groupInfo.offset
-//   heavy kernels   the launch schedule: ascending indices of groups whose
+//   offsets_kernel  exclusive scan of c_g*T over the groups -> groupInfo.offset,
+//                   and the sizes the host checks
+//   heavy_scatter   the launch schedule: ascending indices of groups whose
 //                   chunk loop is long (compaction by an exclusive scan)
 //   fill_kernel     step 4: every slot (j, k) of a group -- element j of chunk
 //   fill_long_kernel k at offset + j*T + k -- is written exactly once: the
@@ -28,6 +29,7 @@
 
 #include "common.hpp"
 #include "group.hpp"
+#include "mailbox.hpp"
 #include "plan.hpp"
 #include "schedule.hpp"
 #include "values.hpp"
@@ -37,37 +39,47 @@ namespace {
 
 constexpr int kWaves = 4;             // waves per workgroup, one group per wave
 constexpr int kMaxBlockDim = 1024;    // conversion accepts 1 <= T <= 1024
+constexpr int kChunkBlocks = 2048;    // workgroups of chunks_kernel: all the GPU holds at once
 constexpr int kScanBlock = 256;
-constexpr int kScanItems = 4;         // groups per thread in the offset scan
-constexpr int kScanTile = kScanBlock * kScanItems;
+constexpr int kScanBlocks = 128;      // workgroups of the offset and heavy scans
+constexpr int kScanShare = kChunkBlocks / kScanBlocks;   // shares of groups each takes
 constexpr int kMinStage = 256;        // CSR elements one fill wave stages in LDS
 constexpr int kMaxStage = 2048;
 constexpr int kMaxFillWaves = 4;
 constexpr int kLongSteps = 16;        // steps per LDS tile in fill_long_kernel
 constexpr int kLongGrid = 4096;       // one-wave workgroups of fill_long_kernel
 
-struct Status {                       // device-side results read back by the host
-  int bad_column;
-  int long_items;                     // entries of the fill's long-row work list
-  long long total_slots;
-  long long total_heavy;
+// Device-side state of one conversion, all zero at its start (but for
+// `groups`, which step 1 on the device fills in).
+struct Status {
+  GroupCount groups;                  // step 1's, when it runs on the device
+  int32_t long_items;                 // entries of the fill's long-row work list
+  int32_t scans_done;                 // workgroups of offsets_kernel that have finished
+  unsigned long long heavy;           // heavy groups of those
 };
 
-__global__ void clear_status_kernel(Status* st) { *st = Status{}; }
+// Words the kernels hand to the host (a pinned slot, or device memory).
+constexpr int kBoxGroups = 0, kBoxSlots = 1, kBoxHeavy = 2, kBoxBadRowPtr = 3, kBoxBadColumn = 4,
+              kBoxNnz = 5;
+constexpr int kBoxWords = Mailbox::kWords;
 
-// dst[i] = src[i] for n 32-bit words (a device plan's tables into the
-// caller's buffers)
-__global__ __launch_bounds__(256) void copy_words_kernel(const int32_t* __restrict__ src,
-                                                        int32_t* __restrict__ dst, int64_t n) {
-  for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n; i += int64_t(gridDim.x) * 256)
-    dst[i] = src[i];
+__global__ __launch_bounds__(64) void clear_words_kernel(int32_t* __restrict__ p, int32_t n) {
+  for (int32_t i = threadIdx.x; i < n; i += 64) p[i] = 0;
 }
 
-void copy_words(const void* src, void* dst, int64_t n, hipStream_t s) {
-  if (n <= 0) return;
-  const int64_t blocks = std::min<int64_t>((n + 255) / 256, 4096);
-  copy_words_kernel<<<dim3(uint32_t(blocks)), 256, 0, s>>>(static_cast<const int32_t*>(src),
-                                                          static_cast<int32_t*>(dst), n);
+// A device plan's tables into the caller's buffers: group records as 4
+// words, then the threads mapping; and a zero work list count for the fill.
+__global__ __launch_bounds__(256) void adopt_plan_kernel(const int32_t* __restrict__ groups,
+                                                         int64_t group_words,
+                                                         const int32_t* __restrict__ tm,
+                                                         int64_t n_rows,
+                                                         int32_t* __restrict__ out_groups,
+                                                         int32_t* __restrict__ out_tm,
+                                                         Status* __restrict__ st) {
+  const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x, stride = int64_t(gridDim.x) * 256;
+  for (int64_t i = t; i < group_words; i += stride) out_groups[i] = groups[i];
+  for (int64_t i = t; i < n_rows; i += stride) out_tm[i] = tm[i];
+  if (t == 0) st->long_items = 0;
 }
 
 // LDS of one fill wave: chunk starts and lengths, then the staged columns and
@@ -78,88 +90,140 @@ __host__ __device__ inline size_t fill_lds_bytes(int32_t T, int32_t stage) {
   return (b + 7) & ~size_t(7);
 }
 
-__device__ __forceinline__ int wave_min(int v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    const int t = __shfl_xor(v, d, 64);
-    v = t < v ? t : v;
-  }
-  return v;
+// The first group of share i of n equal shares.
+__device__ __forceinline__ int32_t share_begin(int32_t n_groups, int32_t i, int32_t n) {
+  return int32_t(int64_t(n_groups) * i / n);
 }
 
-// Step 2 + 3, one wave per group.  Row l of the group lives in lane l % 64,
-// sub-row l / 64.
-__global__ __launch_bounds__(kWaves * 64) void chunks_kernel(
-    const int32_t* __restrict__ rp, argcsr_group_info* __restrict__ groups,
-    int32_t n_groups, int32_t T, int32_t row_grouped, int32_t* __restrict__ tm) {
-  const int lane = lane_id();
-  const int g = blockIdx.x * kWaves + wave_uniform(int(threadIdx.x >> 6));
-  if (g >= n_groups) return;
-  const int32_t first = groups[g].first_row;
-  const int32_t size = groups[g].size;
-  const int sub_rows = (size + 63) / 64;
-
-  int64_t my_nnz = 0;
-  int my_longest = 0;
-  for (int s = 0; s < sub_rows; ++s) {
-    const int l = s * 64 + lane;
-    if (l < size) {
-      const int L = rp[first + l + 1] - rp[first + l];
-      my_nnz += L;
-      my_longest = L > my_longest ? L : my_longest;
-    }
+// Lengths of a group's rows: row l in lane l % 64, sub-row l / 64.
+template <int SUB>
+__device__ __forceinline__ void row_lengths(const int32_t* __restrict__ rp, int32_t first,
+                                            int32_t size, uint32_t (&L)[SUB]) {
+#pragma unroll
+  for (int s = 0; s < SUB; ++s) {
+    const int l = s * 64 + lane_id();
+    L[s] = l < size ? uint32_t(rp[first + l + 1] - rp[first + l]) : 0u;
   }
-  const int64_t total = wave_sum_i64(my_nnz);
-  const int longest = wave_max(my_longest);
+}
 
+// Steps 2 + 3 of one group by the calling wave; returns its chunk size.
+template <int SUB>
+__device__ __forceinline__ uint32_t group_chunks(const uint32_t (&L)[SUB], int32_t first,
+                                                 int32_t size, int32_t T, bool row_grouped,
+                                                 int32_t* __restrict__ tm) {
+  const int lane = lane_id();
+  uint32_t my_nnz = 0;
+  int my_longest = 0;
+#pragma unroll
+  for (int s = 0; s < SUB; ++s) {
+    my_nnz += L[s];
+    my_longest = int(L[s]) > my_longest ? int(L[s]) : my_longest;
+  }
+  const uint32_t total = wave_sum(my_nnz);          // row_ptr is int32: no overflow
+  const uint32_t longest = uint32_t(wave_max(my_longest));
+
+  // chunks of the group's rows at chunk size c (at most nnz + 1024 < 2^32)
   auto chunks_needed = [&](uint32_t c) {
-    int64_t need = 0;
-    for (int s = 0; s < sub_rows; ++s) {
-      const int l = s * 64 + lane;
-      if (l < size) {
-        const uint32_t L = uint32_t(rp[first + l + 1] - rp[first + l]);
-        need += L > c ? (L - 1u) / c + 1u : 1u;
-      }
-    }
-    return wave_sum_i64(need);
+    uint32_t need = 0;
+#pragma unroll
+    for (int s = 0; s < SUB; ++s)
+      if (s * 64 + lane < size) need += L[s] > c ? (L[s] - 1u) / c + 1u : 1u;
+    return wave_sum(need);
   };
   // binary search on the non-increasing chunks_needed(c) between two bounds:
   // no c below total/T fits, and c = longest (one chunk per row) always does;
   // since max(1, ceil(L/c)) <= L/c + 1, every c >= total/(T - size) fits too.
   // Row-grouped CSR, and a group of T rows, take one chunk per row.
-  uint32_t lo = uint32_t((total + T - 1) / T);
+  uint32_t lo = uint32_t((uint64_t(total) + uint32_t(T) - 1) / uint32_t(T));
   lo = lo < 1u ? 1u : lo;
-  uint32_t hi = longest < 1 ? 1u : uint32_t(longest);
+  uint32_t hi = longest < 1u ? 1u : longest;
   if (row_grouped || size >= T) {
     lo = hi;
   } else {
-    const int64_t fit = (total + (T - size) - 1) / (T - size);
-    if (fit < int64_t(hi)) hi = fit < 1 ? 1u : uint32_t(fit);
+    const uint32_t fit = uint32_t((uint64_t(total) + uint32_t(T - size) - 1) / uint32_t(T - size));
+    if (fit < hi) hi = fit < 1u ? 1u : fit;
   }
   while (lo < hi) {
     const uint32_t mid = lo + (hi - lo) / 2;
-    if (chunks_needed(mid) <= T) hi = mid;
+    if (chunks_needed(mid) <= uint32_t(T)) hi = mid;
     else lo = mid + 1;
   }
-  const uint32_t c = lo;
-
   int carry = 0;
-  for (int s = 0; s < sub_rows; ++s) {
+#pragma unroll
+  for (int s = 0; s < SUB; ++s) {
     const int l = s * 64 + lane;
-    int t = 0;
-    if (l < size) {
-      const uint32_t L = uint32_t(rp[first + l + 1] - rp[first + l]);
-      t = L > c ? int((L - 1u) / c + 1u) : 1;
-    }
+    const int t = l < size ? (L[s] > lo ? int((L[s] - 1u) / lo + 1u) : 1) : 0;
     const int incl = wave_inclusive_scan(t) + carry;
     if (l < size) tm[first + l] = incl;
-    carry = __shfl(incl, 63, 64);
+    carry = __builtin_amdgcn_readlane(incl, 63);
   }
-  if (lane == 0) groups[g].chunk_size = int32_t(c);
+  return lo;
 }
 
-// Offsets: block-local sums of c_g*T, a single-block scan of those, then the
-// block-local exclusive scan plus the block's base.
+// Steps 2 + 3.  Workgroup i takes the i-th of kChunkBlocks equal shares of
+// the groups, its waves every fourth group of the share, and leaves the
+// share's slots in share_slots[i]: the scan of the offsets then needs no pass
+// of its own over the groups.  SUB = sub-rows of 64 rows a group may have.
+// The group count is *n_dev when given (step 1 on the device), else n_host.
+// Bound by each group's chain -- record, row offsets, two wave reductions,
+// the search (0 to ~4 rounds of one reduction), the scan -- so a wave has the
+// next group's row offsets and the record after that on their way while it
+// works.  On the power-law matrix of 10^6 rows (63 517 groups) a wave per
+// group with reductions through LDS and the rows read again in every round
+// of the search took 32 us, this takes 18 us; on the 27-point stencil of 10^6
+// rows (7813 groups of T = 128 rows) 8.5 and 7.3 us.
+template <int SUB>
+__global__ __launch_bounds__(kWaves * 64) void chunks_kernel(
+    const int32_t* __restrict__ rp, argcsr_group_info* __restrict__ groups, int32_t n_host,
+    const GroupCount* __restrict__ n_dev, int32_t T, int32_t row_grouped,
+    int32_t* __restrict__ tm, int64_t* __restrict__ share_slots) {
+  __shared__ int64_t wave_slots[kWaves];
+  const int32_t n_groups = n_dev ? n_dev->n_groups : n_host;
+  const int wv = wave_uniform(int(threadIdx.x >> 6));
+  const int32_t g1 = share_begin(n_groups, int32_t(blockIdx.x) + 1, kChunkBlocks);
+  int32_t g = share_begin(n_groups, int32_t(blockIdx.x), kChunkBlocks) + wv;
+  int64_t slots = 0;
+  int2 rec{0, 0}, next{0, 0};                       // first row, size
+  uint32_t L[SUB];
+  auto record = [&](int32_t i) {
+    return i < g1 ? int2{groups[i].first_row, groups[i].size} : int2{0, 0};
+  };
+  rec = record(g);
+  next = record(g + kWaves);
+  row_lengths<SUB>(rp, rec.x, rec.y, L);
+  for (; g < g1; g += kWaves) {
+    uint32_t Ln[SUB];
+    row_lengths<SUB>(rp, next.x, next.y, Ln);
+    const int2 after = record(g + 2 * kWaves);
+    const uint32_t c = group_chunks<SUB>(L, rec.x, rec.y, T, row_grouped != 0, tm);
+    if (lane_id() == 0) groups[g].chunk_size = int32_t(c);
+    slots += int64_t(c) * T;
+    rec = next;
+    next = after;
+#pragma unroll
+    for (int s = 0; s < SUB; ++s) L[s] = Ln[s];
+  }
+  if (lane_id() == 0) wave_slots[wv] = slots;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kWaves; ++w) slots += wave_slots[w];
+    share_slots[blockIdx.x] = slots;
+  }
+}
+
+void launch_chunks(const int32_t* rp, argcsr_group_info* groups, int32_t n_groups,
+                   const GroupCount* n_dev, int32_t T, int32_t format, int32_t* tm,
+                   int64_t* share_slots, hipStream_t s) {
+  const dim3 grid(kChunkBlocks), block(kWaves * 64);
+  const int32_t rg = format == ARGCSR_FORMAT_RG ? 1 : 0;
+  auto* kern = T <= 64    ? &chunks_kernel<1>
+               : T <= 128 ? &chunks_kernel<2>
+               : T <= 256 ? &chunks_kernel<4>
+                          : &chunks_kernel<16>;
+  kern<<<grid, block, 0, s>>>(rp, groups, n_groups, n_dev, T, rg, tm, share_slots);
+}
+
+// Workgroup-wide exclusive scan and sum.
 __device__ int64_t block_exclusive_scan(int64_t v, int64_t* total) {
   __shared__ int64_t wave_tot[kScanBlock / 64];
   const int lane = lane_id(), w = threadIdx.x >> 6;
@@ -181,75 +245,85 @@ __device__ int64_t block_exclusive_scan(int64_t v, int64_t* total) {
   return before + incl - v;
 }
 
-__global__ __launch_bounds__(kScanBlock) void offsets_reduce_kernel(
-    const argcsr_group_info* __restrict__ groups, int32_t n_groups, int32_t T,
-    int64_t* __restrict__ tile_sums) {
-  int64_t s = 0;
-  const int64_t base = int64_t(blockIdx.x) * kScanTile + threadIdx.x * kScanItems;
-  for (int i = 0; i < kScanItems; ++i)
-    if (base + i < n_groups) s += int64_t(groups[base + i].chunk_size) * T;
-  int64_t total;
-  (void)block_exclusive_scan(s, &total);
-  if (threadIdx.x == 0) tile_sums[blockIdx.x] = total;
-}
-
-__global__ __launch_bounds__(kScanBlock) void tiles_scan_kernel(
-    int64_t* __restrict__ tile_sums, int32_t n_tiles, long long* total_out) {
-  int64_t carry = 0;
-  for (int32_t base = 0; base < n_tiles; base += kScanBlock) {
-    const int32_t i = base + threadIdx.x;
-    const int64_t v = i < n_tiles ? tile_sums[i] : 0;
-    int64_t total;
-    const int64_t ex = block_exclusive_scan(v, &total);
-    if (i < n_tiles) tile_sums[i] = carry + ex;
-    carry += total;
+// Sums of v[0 .. at) and of v[at .. n).
+__device__ void split_sums(const int64_t* __restrict__ v, int32_t at, int32_t n, int64_t* before,
+                           int64_t* rest) {
+  int64_t b = 0, r = 0;
+#pragma unroll 8
+  for (int32_t i = threadIdx.x; i < n; i += kScanBlock) {
+    const int64_t x = v[i];
+    if (i < at) b += x;
+    else r += x;
   }
-  if (threadIdx.x == 0) *total_out = carry;
+  (void)block_exclusive_scan(b, before);
+  (void)block_exclusive_scan(r, rest);
 }
 
-__global__ __launch_bounds__(kScanBlock) void offsets_apply_kernel(
-    argcsr_group_info* __restrict__ groups, int32_t n_groups, int32_t T,
-    const int64_t* __restrict__ tile_base) {
-  const int64_t base = int64_t(blockIdx.x) * kScanTile + threadIdx.x * kScanItems;
-  int64_t s = 0;
-  for (int i = 0; i < kScanItems; ++i)
-    if (base + i < n_groups) s += int64_t(groups[base + i].chunk_size) * T;
-  int64_t total;
-  int64_t off = tile_base[blockIdx.x] + block_exclusive_scan(s, &total);
-  for (int i = 0; i < kScanItems; ++i) {
-    if (base + i < n_groups) {
-      groups[base + i].offset = int32_t(off);     // host checks the total fits int32
-      off += int64_t(groups[base + i].chunk_size) * T;
+// Offsets (an exclusive scan of c_g*T over the groups), the heavy groups of
+// every workgroup's part, and, by the workgroup that finishes last, the sizes
+// for the host.  A workgroup takes kScanShare consecutive shares of
+// chunks_kernel and sums the shares before them itself, so the scan is one
+// launch.  Few workgroups: each adds to the two counters of `st`, and atomics
+// on one cache line take turns at about 12 ns each.
+__global__ __launch_bounds__(kScanBlock) void offsets_kernel(
+    argcsr_group_info* __restrict__ groups, int32_t n_host, const GroupCount* __restrict__ n_dev,
+    int32_t T, const int64_t* __restrict__ share_slots, int64_t* __restrict__ heavy_parts,
+    Status* __restrict__ st, const int32_t* __restrict__ rp, int32_t n_rows,
+    int64_t* __restrict__ box) {
+  const int32_t n_groups = n_dev ? n_dev->n_groups : n_host;
+  const int32_t b = int32_t(blockIdx.x);
+  int64_t off, rest;
+  split_sums(share_slots, b * kScanShare, kChunkBlocks, &off, &rest);
+  const int64_t slots = off + rest;
+  const int32_t heavy_chunk = heavy_chunk_for(T, slots, n_groups);
+  const int32_t g0 = share_begin(n_groups, b * kScanShare, kChunkBlocks);
+  const int32_t g1 = share_begin(n_groups, (b + 1) * kScanShare, kChunkBlocks);
+  int32_t heavy = 0;
+  for (int32_t i = g0; i < g1; i += kScanBlock) {
+    const int32_t g = i + int32_t(threadIdx.x);
+    const int32_t c = g < g1 ? groups[g].chunk_size : 0;
+    int64_t all;
+    const int64_t mine = off + block_exclusive_scan(int64_t(c) * T, &all);
+    if (g < g1) groups[g].offset = int32_t(mine);    // the host checks the total
+    heavy += c > heavy_chunk;
+    off += all;
+  }
+  int64_t part_heavy;
+  (void)block_exclusive_scan(heavy, &part_heavy);
+  if (threadIdx.x == 0) {
+    heavy_parts[b] = part_heavy;
+    if (part_heavy) atomicAdd(&st->heavy, (unsigned long long)part_heavy);
+    __threadfence();
+    if (atomicAdd(&st->scans_done, 1) == kScanBlocks - 1) {
+      __threadfence();
+      box[kBoxGroups] = n_groups;
+      box[kBoxSlots] = slots;
+      box[kBoxHeavy] = int64_t(atomicAdd(&st->heavy, 0ull));
+      box[kBoxBadRowPtr] = n_dev ? n_dev->bad : 0;
+      box[kBoxNnz] = n_dev ? rp[n_rows] : 0;
     }
   }
 }
 
-// Heavy-group schedule: per-tile counts, then (after the tile scan) each
-// tile writes the indices of its heavy groups in ascending order.
-__global__ __launch_bounds__(kScanBlock) void heavy_count_kernel(
-    const argcsr_group_info* __restrict__ groups, int32_t n_groups, int32_t heavy_chunk,
-    int64_t* __restrict__ tile_sums) {
-  int64_t s = 0;
-  const int64_t base = int64_t(blockIdx.x) * kScanTile + threadIdx.x * kScanItems;
-  for (int i = 0; i < kScanItems; ++i)
-    if (base + i < n_groups) s += groups[base + i].chunk_size > heavy_chunk;
-  int64_t total;
-  (void)block_exclusive_scan(s, &total);
-  if (threadIdx.x == 0) tile_sums[blockIdx.x] = total;
-}
-
+// The launch schedule: every part of offsets_kernel writes the indices of
+// its heavy groups, ascending, behind those of the parts before it.
 __global__ __launch_bounds__(kScanBlock) void heavy_scatter_kernel(
     const argcsr_group_info* __restrict__ groups, int32_t n_groups, int32_t heavy_chunk,
-    const int64_t* __restrict__ tile_base, int32_t* __restrict__ heavy) {
-  const int64_t base = int64_t(blockIdx.x) * kScanTile + threadIdx.x * kScanItems;
-  int64_t s = 0;
-  for (int i = 0; i < kScanItems; ++i)
-    if (base + i < n_groups) s += groups[base + i].chunk_size > heavy_chunk;
-  int64_t total;
-  int64_t pos = tile_base[blockIdx.x] + block_exclusive_scan(s, &total);
-  for (int i = 0; i < kScanItems; ++i)
-    if (base + i < n_groups && groups[base + i].chunk_size > heavy_chunk)
-      heavy[pos++] = int32_t(base + i);
+    const int64_t* __restrict__ heavy_parts, int32_t* __restrict__ heavy) {
+  const int32_t b = int32_t(blockIdx.x);
+  if (heavy_parts[b] == 0) return;
+  int64_t pos, rest;
+  split_sums(heavy_parts, b, kScanBlocks, &pos, &rest);
+  const int32_t g0 = share_begin(n_groups, b * kScanShare, kChunkBlocks);
+  const int32_t g1 = share_begin(n_groups, (b + 1) * kScanShare, kChunkBlocks);
+  for (int32_t i = g0; i < g1; i += kScanBlock) {
+    const int32_t g = i + int32_t(threadIdx.x);
+    const bool is = g < g1 && groups[g].chunk_size > heavy_chunk;
+    int64_t all;
+    const int64_t at = pos + block_exclusive_scan(is ? 1 : 0, &all);
+    if (is) heavy[at] = g;
+    pos += all;
+  }
 }
 
 // For every chunk k of the group: where its elements start in the CSR arrays
@@ -280,7 +354,7 @@ __device__ inline void chunk_sources(const argcsr_group_info& gi, const int32_t*
 // The CSR range [lo, lo + extent) that holds the elements of the wave's 64
 // chunks (start, len per lane); extent 0 when they have none.
 __device__ inline int32_t block_extent(int32_t start, int32_t len, int32_t* lo_out) {
-  const int32_t lo = wave_min(len > 0 ? start : INT32_MAX);
+  const int32_t lo = INT32_MAX - wave_max(len > 0 ? INT32_MAX - start : 0);
   const int32_t hi = wave_max(len > 0 ? start + len : 0);
   *lo_out = lo;
   return hi > lo ? hi - lo : 0;
@@ -304,7 +378,7 @@ __global__ __launch_bounds__(kMaxFillWaves * 64) void fill_kernel(
     const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
     const double* __restrict__ val, const argcsr_group_info* __restrict__ groups,
     int32_t n_groups, int32_t n_cols, int32_t T, const int32_t* __restrict__ tm, int32_t stage,
-    Status* __restrict__ st, int32_t* __restrict__ long_list,
+    Status* __restrict__ st, int64_t* __restrict__ box, int32_t* __restrict__ long_list,
     int32_t* __restrict__ columns, typename Val<DT>::storage* __restrict__ values) {
   using S = typename Val<DT>::storage;
   extern __shared__ int32_t fill_lds[];   // per wave: [T] starts, [T] lengths, stage
@@ -364,7 +438,7 @@ __global__ __launch_bounds__(kMaxFillWaves * 64) void fill_kernel(
       wave_lds_sync();   // the next block overwrites the stage
     }
   }
-  if (__ballot(bad) != 0 && lane == 0) atomicOr(&st->bad_column, 1);
+  if (__ballot(bad) != 0 && lane == 0) box[kBoxBadColumn] = 1;
 }
 
 // Step 4 for the blocks fill_kernel leaves: those whose CSR range is longer
@@ -382,7 +456,7 @@ __global__ __launch_bounds__(64) void fill_long_kernel(
     const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
     const double* __restrict__ val, const argcsr_group_info* __restrict__ groups,
     int32_t n_cols, int32_t T, const int32_t* __restrict__ tm, int32_t stage,
-    Status* __restrict__ st,
+    const Status* __restrict__ st, int64_t* __restrict__ box,
     const int32_t* __restrict__ long_list, int32_t* __restrict__ columns,
     typename Val<DT>::storage* __restrict__ values) {
   using S = typename Val<DT>::storage;
@@ -438,7 +512,7 @@ __global__ __launch_bounds__(64) void fill_long_kernel(
       wave_lds_sync();   // the next block or item overwrites the tile and tables
     }
   }
-  if (__ballot(bad) != 0 && lane == 0) atomicOr(&st->bad_column, 1);
+  if (__ballot(bad) != 0 && lane == 0) box[kBoxBadColumn] = 1;
 }
 
 // The stage holds the blocks of chunks up to twice the matrix's mean chunk
@@ -447,7 +521,8 @@ __global__ __launch_bounds__(64) void fill_long_kernel(
 // matrices need to hide their latency.
 template <int DT>
 void launch_fill(int32_t n_groups, hipStream_t s, const int32_t* rp, const int32_t* col,
-                 const double* val, Status* st, int32_t* long_list, const argcsr_matrix* out) {
+                 const double* val, Status* st, int64_t* box, int32_t* long_list,
+                 const argcsr_matrix* out) {
   using S = typename Val<DT>::storage;
   const int64_t T = out->block_dim;
   const int64_t mean_chunk = (out->n_slots + int64_t(n_groups) * T - 1) / (int64_t(n_groups) * T);
@@ -458,27 +533,30 @@ void launch_fill(int32_t n_groups, hipStream_t s, const int32_t* rp, const int32
   const uint32_t blocks = uint32_t((int64_t(n_groups) + waves - 1) / waves);
   fill_kernel<DT><<<dim3(blocks), 64 * waves, lds, s>>>(
       rp, col, val, out->groups, out->n_groups, out->n_cols, out->block_dim, out->threads_mapping,
-      stage, st, long_list, out->columns, static_cast<S*>(out->values));
+      stage, st, box, long_list, out->columns, static_cast<S*>(out->values));
   const int64_t long_blocks = std::min<int64_t>(n_groups, kLongGrid);
   fill_long_kernel<DT><<<dim3(uint32_t(long_blocks)), 64, sizeof(int32_t) * 2 * size_t(T), s>>>(
       rp, col, val, out->groups, out->n_cols, out->block_dim, out->threads_mapping, stage, st,
-      long_list, out->columns, static_cast<S*>(out->values));
+      box, long_list, out->columns, static_cast<S*>(out->values));
 }
 
 }  // namespace
 }  // namespace argcsr
 
 // A device plan (argcsr_plan_device_keep): steps 1-3 of one matrix kept on
-// the device for argcsr_convert_planned.
+// the device for argcsr_convert_planned, and the sizes of the result.
 // Its buffers are stream-ordered allocations on the planning stream (freed
 // on it too: every conversion with the plan has waited for its own work).
+// The group table has room for one group a row, because the number of groups
+// is only known to the device while the plan is made.
 struct argcsr_device_plan {
   int32_t n_rows = 0, block_dim = 0, desired_chunk_size = 0, format = 0;
   int32_t n_groups = 0, n_heavy = 0;
-  int64_t n_slots = 0;
-  argcsr_group_info* groups = nullptr;    // first_row, size, chunk_size (offset not yet set)
+  int64_t n_slots = 0, nnz = 0;
+  argcsr_group_info* groups = nullptr;    // complete, offsets included
   int32_t* tm = nullptr;                  // threads mapping
-  void* block = nullptr;                  // the one allocation holding both
+  int64_t* heavy_parts = nullptr;         // heavy groups per part of offsets_kernel
+  void* block = nullptr;                  // the one allocation holding them
   hipStream_t stream = nullptr;
   ~argcsr_device_plan() {
     if (block) (void)hipFreeAsync(block, stream);
@@ -488,31 +566,104 @@ struct argcsr_device_plan {
 // Fixed scratch of argcsr_convert_noalloc: one copy per GPU (this process's
 // code object), held until the process ends.  Host code reaches it only
 // through the address hipGetSymbolAddress returns for the current device.
+constexpr size_t kHeadBytes = 256;      // Status and the result words
+constexpr size_t kNoAllocExtra = 32768;   // head and shares
 constexpr size_t kNoAllocScratchBytes = size_t(16) << 20;
-static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kNoAllocExtra + kNoAllocScratchBytes];
 
 namespace argcsr {
 namespace {
 
-// Device scratch of one conversion: status words, the two tile-sum arrays of
-// the offset and heavy scans, and the fill's long-row list.  Items of that
+// Device scratch of one conversion: a head of kHeadBytes (Status and, for
+// argcsr_convert_noalloc, the result words), the slots of the shares of
+// chunks_kernel and the heavy groups of the parts of offsets_kernel, and the
+// fill's long-row list.  Items of that
 // list: a group makes them only when its chunk size c exceeds
 // stage/64 >= kMinStage/64 = 4, and then ceil(c/16) <= c/4 of them, so all
 // groups together make at most n_slots/(4T).
 static_assert(kMinStage / 64 >= 4 && kLongSteps == 16, "long-list bound");
-struct ConvertScratch {
-  int32_t n_tiles;
-  int64_t long_capacity;
-  size_t bytes;
+static_assert(sizeof(Status) + sizeof(int64_t) * kBoxWords <= kHeadBytes, "head of the scratch");
+static_assert(kHeadBytes + sizeof(int64_t) * (kChunkBlocks + kScanBlocks) <= kNoAllocExtra,
+              "head and shares of the fixed scratch");
+constexpr size_t kShareBytes = sizeof(int64_t) * (kChunkBlocks + kScanBlocks);
+
+int64_t long_capacity(int64_t n_slots, int32_t T) { return n_slots / (4 * int64_t(T)) + 1; }
+
+size_t convert_scratch(int64_t n_slots, int32_t T) {
+  return kHeadBytes + kShareBytes + 2 * sizeof(int32_t) * size_t(long_capacity(n_slots, T));
+}
+
+// The result words of one conversion: a pinned slot, or (fixed) words of the
+// device scratch that are copied back.
+struct ResultBox {
+  Mailbox mail;
+  int64_t* dev = nullptr;
+  int64_t word[kBoxWords] = {};
+  bool fixed = false;
+  int init(int64_t* fixed_words) {
+    fixed = fixed_words != nullptr;
+    if (fixed) {
+      dev = fixed_words;
+      return ARGCSR_OK;
+    }
+    const int rc = mail.init();
+    dev = mail.device();
+    return rc;
+  }
+  // waits for the stream and reads the words
+  int read(hipStream_t s) {
+    hipError_t e = hipSuccess;
+    if (fixed) e = hipMemcpyAsync(word, dev, sizeof(word), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) {
+      mail.abandon();
+      return fail(ARGCSR_EHIP, "conversion: %s", hipGetErrorString(e));
+    }
+    if (!fixed)
+      for (int i = 0; i < kBoxWords; ++i) word[i] = mail.word(i);
+    return ARGCSR_OK;
+  }
 };
 
-ConvertScratch convert_scratch(int32_t n_groups, int64_t n_slots, int32_t T) {
-  ConvertScratch c;
-  c.n_tiles = (n_groups + kScanTile - 1) / kScanTile;
-  c.long_capacity = n_slots / (4 * int64_t(T)) + 1;
-  c.bytes = sizeof(Status) + 2 * sizeof(int64_t) * size_t(c.n_tiles) +
-            2 * sizeof(int32_t) * size_t(c.long_capacity);
-  return c;
+// Steps 1-3 of n_rows > 0 rows on the device, and the sizes of the result
+// (one wait for the stream).
+int build_plan(int32_t n_rows, const int32_t* row_ptr, int32_t T, int32_t desired, int32_t format,
+               int32_t region_rows, const int32_t* regions, hipStream_t s, argcsr_device_plan* p) {
+  const size_t groups_b = sizeof(argcsr_group_info) * size_t(n_rows);
+  const size_t tm_b = (sizeof(int32_t) * size_t(n_rows) + 15) / 16 * 16;
+  ResultBox box;
+  int rc = box.init(nullptr);
+  if (rc) return rc;
+  p->stream = s;
+  rc = scratch_alloc_async(&p->block, groups_b + tm_b + kShareBytes + sizeof(Status), s);
+  if (rc) return rc;
+  char* base = static_cast<char*>(p->block);
+  p->groups = reinterpret_cast<argcsr_group_info*>(base);
+  p->tm = reinterpret_cast<int32_t*>(base + groups_b);
+  auto* share_slots = reinterpret_cast<int64_t*>(base + groups_b + tm_b);
+  p->heavy_parts = share_slots + kChunkBlocks;
+  auto* st = reinterpret_cast<Status*>(p->heavy_parts + kScanBlocks);
+  rc = group_on_device(n_rows, row_ptr, T, desired, format, region_rows, regions, p->groups,
+                       &st->groups, reinterpret_cast<int32_t*>(st),
+                       int64_t(sizeof(Status) / sizeof(int32_t)), s);
+  if (rc) return rc;
+  launch_chunks(row_ptr, p->groups, 0, &st->groups, T, format, p->tm, share_slots, s);
+  offsets_kernel<<<kScanBlocks, kScanBlock, 0, s>>>(p->groups, 0, &st->groups, T, share_slots,
+                                                    p->heavy_parts, st, row_ptr, n_rows, box.dev);
+  ARGCSR_HIP(hipGetLastError());
+  rc = box.read(s);
+  if (rc) return rc;
+  if (box.word[kBoxBadRowPtr])
+    return fail(ARGCSR_EINVAL, "row_ptr does not start at 0 or decreases");
+  p->n_rows = n_rows;
+  p->block_dim = T;
+  p->desired_chunk_size = format == ARGCSR_FORMAT_RG ? 0 : desired;
+  p->format = format;
+  p->n_groups = int32_t(box.word[kBoxGroups]);
+  p->n_slots = box.word[kBoxSlots];
+  p->n_heavy = int32_t(box.word[kBoxHeavy]);
+  p->nnz = box.word[kBoxNnz];
+  return ARGCSR_OK;
 }
 
 constexpr int kMaxDevices = 64;
@@ -570,28 +721,34 @@ int convert_impl(int32_t n_rows, int32_t n_cols, const int32_t* row_ptr_host,
   if (fixed) {
     if (!row_ptr_host)
       return fail(ARGCSR_EINVAL, "argcsr_convert_noalloc needs row_ptr_host (step 1 on the host)");
-    const ConvertScratch need = convert_scratch(out->n_groups, out->n_slots, T);
-    if (need.bytes > kNoAllocScratchBytes)
+    // the documented limit: 24 bytes, 16 a thousand groups, the long-row list
+    const size_t need = 24 + 16 * ((size_t(out->n_groups) + 1023) / 1024) +
+                        2 * sizeof(int32_t) * size_t(long_capacity(out->n_slots, T));
+    if (need > kNoAllocScratchBytes)
       return fail(ARGCSR_EINVAL,
                   "the conversion needs %zu bytes of scratch, more than the %zu bytes "
-                  "argcsr_convert_noalloc holds", need.bytes, kNoAllocScratchBytes);
+                  "argcsr_convert_noalloc holds", need, kNoAllocScratchBytes);
   }
   // step 1: on the host from row_ptr_host, or on the device (group.hip)
   std::vector<argcsr_group_info> host_groups;
-  DeviceGrouping device_groups;
+  argcsr_device_plan own_plan;
   int64_t nnz = 0;
   int32_t G = 0;
   bool groups_uploaded = false;
-  if (planned) {
-    // steps 1-3 were kept by argcsr_plan_device_keep
-    if (n_rows > 0 && !row_ptr) return fail(ARGCSR_EINVAL, "row_ptr is NULL");
-    G = planned->n_groups;
+  if (n_rows > 0 && !row_ptr && !row_ptr_host) return fail(ARGCSR_EINVAL, "row_ptr is NULL");
+  if (planned && n_rows > 0 && !row_ptr) return fail(ARGCSR_EINVAL, "row_ptr is NULL");
+  if (!planned && !row_ptr_host) {
     if (n_rows > 0) {
-      int32_t last = 0;
-      ARGCSR_HIP(hipMemcpyAsync(&last, row_ptr + n_rows, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-      ARGCSR_HIP(hipStreamSynchronize(s));
-      nnz = last;
+      rc = build_plan(n_rows, row_ptr, T, out->desired_chunk_size, out->format, out->region_rows,
+                      regions, s, &own_plan);
+      if (rc) return rc;
     }
+    planned = &own_plan;
+  }
+  if (planned) {
+    // steps 1-3 are done (here or by argcsr_plan_device_keep)
+    G = planned->n_groups;
+    nnz = planned->nnz;
   } else if (row_ptr_host && pregrouped) {
     // step 1 done (and row_ptr_host validated) by the caller
     nnz = n_rows > 0 ? row_ptr_host[n_rows] : 0;
@@ -639,18 +796,6 @@ int convert_impl(int32_t n_rows, int32_t n_cols, const int32_t* row_ptr_host,
       if (rc) return rc;
       G = (int32_t)host_groups.size();
     }
-  } else {
-    if (n_rows > 0 && !row_ptr) return fail(ARGCSR_EINVAL, "row_ptr is NULL");
-    rc = device_groups.build(n_rows, row_ptr, T, out->desired_chunk_size, out->format, s,
-                             out->region_rows, regions);
-    if (rc) return rc;
-    G = device_groups.n_groups;
-    if (n_rows > 0) {
-      int32_t last = 0;
-      ARGCSR_HIP(hipMemcpyAsync(&last, row_ptr + n_rows, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-      ARGCSR_HIP(hipStreamSynchronize(s));
-      nnz = last;
-    }
   }
   if (G != out->n_groups)
     return fail(ARGCSR_EINVAL, "out->n_groups = %d but the matrix has %d groups", out->n_groups, G);
@@ -665,77 +810,84 @@ int convert_impl(int32_t n_rows, int32_t n_cols, const int32_t* row_ptr_host,
       (nnz > 0 && (!col || !val)))
     return fail(ARGCSR_EINVAL, "NULL device buffer");
 
-  const ConvertScratch cs = convert_scratch(G, out->n_slots, T);
-  const int32_t n_tiles = cs.n_tiles;
   StreamScratch ws;
   void* base = fixed_ptr;
   if (!fixed) {
-    rc = ws.alloc(cs.bytes, s);
+    rc = ws.alloc(convert_scratch(out->n_slots, T), s);
     if (rc) return rc;
     base = ws.ptr;
   }
   Status* st = static_cast<Status*>(base);
-  int64_t* tile_sums = reinterpret_cast<int64_t*>(st + 1);
-  int64_t* heavy_tiles = tile_sums + n_tiles;
+  auto* share_slots = reinterpret_cast<int64_t*>(static_cast<char*>(base) + kHeadBytes);
+  const int64_t* heavy_parts = share_slots + kChunkBlocks;
   // (group, first step) per tile of the fill's long blocks
-  int32_t* long_list = reinterpret_cast<int32_t*>(heavy_tiles + n_tiles);
+  int32_t* long_list = reinterpret_cast<int32_t*>(share_slots + kChunkBlocks + kScanBlocks);
+  ResultBox box;
+  rc = box.init(fixed ? reinterpret_cast<int64_t*>(st + 1) : nullptr);
+  if (rc) return rc;
   // uses the caller's slot count; it is checked against the device total
   // before anything is written to the caller's heavy_groups buffer
   const int32_t heavy_chunk = out->heavy_chunk;
+  int64_t slots = 0, heavy = 0;
 
-  clear_status_kernel<<<1, 1, 0, s>>>(st);
   if (planned) {
-    copy_words(planned->groups, out->groups, 4 * int64_t(G), s);
-    copy_words(planned->tm, out->threads_mapping, int64_t(n_rows), s);
+    slots = planned->n_slots;
+    heavy = planned->n_heavy;
   } else {
-    if (row_ptr_host) {
-      if (!groups_uploaded)
-        ARGCSR_HIP(hipMemcpyAsync(out->groups, host_groups.data(),
-                                  sizeof(argcsr_group_info) * size_t(G), hipMemcpyHostToDevice,
-                                  s));
-    } else {
-      rc = device_groups.write(out->groups);
-      if (rc) return rc;
-    }
-    const int wave_blocks = (G + kWaves - 1) / kWaves;
-    chunks_kernel<<<wave_blocks, kWaves * 64, 0, s>>>(row_ptr, out->groups, G, T,
-                                                     out->format == ARGCSR_FORMAT_RG ? 1 : 0,
-                                                     out->threads_mapping);
+    clear_words_kernel<<<1, 64, 0, s>>>(static_cast<int32_t*>(base),
+                                        int32_t(kHeadBytes / sizeof(int32_t)));
+    if (!groups_uploaded)
+      ARGCSR_HIP(hipMemcpyAsync(out->groups, host_groups.data(),
+                                sizeof(argcsr_group_info) * size_t(G), hipMemcpyHostToDevice, s));
+    launch_chunks(row_ptr, out->groups, G, nullptr, T, out->format, out->threads_mapping,
+                  share_slots, s);
+    offsets_kernel<<<kScanBlocks, kScanBlock, 0, s>>>(out->groups, G, nullptr, T, share_slots,
+                                                      share_slots + kChunkBlocks, st, row_ptr,
+                                                      n_rows, box.dev);
+    ARGCSR_HIP(hipGetLastError());
+    rc = box.read(s);
+    if (rc) return rc;
+    slots = box.word[kBoxSlots];
+    heavy = box.word[kBoxHeavy];
   }
-  ARGCSR_HIP(hipGetLastError());
-  offsets_reduce_kernel<<<n_tiles, kScanBlock, 0, s>>>(out->groups, G, T, tile_sums);
-  tiles_scan_kernel<<<1, kScanBlock, 0, s>>>(tile_sums, n_tiles, &st->total_slots);
-  offsets_apply_kernel<<<n_tiles, kScanBlock, 0, s>>>(out->groups, G, T, tile_sums);
-  heavy_count_kernel<<<n_tiles, kScanBlock, 0, s>>>(out->groups, G, heavy_chunk, heavy_tiles);
-  tiles_scan_kernel<<<1, kScanBlock, 0, s>>>(heavy_tiles, n_tiles, &st->total_heavy);
-  ARGCSR_HIP(hipGetLastError());
-
-  Status host_st{};
-  ARGCSR_HIP(hipMemcpyAsync(&host_st, st, sizeof(Status), hipMemcpyDeviceToHost, s));
-  ARGCSR_HIP(hipStreamSynchronize(s));
-  if (host_st.total_slots > INT32_MAX)
-    return fail(ARGCSR_EOVERFLOW, "%lld slots exceed INT32_MAX", host_st.total_slots);
-  if (host_st.total_slots != out->n_slots)
+  if (slots > INT32_MAX)
+    return fail(ARGCSR_EOVERFLOW, "%lld slots exceed INT32_MAX", (long long)slots);
+  if (slots != out->n_slots)
     return fail(ARGCSR_EINVAL, "out->n_slots = %lld but the matrix needs %lld",
-                (long long)out->n_slots, host_st.total_slots);
-  if (out->heavy_groups && host_st.total_heavy != out->n_heavy)
+                (long long)out->n_slots, (long long)slots);
+  if (out->heavy_groups && heavy != out->n_heavy)
     return fail(ARGCSR_EINVAL, "out->n_heavy = %d but the matrix has %lld heavy groups",
-                out->n_heavy, host_st.total_heavy);
-  out->n_heavy = int32_t(host_st.total_heavy);
+                out->n_heavy, (long long)heavy);
+  out->n_heavy = int32_t(heavy);
+  if (planned) {
+    heavy_parts = planned->heavy_parts;
+    const int64_t blocks = std::min<int64_t>((4 * int64_t(G) + n_rows + 255) / 256, 2048);
+    adopt_plan_kernel<<<dim3(uint32_t(blocks)), 256, 0, s>>>(
+        reinterpret_cast<const int32_t*>(planned->groups), 4 * int64_t(G), planned->tm, n_rows,
+        reinterpret_cast<int32_t*>(out->groups), out->threads_mapping, st);
+  }
   if (out->heavy_groups && out->n_heavy > 0)
-    heavy_scatter_kernel<<<n_tiles, kScanBlock, 0, s>>>(out->groups, G, heavy_chunk, heavy_tiles,
-                                                        out->heavy_groups);
+    heavy_scatter_kernel<<<kScanBlocks, kScanBlock, 0, s>>>(out->groups, G, heavy_chunk,
+                                                            heavy_parts, out->heavy_groups);
 
   switch (out->dtype) {
-    case ARGCSR_F64: launch_fill<ARGCSR_F64>(G, s, row_ptr, col, val, st, long_list, out); break;
-    case ARGCSR_F32: launch_fill<ARGCSR_F32>(G, s, row_ptr, col, val, st, long_list, out); break;
-    case ARGCSR_BF16: launch_fill<ARGCSR_BF16>(G, s, row_ptr, col, val, st, long_list, out); break;
-    default: launch_fill<ARGCSR_F16>(G, s, row_ptr, col, val, st, long_list, out); break;
+    case ARGCSR_F64:
+      launch_fill<ARGCSR_F64>(G, s, row_ptr, col, val, st, box.dev, long_list, out);
+      break;
+    case ARGCSR_F32:
+      launch_fill<ARGCSR_F32>(G, s, row_ptr, col, val, st, box.dev, long_list, out);
+      break;
+    case ARGCSR_BF16:
+      launch_fill<ARGCSR_BF16>(G, s, row_ptr, col, val, st, box.dev, long_list, out);
+      break;
+    default:
+      launch_fill<ARGCSR_F16>(G, s, row_ptr, col, val, st, box.dev, long_list, out);
+      break;
   }
   ARGCSR_HIP(hipGetLastError());
-  ARGCSR_HIP(hipMemcpyAsync(&host_st, st, sizeof(Status), hipMemcpyDeviceToHost, s));
-  ARGCSR_HIP(hipStreamSynchronize(s));
-  if (host_st.bad_column)
+  rc = box.read(s);
+  if (rc) return rc;
+  if (box.word[kBoxBadColumn])
     return fail(ARGCSR_EINVAL, "a column index lies outside [0, %d)", n_cols);
   return ARGCSR_OK;
 }
@@ -777,12 +929,10 @@ extern "C" int argcsr_convert_noalloc(int32_t n_rows, int32_t n_cols, const int3
 namespace argcsr {
 namespace {
 
-// Steps 1-3 from a device row_ptr; the sizes of the result.  With `keep`,
-// the group table and the threads mapping stay in device memory the plan
-// owns; otherwise they live in stream-ordered scratch and are dropped.
+// Steps 1-3 from a device row_ptr into *p, and the sizes of the result.
 int plan_device_impl(int32_t n_rows, const int32_t* row_ptr, int32_t block_dim,
                      int32_t desired_chunk_size, int32_t format, int32_t* n_groups,
-                     int64_t* n_slots, int32_t* n_heavy, hipStream_t s, argcsr_device_plan* keep) {
+                     int64_t* n_slots, int32_t* n_heavy, hipStream_t s, argcsr_device_plan* p) {
   if (!n_groups || !n_slots) return fail(ARGCSR_EINVAL, "NULL output pointer");
   if (n_rows < 0) return fail(ARGCSR_EINVAL, "n_rows < 0");
   if (format != ARGCSR_FORMAT_ARG && format != ARGCSR_FORMAT_RG)
@@ -792,62 +942,16 @@ int plan_device_impl(int32_t n_rows, const int32_t* row_ptr, int32_t block_dim,
     return fail(ARGCSR_EINVAL, "block_dim must be in [1, %d] and desired_chunk_size >= 1",
                 kMaxBlockDim);
   if (n_rows > 0 && !row_ptr) return fail(ARGCSR_EINVAL, "row_ptr is NULL");
-  DeviceGrouping dg;
-  int rc = dg.build(n_rows, row_ptr, block_dim, desired_chunk_size, format, s);
-  if (rc) return rc;
-  const int32_t G = dg.n_groups;
-  *n_groups = G;
-  *n_slots = 0;
-  if (n_heavy) *n_heavy = 0;
-  if (G == 0) return ARGCSR_OK;
-  // steps 2-3 (into the plan's buffers or scratch): the chunk sizes give the
-  // slot count and the heavy-group count exactly as argcsr_plan computes
-  // them on the host
-  const int32_t n_tiles = (G + kScanTile - 1) / kScanTile;
-  const size_t groups_bytes = sizeof(argcsr_group_info) * size_t(G);
-  const size_t tm_bytes = (sizeof(int32_t) * size_t(n_rows) + 15) / 16 * 16;
-  StreamScratch ws;
-  rc = ws.alloc(groups_bytes + tm_bytes + sizeof(Status) + 2 * sizeof(int64_t) * size_t(n_tiles), s);
-  if (rc) return rc;
-  argcsr_group_info* groups = static_cast<argcsr_group_info*>(ws.ptr);
-  int32_t* tm = reinterpret_cast<int32_t*>(static_cast<char*>(ws.ptr) + groups_bytes);
-  if (keep) {                    // the plan takes the scratch over at the end (groups and mapping first)
-    keep->stream = s;
-    keep->groups = groups;
-    keep->tm = tm;
+  if (n_rows > 0) {
+    const int rc = build_plan(n_rows, row_ptr, block_dim, desired_chunk_size, format, 0, nullptr,
+                              s, p);
+    if (rc) return rc;
   }
-  auto* st = reinterpret_cast<Status*>(static_cast<char*>(ws.ptr) + groups_bytes + tm_bytes);
-  int64_t* tile_sums = reinterpret_cast<int64_t*>(st + 1);
-  int64_t* heavy_tiles = tile_sums + n_tiles;
-  clear_status_kernel<<<1, 1, 0, s>>>(st);
-  rc = dg.write(groups);
-  if (rc) return rc;
-  const int wave_blocks = (G + kWaves - 1) / kWaves;
-  chunks_kernel<<<wave_blocks, kWaves * 64, 0, s>>>(row_ptr, groups, G, block_dim,
-                                                   format == ARGCSR_FORMAT_RG ? 1 : 0, tm);
-  offsets_reduce_kernel<<<n_tiles, kScanBlock, 0, s>>>(groups, G, block_dim, tile_sums);
-  tiles_scan_kernel<<<1, kScanBlock, 0, s>>>(tile_sums, n_tiles, &st->total_slots);
-  ARGCSR_HIP(hipGetLastError());
-  Status host_st{};
-  ARGCSR_HIP(hipMemcpyAsync(&host_st, st, sizeof(Status), hipMemcpyDeviceToHost, s));
-  ARGCSR_HIP(hipStreamSynchronize(s));
-  const int64_t S = host_st.total_slots;
-  const int32_t heavy_chunk = heavy_chunk_for(block_dim, S, G);
-  heavy_count_kernel<<<n_tiles, kScanBlock, 0, s>>>(groups, G, heavy_chunk, heavy_tiles);
-  tiles_scan_kernel<<<1, kScanBlock, 0, s>>>(heavy_tiles, n_tiles, &st->total_heavy);
-  ARGCSR_HIP(hipGetLastError());
-  ARGCSR_HIP(hipMemcpyAsync(&host_st, st, sizeof(Status), hipMemcpyDeviceToHost, s));
-  ARGCSR_HIP(hipStreamSynchronize(s));
-  *n_slots = S;
-  if (n_heavy) *n_heavy = int32_t(host_st.total_heavy);
-  if (keep) {
-    keep->block = ws.ptr;        // owned by the plan now (freed with it)
-    ws.ptr = nullptr;
-    keep->n_groups = G;
-    keep->n_slots = S;
-    keep->n_heavy = int32_t(host_st.total_heavy);
-  }
-  if (S > INT32_MAX) return fail(ARGCSR_EOVERFLOW, "%lld slots exceed INT32_MAX", (long long)S);
+  *n_groups = p->n_groups;
+  *n_slots = p->n_slots;
+  if (n_heavy) *n_heavy = p->n_heavy;
+  if (p->n_slots > INT32_MAX)
+    return fail(ARGCSR_EOVERFLOW, "%lld slots exceed INT32_MAX", (long long)p->n_slots);
   return ARGCSR_OK;
 }
 
@@ -858,9 +962,10 @@ extern "C" int argcsr_plan_device(int32_t n_rows, const int32_t* row_ptr, int32_
                                   int32_t desired_chunk_size, int32_t format, int32_t* n_groups,
                                   int64_t* n_slots, int32_t* n_heavy, void* stream) {
   argcsr::clear_error();
+  argcsr_device_plan p;
   return argcsr::plan_device_impl(n_rows, row_ptr, block_dim, desired_chunk_size, format,
                                   n_groups, n_slots, n_heavy, static_cast<hipStream_t>(stream),
-                                  nullptr);
+                                  &p);
 }
 
 extern "C" int argcsr_plan_device_keep(int32_t n_rows, const int32_t* row_ptr, int32_t block_dim,

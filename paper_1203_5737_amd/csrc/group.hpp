@@ -1,5 +1,5 @@
-// Conversion step 1 (grouping) on the GPU: binary lifting over the
-// next-group-start function of the rows (group.hip).
+// Conversion step 1 (grouping) on the GPU (group.hip), and the library's
+// stream-ordered device scratch.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -10,30 +10,27 @@
 
 namespace argcsr {
 
-// The grouping of one matrix while its jump tables live (stream-ordered
-// scratch on the stream given to build).  build() validates row_ptr on the
-// device and counts the groups (synchronous: it reads the count back);
-// write() enqueues the group table (first_row, size; offset and chunk size
-// 0) into `groups`, which holds n_groups entries; release() frees the
-// tables in stream order.
-struct DeviceGrouping {
-  int32_t n_rows = 0;
-  int32_t n_groups = 0;
-  int32_t levels_n = 0;
-  int64_t stride = 0;
-  int32_t* levels = nullptr;
-  hipStream_t stream = nullptr;
+// Rows a workgroup of the grouping kernels handles.
+constexpr int kGroupRows = 4096;
 
-  // format ARGCSR_FORMAT_RG: groups of block_dim rows (no nonzero budget);
-  // region_desired (host, checked by the caller): a desiredChunkSize per
-  // region of region_rows rows, taken from the region of a group's first row
-  int build(int32_t n, const int32_t* row_ptr, int32_t block_dim, int32_t desired,
-            int32_t format, hipStream_t s, int32_t region_rows = 0,
-            const int32_t* region_desired = nullptr);
-  int write(argcsr_group_info* groups) const;
-  void release();
-  ~DeviceGrouping() { release(); }
+// Device words the grouping writes for the kernels after it.
+struct GroupCount {
+  int32_t n_groups;
+  int32_t bad;           // row_ptr does not start at 0 or decreases
 };
+
+// Enqueues the grouping of n > 0 rows: `groups` (room for n entries) gets
+// first_row and size of every group (offset and chunk size 0), *count the
+// number of groups and whether row_ptr is malformed (the groups then still
+// cover the rows, each at most block_dim of them), and the `clear_words`
+// 32-bit words at `clear` are set to 0.  block_dim in [1, 1024].
+// format ARGCSR_FORMAT_RG: groups of block_dim rows (no nonzero budget);
+// region_desired (host, checked by the caller): a desiredChunkSize per region
+// of region_rows rows, taken from the region of a group's first row.
+int group_on_device(int32_t n, const int32_t* row_ptr, int32_t block_dim, int32_t desired,
+                    int32_t format, int32_t region_rows, const int32_t* region_desired,
+                    argcsr_group_info* groups, GroupCount* count, int32_t* clear,
+                    int64_t clear_words, hipStream_t s);
 
 // Stream-ordered device allocation from the library's own memory pool on
 // the current device (created on first use, one per device, with a release

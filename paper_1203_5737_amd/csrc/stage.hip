@@ -86,12 +86,7 @@ __device__ __forceinline__ void block_min_max(int& mn, int& mx, int* red) {
 template <int NT>
 __device__ __forceinline__ int block_excl_max(int v, int* red, int* all) {
   const int lane = lane_id();
-  int incl = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int t = __shfl_up(incl, d, 64);
-    if (lane >= d) incl = t > incl ? t : incl;
-  }
+  const int incl = wave_inclusive_max(v);
   int before = __shfl_up(incl, 1, 64);
   if (lane == 0) before = -1;
   if constexpr (NT == 64) {

@@ -253,6 +253,39 @@ def test_device_grouping_edge_cases(ac):
                            device_grouping=True)
 
 
+# device grouping works in blocks of 4096 rows, entered in one of their first
+# T rows, and composes 28672/T (at most 1024) blocks' maps at a time; rows of
+# these kinds open groups of T rows, of one row, of two, and of varying many
+GROUPING_ROWS = {
+    "empty": lambda n, T: np.zeros(n, np.int64),
+    "long": lambda n, T: np.full(n, 2 * T, np.int64),
+    "pairs": lambda n, T: np.full(n, max(1, T // 2), np.int64),
+    "mixed": lambda n, T: np.random.default_rng(n).integers(0, 12, n),
+}
+
+
+@pytest.mark.parametrize("kind", sorted(GROUPING_ROWS))
+@pytest.mark.parametrize("n,T", [(4095, 64), (4096, 64), (4097, 64), (8192 + 63, 64),
+                                 (4096 + 1023, 1024), (28 * 4096, 1024), (28 * 4096 + 1, 1024),
+                                 (114_000, 1000), (448 * 4096 + 5, 64), (9000, 1),
+                                 (1024 * 4096 + 4097, 7)])
+def test_device_grouping_blocks(ac, kind, n, T):
+    L = GROUPING_ROWS[kind](n, T)
+    rp = np.concatenate([[0], np.cumsum(L)]).astype(np.int32)
+    rpd = torch.from_numpy(rp).to(DEV)
+    for fmt in (ac.FORMAT_ARG, ac.FORMAT_RG):
+        assert ac.plan_device(rpd, T, 1, fmt=fmt) == ac.plan(rp, T, 1, fmt)
+
+
+@pytest.mark.parametrize("n", [16383, 16384, 16385, 40_000])
+def test_default_conversion_around_its_grouping_rule(ac, n):
+    """convert() groups small matrices on the host and larger ones on the
+    device; both give the oracle's bytes."""
+    A = csr_from_lengths(np.random.default_rng(n).integers(0, 9, n), 500, n)
+    compare_conversion(ac, A, 64, 1, oracle.F64)
+    compare_conversion(ac, A, 128, 3, oracle.F32, fmt=ac.FORMAT_RG)
+
+
 def test_device_grouping_random(ac):
     rng = np.random.default_rng(42)
     for i in range(30):
