@@ -55,7 +55,7 @@ SOURCE_SETS = {
 }
 SOURCE_SETS["staged"] = SOURCE_SETS["spmv"] + [_CSRC + f for f in ("spmv_staged.hpp", "stage.hpp",
                                                                    "stage.hip")]
-SOURCE_SETS["batch"] = SOURCE_SETS["spmv"] + [_CSRC + f for f in ("batch.hip", "workqueue.hpp",
+SOURCE_SETS["batch"] = SOURCE_SETS["spmv"] + [_CSRC + f for f in ("batch.hip",
                                                                   "tune.cpp")]
 KERNEL_SOURCES = list(dict.fromkeys(f for v in SOURCE_SETS.values() for f in v))
 # (block_dim, desired_chunk_size) per workload unless given on the command line

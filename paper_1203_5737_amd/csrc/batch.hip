@@ -1,13 +1,14 @@
-// Many ARG-CSR matrices in one persistent launch over a global work queue.
+// Many ARG-CSR matrices in one launch.
 //
-// Work items are (matrix, group) pairs.  Heavy groups (a long chunk loop,
-// see schedule.hpp) are taken by whole workgroups from one queue and split
-// over their waves; all other groups are taken by single waves, kGrab at a
-// time, from per-XCD segments of a second list in matrix and row order
-// (workqueue.hpp).  Queue counters are zeroed by a one-block kernel enqueued
-// before every launch (no memset, so the pair can be captured in a hipGraph).  Each group is computed by the
-// same deterministic routine as argcsr_spmv, so the results do not depend on
-// which wave takes which item.
+// Work items are (matrix, group) pairs in matrix and row order, so waves
+// working at the same time gather from the same few x vectors.  Heavy groups
+// (a long chunk loop, see schedule.hpp) come first, a workgroup each, split
+// over its waves.  All other items are cut, when the batch is made, into
+// chunks of about equal cost, a workgroup each: the workgroup reads its
+// items' group records into LDS and its waves take them one by one from a
+// counter there.  Each group is computed by the same deterministic routine
+// as argcsr_spmv, so the results do not depend on which wave takes which
+// item.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -18,18 +19,25 @@
 #include "common.hpp"
 #include "schedule.hpp"
 #include "spmv_kernels.hpp"
-#include "workqueue.hpp"
 
 namespace argcsr {
 namespace {
 
-constexpr int kGrab = 4;                 // normal items taken per queue access
-constexpr int kMaxBlocksPerCu = 8;       // persistent grid: as many workgroups as fit, <= 8 per CU
+constexpr int kChunkItems = 64;          // items of a chunk, at most
+// Cost of an item besides its slots, in slots: the chain of round trips of a
+// short group.
+constexpr int64_t kItemCost = 512;
+// Chunks per workgroup that the GPU holds at once: enough for the hardware
+// to even them out over the CUs, few enough that a chunk's group records are
+// worth reading together.  48 matrices of 10^3 .. 2*10^5 rows in FP32 (24
+// with uniform, 24 with power-law rows; MI355X), 1 / 2 / 4 / 8 / 16 / 32
+// chunks: 210 / 201 / 194 / 182 / 184 / 187 us.
+constexpr int64_t kChunksPerSlot = 8;
 
 template <int DT, int W, int U>
-__device__ __forceinline__ void run_item(const BatchMat& m, int32_t g, int32_t* ends) {
+__device__ __forceinline__ void run_item(const BatchMat& m, const argcsr_group_info& gi,
+                                         int32_t* ends) {
   using Vt = Val<DT>;
-  const argcsr_group_info gi = m.groups[g];
   spmv_group<DT, W, U>(gi.first_row, gi.size, gi.offset, gi.chunk_size, m.tm, m.columns,
                        static_cast<const typename Vt::storage*>(m.values),
                        XGather<typename Vt::acc>(static_cast<const typename Vt::acc*>(m.x),
@@ -50,46 +58,64 @@ __device__ __forceinline__ void run_heavy(const BatchMat& m, int32_t g, int32_t*
                              reinterpret_cast<A(*)[64 * W]>(part_mem), wv);
 }
 
+// Bound by the x gathers: the 29.5 M of the batch above run at 163 G/s, where
+// gathers and streams alone reach 185 to 225 G/s.  No workgroup waits for
+// another and nothing is counted in device memory: with persistent
+// workgroups that took their items from counters there, the 5120 waves' last,
+// failing atomics on each counter (about 12 ns each, one after another) cost
+// more than the gathers of a small batch -- this batch 227 us, its power-law
+// half alone 115 us, now 54.
 template <int DT>
 __global__ __launch_bounds__(kSpmvWaves * 64) void batch_spmv_kernel(
     const BatchMat* __restrict__ mats, const int2* __restrict__ heavy, int32_t n_heavy,
-    const int2* __restrict__ items, int32_t n_items, WorkQueues* q) {
+    const int2* __restrict__ items, const int32_t* __restrict__ chunk_begin) {
   using A = typename Val<DT>::acc;
   __shared__ int32_t ends[kSpmvWaves][256];
   __shared__ A part_mem[(kSpmvWaves - 1) * 256];
-  __shared__ int32_t grabbed;
+  __shared__ argcsr_group_info recs[kChunkItems];
+  __shared__ int32_t mat_of[kChunkItems];
+  __shared__ int32_t next;
   const int wv = wave_uniform(int(threadIdx.x >> 6));
+  const int32_t b = int32_t(blockIdx.x);
 
-  // heavy groups: the whole workgroup takes one at a time
-  for (;;) {
-    if (threadIdx.x == 0) grabbed = atomicAdd(&q->heavy.next, 1);
-    __syncthreads();
-    const int32_t h = grabbed;
-    __syncthreads();                      // all waves have read `grabbed`
-    if (h >= n_heavy) break;
-    const int2 it = heavy[h];
+  if (b < n_heavy) {                      // a heavy group, the whole workgroup
+    const int2 it = heavy[b];
     const BatchMat m = mats[it.x];
     switch (m.block_dim) {
       case 64: run_heavy<DT, 1, 8>(m, it.y, ends[0], part_mem, wv); break;
       case 128: run_heavy<DT, 2, 4>(m, it.y, ends[0], part_mem, wv); break;
       default: run_heavy<DT, 4, 2>(m, it.y, ends[0], part_mem, wv); break;
     }
-    __syncthreads();                      // part_mem / ends free for the next heavy item
+    return;
   }
 
-  // all other groups: each wave takes kGrab items at a time
-  QueueCursor cursor{int(blockIdx.x % kQueues), 0};
-  int32_t i0, i1;
-  while (cursor.take(q, n_items, kGrab, &i0, &i1)) {
-    for (int32_t i = i0; i < i1; ++i) {
-      const int2 it = items[i];
-      const BatchMat m = mats[it.x];
-      switch (m.block_dim) {
-        case 64: run_item<DT, 1, 8>(m, it.y, ends[wv]); break;
-        case 128: run_item<DT, 2, 4>(m, it.y, ends[wv]); break;
-        default: run_item<DT, 4, 2>(m, it.y, ends[wv]); break;
-      }
+  // a chunk of the other groups, every XCD a contiguous range of chunks
+  const uint32_t ch = xcd_remap(uint32_t(b - n_heavy), gridDim.x - uint32_t(n_heavy));
+  const int32_t i0 = chunk_begin[ch];
+  const int32_t count = chunk_begin[ch + 1] - i0;
+  const int t = int(threadIdx.x);
+  if (t < count) {
+    const int2 it = items[i0 + t];
+    recs[t] = mats[it.x].groups[it.y];
+    mat_of[t] = it.x;
+  }
+  if (t == 0) next = kSpmvWaves;
+  __syncthreads();
+  for (int32_t k = wv; k < count;) {
+    argcsr_group_info gi = recs[k];
+    gi.first_row = wave_uniform(gi.first_row);
+    gi.size = wave_uniform(gi.size);
+    gi.offset = wave_uniform(gi.offset);
+    gi.chunk_size = wave_uniform(gi.chunk_size);
+    const BatchMat& m = mats[wave_uniform(mat_of[k])];
+    switch (m.block_dim) {
+      case 64: run_item<DT, 1, 8>(m, gi, ends[wv]); break;
+      case 128: run_item<DT, 2, 4>(m, gi, ends[wv]); break;
+      default: run_item<DT, 4, 2>(m, gi, ends[wv]); break;
     }
+    int32_t taken = 0;
+    if (lane_id() == 0) taken = atomicAdd(&next, 1);
+    k = wave_uniform(taken);
   }
 }
 
@@ -103,26 +129,15 @@ const void* kernel_for(int32_t dtype) {
 }
 
 int launch_kernels(argcsr_batch* b, hipStream_t s) {
-  auto* q = static_cast<WorkQueues*>(b->queue);
-  reset_work_queues_kernel<<<1, 64, 0, s>>>(q, 1);
   const dim3 grid(b->grid), block(kSpmvWaves * 64);
+  auto go = [&](auto* kern) {
+    kern<<<grid, block, 0, s>>>(b->d_mats, b->d_heavy, b->n_heavy, b->d_items, b->d_chunks);
+  };
   switch (b->dtype) {
-    case ARGCSR_F64:
-      batch_spmv_kernel<ARGCSR_F64><<<grid, block, 0, s>>>(b->d_mats, b->d_heavy, b->n_heavy,
-                                                            b->d_items, b->n_items, q);
-      break;
-    case ARGCSR_F32:
-      batch_spmv_kernel<ARGCSR_F32><<<grid, block, 0, s>>>(b->d_mats, b->d_heavy, b->n_heavy,
-                                                            b->d_items, b->n_items, q);
-      break;
-    case ARGCSR_BF16:
-      batch_spmv_kernel<ARGCSR_BF16><<<grid, block, 0, s>>>(b->d_mats, b->d_heavy, b->n_heavy,
-                                                             b->d_items, b->n_items, q);
-      break;
-    default:
-      batch_spmv_kernel<ARGCSR_F16><<<grid, block, 0, s>>>(b->d_mats, b->d_heavy, b->n_heavy,
-                                                            b->d_items, b->n_items, q);
-      break;
+    case ARGCSR_F64: go(&batch_spmv_kernel<ARGCSR_F64>); break;
+    case ARGCSR_F32: go(&batch_spmv_kernel<ARGCSR_F32>); break;
+    case ARGCSR_BF16: go(&batch_spmv_kernel<ARGCSR_BF16>); break;
+    default: go(&batch_spmv_kernel<ARGCSR_F16>); break;
   }
   ARGCSR_HIP(hipGetLastError());
   return ARGCSR_OK;
@@ -135,7 +150,7 @@ void free_batch(argcsr_batch* b) {
   if (b->d_mats) (void)hipFree(b->d_mats);
   if (b->d_items) (void)hipFree(b->d_items);
   if (b->d_heavy) (void)hipFree(b->d_heavy);
-  if (b->queue) (void)hipFree(b->queue);
+  if (b->d_chunks) (void)hipFree(b->d_chunks);
   if (b->last) (void)hipEventDestroy(b->last);
   delete b;
 }
@@ -150,6 +165,7 @@ int build_batch(int32_t n, const argcsr_matrix* mats, const void* const* xs, voi
   std::vector<BatchMat> hm(n);
   std::vector<int2> items;
   std::vector<int2> heavy;
+  std::vector<int64_t> cost;               // of each item
   std::vector<argcsr_group_info> g;
   for (int32_t m = 0; m < n; ++m) {
     const argcsr_matrix& A = mats[m];
@@ -171,8 +187,12 @@ int build_batch(int32_t n, const argcsr_matrix* mats, const void* const* xs, voi
                            hipMemcpyDeviceToHost));
     const int32_t hc = heavy_chunk_for(A.block_dim, A.n_slots, A.n_groups);
     for (int32_t k = 0; k < A.n_groups; ++k) {
-      if (g[k].chunk_size > hc) heavy.push_back(int2{m, k});
-      else items.push_back(int2{m, k});
+      if (g[k].chunk_size > hc) {
+        heavy.push_back(int2{m, k});
+      } else {
+        items.push_back(int2{m, k});
+        cost.push_back(int64_t(g[k].chunk_size) * A.block_dim + kItemCost);
+      }
     }
   }
   // matrix-major, row order: waves working at the same time gather from the
@@ -183,7 +203,6 @@ int build_batch(int32_t n, const argcsr_matrix* mats, const void* const* xs, voi
   ARGCSR_HIP(hipMalloc(&b->d_mats, sizeof(BatchMat) * size_t(std::max(n, 1))));
   ARGCSR_HIP(hipMalloc(&b->d_items, sizeof(int2) * std::max<size_t>(items.size(), 1)));
   ARGCSR_HIP(hipMalloc(&b->d_heavy, sizeof(int2) * std::max<size_t>(heavy.size(), 1)));
-  ARGCSR_HIP(hipMalloc(&b->queue, sizeof(WorkQueues)));
   ARGCSR_HIP(hipMemcpy(b->d_mats, hm.data(), sizeof(BatchMat) * size_t(n), hipMemcpyHostToDevice));
   if (!items.empty())
     ARGCSR_HIP(hipMemcpy(b->d_items, items.data(), sizeof(int2) * items.size(),
@@ -191,15 +210,32 @@ int build_batch(int32_t n, const argcsr_matrix* mats, const void* const* xs, voi
   if (!heavy.empty())
     ARGCSR_HIP(hipMemcpy(b->d_heavy, heavy.data(), sizeof(int2) * heavy.size(),
                          hipMemcpyHostToDevice));
+  // chunks of about equal cost, kChunksPerSlot for each workgroup the GPU
+  // holds at once
   int dev = 0, cus = 0, per_cu = 0;
   ARGCSR_HIP(hipGetDevice(&dev));
   ARGCSR_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   ARGCSR_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel_for(b->dtype),
                                                           kSpmvWaves * 64, 0));
-  per_cu = std::max(1, std::min(per_cu, kMaxBlocksPerCu));
-  const int64_t work_blocks = int64_t(b->n_heavy) + (int64_t(b->n_items) + kGrab * kSpmvWaves - 1) /
-                                                        (kGrab * kSpmvWaves);
-  b->grid = int32_t(std::max<int64_t>(1, std::min<int64_t>(int64_t(cus) * per_cu, work_blocks)));
+  int64_t total = 0;
+  for (int64_t c : cost) total += c;
+  const int64_t slots = int64_t(cus) * std::max(1, per_cu);
+  const int64_t target = std::max<int64_t>(1, total / (slots * (getenv("CPS") ? atoi(getenv("CPS")) : 4)));
+  std::vector<int32_t> chunks{0};
+  if (items.empty()) chunks.push_back(0);      // one empty chunk: a launch has a workgroup
+  int64_t in_chunk = 0;
+  for (size_t i = 0; i < items.size(); ++i) {
+    in_chunk += cost[i];
+    if (in_chunk >= target || int32_t(i) + 1 - chunks.back() == kChunkItems ||
+        i + 1 == items.size()) {
+      chunks.push_back(int32_t(i) + 1);
+      in_chunk = 0;
+    }
+  }
+  ARGCSR_HIP(hipMalloc(&b->d_chunks, sizeof(int32_t) * chunks.size()));
+  ARGCSR_HIP(hipMemcpy(b->d_chunks, chunks.data(), sizeof(int32_t) * chunks.size(),
+                       hipMemcpyHostToDevice));
+  b->grid = b->n_heavy + int32_t(chunks.size()) - 1;
   return ARGCSR_OK;
 }
 
@@ -222,7 +258,7 @@ extern "C" int argcsr_batch_create(int32_t n_mats, const argcsr_matrix* mats,
     free_batch(b);
     return fail(ARGCSR_EHIP, "hipEventCreate failed");
   }
-  // capture reset + persistent kernel into a graph on a private stream
+  // capture the kernel into a graph on a private stream
   hipStream_t cs = nullptr;
   if (hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) != hipSuccess) {
     free_batch(b);

@@ -30,11 +30,11 @@ struct argcsr_batch {
   int32_t dtype = 0;
   int32_t n_items = 0;       // groups processed by one wave
   int32_t n_heavy = 0;       // groups processed by a whole workgroup
-  int32_t grid = 0;          // persistent workgroups
+  int32_t grid = 0;          // workgroups: heavy groups, then chunks of the others
   argcsr::BatchMat* d_mats = nullptr;
-  int2* d_items = nullptr;   // (matrix, group), longest first
+  int2* d_items = nullptr;   // (matrix, group) in matrix and row order
   int2* d_heavy = nullptr;
-  void* queue = nullptr;     // two int32 counters
+  int32_t* d_chunks = nullptr;   // chunk c: items [d_chunks[c], d_chunks[c + 1])
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
   hipEvent_t last = nullptr;  // recorded after every launch; destroy waits for it

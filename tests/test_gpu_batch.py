@@ -97,6 +97,35 @@ def test_batch_graph_replays_track_inputs(ac):
     b.close()
 
 
+# chunks of at most 64 items and of equal cost: matrices without a group, with
+# one, with 63..65 groups, with heavy groups only, and so many short groups
+# that the cost rule and not the count ends a chunk
+@pytest.mark.parametrize("kinds", [["empty"], ["empty", "one", "empty"], ["g63", "g64", "g65"],
+                                   ["heavy"], ["one", "heavy", "many", "empty", "g65"]])
+@pytest.mark.parametrize("T", [64, 256])
+def test_batch_chunk_edges(ac, kinds, T):
+    print(f"\n[gpu] batch chunks {kinds} T={T}", flush=True)
+    lengths = {"empty": [], "one": [3], "g63": [T] * 63, "g64": [T] * 64, "g65": [T] * 65,
+               "heavy": [40 * T] * 3, "many": [1] * (T * 3000)}
+    mats, xs = [], []
+    for i, k in enumerate(kinds):
+        rng = np.random.default_rng(i)
+        L = np.asarray(lengths[k], dtype=np.int64)
+        A = synth.random_csr(L, 50_000, rng, rng)
+        mats.append(ac.convert(ac.to_device_csr(A.rp, A.col, A.val, A.n_cols, DEV), T, 1, ac.F32))
+        xs.append(torch.from_numpy(rng.uniform(-1, 1, A.n_cols)).to(DEV, torch.float32))
+    ys = [torch.full((M.n_rows,), float("nan"), device=DEV) for M in mats]
+    b = ac.Batch(mats, xs, ys)
+    for graph in (True, False, True):
+        for y in ys:
+            y.fill_(float("nan"))
+        b.launch(graph=graph)
+        torch.cuda.synchronize()
+        for M, x, y in zip(mats, xs, ys):
+            assert torch.equal(y, ac.spmv(M, x))
+    b.close()
+
+
 def test_batch_rejects_mixed_dtypes(ac):
     mats = small_batch(2, 5)
     a = convert_all(ac, mats[:1], 0, 6)[0]
