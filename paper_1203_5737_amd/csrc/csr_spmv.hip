@@ -7,8 +7,8 @@
 // Binned variant (still plain CSR, no other storage): the rows are grouped
 // by length once (argcsr_csr_bin_rows: bin k < 7 holds the rows of at most
 // 2^k nonzeros and more than 2^(k-1), bin 7 the longer ones), and one launch
-// gives each bin its own width: 2^k lanes per row, a whole 256-lane
-// workgroup per row of bin 7.  A row of bin k < 7 is summed exactly as by
+// gives each bin its own width: 2^k lanes per row, and for bin 7 a wave per
+// row of up to 1024 nonzeros, a 256-lane workgroup per longer row.  A row of bin k < 7 is summed exactly as by
 // the uniform kernel with V = 2^k.
 #include <hip/hip_runtime.h>
 
@@ -22,7 +22,41 @@ namespace argcsr {
 namespace {
 
 constexpr int kCsrBlock = 256;
+constexpr int kWaveRow = 1024;              // bin 7: longest row of one wave
 constexpr int kBins = ARGCSR_CSR_BINS;      // 8: widths 1, 2, 4, ..., 64, then a workgroup
+
+// sum plus fma(val, x[col], ...) over elements k, k + stride, ... below end, in that
+// order, U of them loaded at a time: a long row is not one chain of column,
+// x and sum after the other.  STREAM: the elements are read once and by this
+// wave alone (non-temporal loads: L2 stays for x).
+template <int DT, int U, bool STREAM>
+__device__ __forceinline__ typename Val<DT>::acc strided_sum(
+    int32_t k, int32_t end, int32_t stride, const int32_t* __restrict__ col,
+    const typename Val<DT>::storage* __restrict__ val,
+    const typename Val<DT>::acc* __restrict__ x, typename Val<DT>::acc sum = 0) {
+  using Vt = Val<DT>;
+  using A = typename Vt::acc;
+  for (; end - k > (U - 1) * stride; k += U * stride) {
+    int32_t c[U];
+    typename Vt::storage v[U];
+    A xv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      c[u] = STREAM ? __builtin_nontemporal_load(col + k + u * stride) : col[k + u * stride];
+      v[u] = STREAM ? __builtin_nontemporal_load(val + k + u * stride) : val[k + u * stride];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) xv[u] = x[c[u]];
+#pragma unroll
+    for (int u = 0; u < U; ++u) sum = __builtin_fma(Vt::load(v[u]), xv[u], sum);
+  }
+  for (; k < end; k += stride) {
+    const int32_t c = STREAM ? __builtin_nontemporal_load(col + k) : col[k];
+    const typename Vt::storage v = STREAM ? __builtin_nontemporal_load(val + k) : val[k];
+    sum = __builtin_fma(Vt::load(v), x[c], sum);
+  }
+  return sum;
+}
 
 // Sum of row `row` by V consecutive lanes; lane `sub` of the row strides
 // through its nonzeros, then a butterfly over the V lanes.
@@ -31,14 +65,9 @@ __device__ __forceinline__ typename Val<DT>::acc csr_row_sum(
     int64_t row, bool valid, int sub, const int32_t* __restrict__ rp,
     const int32_t* __restrict__ col, const typename Val<DT>::storage* __restrict__ val,
     const typename Val<DT>::acc* __restrict__ x) {
-  using Vt = Val<DT>;
-  using A = typename Vt::acc;
+  using A = typename Val<DT>::acc;
   A sum = A(0);
-  if (valid) {
-    const int32_t begin = rp[row], end = rp[row + 1];
-    for (int32_t k = begin + sub; k < end; k += V)
-      sum = __builtin_fma(Vt::load(val[k]), x[col[k]], sum);
-  }
+  if (valid) sum = strided_sum<DT, 4, false>(rp[row] + sub, rp[row + 1], V, col, val, x);
 #pragma unroll
   for (int d = V / 2; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
   return sum;
@@ -64,12 +93,29 @@ __host__ __device__ __forceinline__ int row_bin(int32_t L) {
   return k;
 }
 
+// Workgroups of a binned launch.  Bin 7's come first (its rows take longest).
+// Those of the other bins are dealt out in `regions`: region g holds the g-th
+// of `regions` equal shares of every bin's rows -- rows ascend within a bin, so
+// these lie close together in the matrix -- and each XCD takes an eighth of the
+// regions, one after another.  Then the cache lines that hold rows of several
+// bins are read by one XCD, while they are in its L2, and not once per bin
+// (power-law rows of 10^6, FP64: 105 us with the bins one after another, 90
+// so).  Any bins that cover the rows give the
+// right result; only the speed depends on how they lie.
 struct BinLaunch {
   int32_t row_start[kBins + 1];     // bin k's rows: rows[row_start[k] .. row_start[k+1])
-  int32_t block_start[kBins + 1];   // bin k's workgroups: [block_start[k], block_start[k+1])
+  int32_t blocks[kBins];            // workgroups of bin k
+  int32_t per[kBins - 1];           // at most, in one region
+  int32_t per_region;               // sum of per
+  int32_t log2_regions;             // a power of two, at least the XCD count
+  int32_t long_blocks;              // bin 7's, rounded up to a multiple of the XCD count
 };
+constexpr int kXcds = 8, kLog2Xcds = 3;
+constexpr int kRegionBlocks = 64;   // workgroups of a region, about
 
-template <int DT, int V>
+// Workgroup b of bin k: each team of V lanes sums R rows, their loads in
+// flight together.
+template <int DT, int V, int R>
 __device__ __forceinline__ void binned_rows(const BinLaunch& bl, int k, int32_t b,
                                             const int32_t* __restrict__ rows,
                                             const int32_t* __restrict__ rp,
@@ -77,52 +123,120 @@ __device__ __forceinline__ void binned_rows(const BinLaunch& bl, int k, int32_t 
                                             const typename Val<DT>::storage* __restrict__ val,
                                             const typename Val<DT>::acc* __restrict__ x,
                                             typename Val<DT>::acc* __restrict__ y) {
-  constexpr int kRowsPerBlock = kCsrBlock / V;
+  using Vt = Val<DT>;
+  using A = typename Vt::acc;
+  constexpr int kTeams = kCsrBlock / V;
   const int sub = threadIdx.x % V;
-  const int64_t i = int64_t(b - bl.block_start[k]) * kRowsPerBlock + threadIdx.x / V;
-  const bool valid = i < bl.row_start[k + 1] - bl.row_start[k];
-  const int64_t row = valid ? rows[bl.row_start[k] + i] : 0;
-  const auto sum = csr_row_sum<DT, V>(row, valid, sub, rp, col, val, x);
-  if (valid && sub == 0) y[row] = sum;
+  const int32_t* list = rows + bl.row_start[k];
+  const int32_t n = bl.row_start[k + 1] - bl.row_start[k];
+  const int64_t i0 = int64_t(b) * (kTeams * R) + threadIdx.x / V;
+  int32_t row[R], at[R], end[R], c[R];
+  typename Vt::storage v[R];
+  A xv[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) row[r] = i0 + r * kTeams < n ? list[i0 + r * kTeams] : -1;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    at[r] = row[r] >= 0 ? rp[row[r]] + sub : 0;
+    end[r] = row[r] >= 0 ? rp[row[r] + 1] : 0;
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const bool has = at[r] < end[r];
+    c[r] = has ? col[at[r]] : -1;
+    v[r] = has ? val[at[r]] : typename Vt::storage(0);
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) xv[r] = c[r] >= 0 ? x[c[r]] : A(0);
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    A sum = A(0);
+    if (c[r] >= 0) sum = __builtin_fma(Vt::load(v[r]), xv[r], sum);
+    // rows of bin k have at most V nonzeros; bins made for another matrix
+    // may hold longer ones
+    if (end[r] - at[r] > V) sum = strided_sum<DT, 1, false>(at[r] + V, end[r], V, col, val, x, sum);
+#pragma unroll
+    for (int d = V / 2; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
+    if (row[r] >= 0 && sub == 0) y[row[r]] = sum;
+  }
 }
 
-template <int DT>
+// Bound by the x gathers on power-law rows and by the CSR stream on regular
+// ones.  MI355X: power-law rows of 10^6 FP64 125 us -> 90 (long rows first and
+// loaded eight elements at a time a lane 105, regions 90), 27-point stencil
+// 100^3 FP64 171 -> 105.
+template <int DT, int R>
 __global__ __launch_bounds__(kCsrBlock) void csr_binned_kernel(
     BinLaunch bl, const int32_t* __restrict__ rows, const int32_t* __restrict__ rp,
     const int32_t* __restrict__ col, const typename Val<DT>::storage* __restrict__ val,
     const typename Val<DT>::acc* __restrict__ x, typename Val<DT>::acc* __restrict__ y) {
-  using Vt = Val<DT>;
-  using A = typename Vt::acc;
-  const int32_t b = int32_t(blockIdx.x);
-  int k = 0;
-  while (k < kBins - 1 && b >= bl.block_start[k + 1]) ++k;
+  using A = typename Val<DT>::acc;
+  constexpr int kBlockWaves = kCsrBlock / 64;
+  int k = kBins - 1;
+  int32_t b = int32_t(blockIdx.x);
+  if (b >= bl.long_blocks) {
+    b -= bl.long_blocks;
+    const uint32_t q = uint32_t(b) / kXcds;      // of this XCD's workgroups
+    const uint32_t mine = q / uint32_t(bl.per_region);
+    const uint32_t region = uint32_t(b % kXcds) * (1u << (bl.log2_regions - kLog2Xcds)) + mine;
+    int32_t j = int32_t(q - mine * uint32_t(bl.per_region));
+    for (k = kBins - 2; k > 0 && j >= bl.per[k]; --k) j -= bl.per[k];
+    const int32_t first = int32_t(uint64_t(uint32_t(bl.blocks[k])) * region >> bl.log2_regions);
+    const int32_t last = int32_t(uint64_t(uint32_t(bl.blocks[k])) * (region + 1) >> bl.log2_regions);
+    b = first + j;
+    if (b >= last) return;
+  } else if (b >= bl.blocks[k]) {
+    return;
+  }
   switch (k) {
-    case 0: binned_rows<DT, 1>(bl, k, b, rows, rp, col, val, x, y); return;
-    case 1: binned_rows<DT, 2>(bl, k, b, rows, rp, col, val, x, y); return;
-    case 2: binned_rows<DT, 4>(bl, k, b, rows, rp, col, val, x, y); return;
-    case 3: binned_rows<DT, 8>(bl, k, b, rows, rp, col, val, x, y); return;
-    case 4: binned_rows<DT, 16>(bl, k, b, rows, rp, col, val, x, y); return;
-    case 5: binned_rows<DT, 32>(bl, k, b, rows, rp, col, val, x, y); return;
-    case 6: binned_rows<DT, 64>(bl, k, b, rows, rp, col, val, x, y); return;
+    case 0: binned_rows<DT, 1, R>(bl, k, b, rows, rp, col, val, x, y); return;
+    case 1: binned_rows<DT, 2, R>(bl, k, b, rows, rp, col, val, x, y); return;
+    case 2: binned_rows<DT, 4, R>(bl, k, b, rows, rp, col, val, x, y); return;
+    case 3: binned_rows<DT, 8, R>(bl, k, b, rows, rp, col, val, x, y); return;
+    case 4: binned_rows<DT, 16, R>(bl, k, b, rows, rp, col, val, x, y); return;
+    case 5: binned_rows<DT, 32, R>(bl, k, b, rows, rp, col, val, x, y); return;
+    case 6: binned_rows<DT, 64, R>(bl, k, b, rows, rp, col, val, x, y); return;
     default: break;
   }
-  // bin 7: the workgroup's 256 lanes stride through one row; wave sums
-  // added in wave order
-  __shared__ A part[kCsrBlock / 64];
-  const int64_t row = rows[bl.row_start[kBins - 1] + (b - bl.block_start[kBins - 1])];
-  A sum = A(0);
-  const int32_t begin = rp[row], end = rp[row + 1];
-  for (int32_t k2 = begin + int32_t(threadIdx.x); k2 < end; k2 += kCsrBlock)
-    sum = __builtin_fma(Vt::load(val[k2]), x[col[k2]], sum);
+  // bin 7: four rows, a wave each where the row is short enough for one
+  // (512, 1024 and 4096 measured within 3% on power-law rows); the others by
+  // the workgroup's 256 lanes together, wave sums added in wave order
+  __shared__ A part[kBlockWaves];
+  const int wv = wave_uniform(int(threadIdx.x >> 6));
+  const int lane = lane_id();
+  const int32_t i0 = bl.row_start[k] + b * kBlockWaves;
+  const int32_t n = min(kBlockWaves, bl.row_start[k + 1] - i0);
+  int32_t row[kBlockWaves], begin[kBlockWaves], end[kBlockWaves];
 #pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    A t = part[0];
+  for (int q = 0; q < kBlockWaves; ++q) row[q] = q < n ? rows[i0 + q] : -1;
 #pragma unroll
-    for (int w = 1; w < kCsrBlock / 64; ++w) t += part[w];
-    y[row] = t;
+  for (int q = 0; q < kBlockWaves; ++q) {
+    begin[q] = q < n ? rp[row[q]] : 0;
+    end[q] = q < n ? rp[row[q] + 1] : 0;
+  }
+#pragma unroll
+  for (int q = 0; q < kBlockWaves; ++q) {
+    if (q != wv || q >= n || end[q] - begin[q] > kWaveRow) continue;
+    A sum = strided_sum<DT, 8, true>(begin[q] + lane, end[q], 64, col, val, x);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
+    if (lane == 0) y[row[q]] = sum;
+  }
+#pragma unroll
+  for (int q = 0; q < kBlockWaves; ++q) {
+    if (end[q] - begin[q] <= kWaveRow) continue;             // the same for all waves
+    A sum = strided_sum<DT, 8, true>(begin[q] + int32_t(threadIdx.x), end[q], kCsrBlock, col, val, x);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
+    if (lane == 0) part[wv] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      A t = part[0];
+#pragma unroll
+      for (int w = 1; w < kBlockWaves; ++w) t += part[w];
+      y[row[q]] = t;
+    }
+    __syncthreads();
   }
 }
 
@@ -228,11 +342,31 @@ extern "C" int argcsr_csr_spmv(int32_t n_rows, int32_t n_cols, int64_t nnz,
 namespace argcsr {
 namespace {
 
+// Rows of a team: four where one bin holds at least half of the workgroups
+// (at one row a team) -- rows of about one length -- and else one.  Four rows'
+// loads in flight hide the chain of list, offsets, element and x: FP64
+// 27-point stencil 100^3 171 us before, 190 with one, 134 with two, 105 with
+// four; uniform 5..50 nonzeros 56 / 55 / 50 / 49.  But rows of mixed lengths
+// share cache lines across bins (see BinLaunch), and four times the rows in
+// flight no longer fit the XCD's 4-MB L2: power-law rows of 10^6, FP64, 90 /
+// 95 / 101 us with one, two, four.
+int team_rows(const int32_t* bin_start) {
+  int64_t most = 0, all = 0;
+  for (int k = 0; k < kBins - 1; ++k) {
+    const int64_t blocks = ((int64_t(bin_start[k + 1]) - bin_start[k]) << k) / kCsrBlock;
+    most = blocks > most ? blocks : most;
+    all += blocks;
+  }
+  return 2 * most >= all ? 4 : 1;
+}
+
 template <int DT>
-void launch_binned(const BinLaunch& bl, int32_t blocks, const int32_t* rows, const int32_t* rp,
-                   const int32_t* col, const void* val, const void* x, void* y, hipStream_t s) {
+void launch_binned(const BinLaunch& bl, int team, int32_t blocks, const int32_t* rows,
+                   const int32_t* rp, const int32_t* col, const void* val, const void* x, void* y,
+                   hipStream_t s) {
   using Vt = Val<DT>;
-  csr_binned_kernel<DT><<<blocks, kCsrBlock, 0, s>>>(
+  auto* kern = team == 4 ? &csr_binned_kernel<DT, 4> : &csr_binned_kernel<DT, 1>;
+  kern<<<blocks, kCsrBlock, 0, s>>>(
       bl, rows, rp, col, static_cast<const typename Vt::storage*>(val),
       static_cast<const typename Vt::acc*>(x), static_cast<typename Vt::acc*>(y));
 }
@@ -298,29 +432,39 @@ extern "C" int argcsr_csr_spmv_binned(int32_t n_rows, int32_t n_cols, int64_t nn
   if (!bin_start) return fail(ARGCSR_EINVAL, "bin_start is NULL");
   if (bin_start[0] != 0 || bin_start[kBins] != n_rows)
     return fail(ARGCSR_EINVAL, "bin_start does not cover the %d rows", n_rows);
-  BinLaunch bl{};
-  int64_t blocks = 0;
-  for (int k = 0; k < kBins; ++k) {
+  for (int k = 0; k < kBins; ++k)
     if (bin_start[k + 1] < bin_start[k]) return fail(ARGCSR_EINVAL, "bin_start decreases");
+  const int team = team_rows(bin_start);
+  BinLaunch bl{};
+  int64_t blocks = 0;                 // of the bins but the last
+  for (int k = 0; k < kBins; ++k) {
     bl.row_start[k] = bin_start[k];
-    bl.block_start[k] = int32_t(blocks);
     const int64_t cnt = bin_start[k + 1] - bin_start[k];
-    const int64_t per = k < kBins - 1 ? kCsrBlock / (1 << k) : 1;     // rows per workgroup
-    blocks += (cnt + per - 1) / per;
+    const int64_t per = k < kBins - 1 ? team * (kCsrBlock >> k) : kCsrBlock / 64;  // rows per workgroup
+    bl.blocks[k] = int32_t((cnt + per - 1) / per);
+    if (k < kBins - 1) blocks += bl.blocks[k];
   }
   bl.row_start[kBins] = bin_start[kBins];
-  bl.block_start[kBins] = int32_t(blocks);
+  bl.long_blocks = (bl.blocks[kBins - 1] + kXcds - 1) / kXcds * kXcds;
+  bl.log2_regions = kLog2Xcds;
+  while ((int64_t(kRegionBlocks) << bl.log2_regions) < blocks) ++bl.log2_regions;
+  for (int k = 0; k < kBins - 1; ++k) {
+    bl.per[k] = int32_t((int64_t(bl.blocks[k]) + (1 << bl.log2_regions) - 1) >> bl.log2_regions);
+    bl.per_region += bl.per[k];
+  }
+  if (bl.per_region < 1) bl.per_region = 1;      // (no division by 0; nothing to do)
+  const int64_t grid = bl.long_blocks + (blocks > 0 ? int64_t(bl.per_region) << bl.log2_regions : 0);
   if (n_rows == 0) return ARGCSR_OK;
   if (!row_ptr || !rows || !x || !y || (nnz > 0 && (!col || !val)))
     return fail(ARGCSR_EINVAL, "NULL device buffer");
   if (x == y) return fail(ARGCSR_EINVAL, "y must not alias x");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int32_t nb = int32_t(blocks);
+  const int32_t nb = int32_t(grid);
   switch (dtype) {
-    case ARGCSR_F64: launch_binned<ARGCSR_F64>(bl, nb, rows, row_ptr, col, val, x, y, s); break;
-    case ARGCSR_F32: launch_binned<ARGCSR_F32>(bl, nb, rows, row_ptr, col, val, x, y, s); break;
-    case ARGCSR_BF16: launch_binned<ARGCSR_BF16>(bl, nb, rows, row_ptr, col, val, x, y, s); break;
-    default: launch_binned<ARGCSR_F16>(bl, nb, rows, row_ptr, col, val, x, y, s); break;
+    case ARGCSR_F64: launch_binned<ARGCSR_F64>(bl, team, nb, rows, row_ptr, col, val, x, y, s); break;
+    case ARGCSR_F32: launch_binned<ARGCSR_F32>(bl, team, nb, rows, row_ptr, col, val, x, y, s); break;
+    case ARGCSR_BF16: launch_binned<ARGCSR_BF16>(bl, team, nb, rows, row_ptr, col, val, x, y, s); break;
+    default: launch_binned<ARGCSR_F16>(bl, team, nb, rows, row_ptr, col, val, x, y, s); break;
   }
   ARGCSR_HIP(hipGetLastError());
   return ARGCSR_OK;

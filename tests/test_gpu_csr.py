@@ -105,6 +105,48 @@ def test_binned_full_powerlaw_and_stencil(ac):
         check_f64(A, x, y.cpu().numpy())
 
 
+# launches of every make-up: one bin alone (teams of four rows), bins of about
+# equal work (teams of one), bin 7 around the 1024 nonzeros of one wave, fewer
+# rows than a workgroup or a region holds, and remainders
+@pytest.mark.parametrize("lengths", ["one_bin", "equal_bins", "long", "few", "odd"])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_binned_launch_shapes(ac, lengths, dtype):
+    rng = np.random.default_rng(5)
+    L = {"one_bin": rng.integers(17, 33, 20_011),
+         "equal_bins": np.repeat([1, 2, 4, 8, 16, 32, 64], 40_000 >> np.arange(7)),
+         "long": np.array([65, 1023, 1024, 1025, 64, 1026, 2049, 0, 3000, 70, 4000]),
+         "few": np.array([3, 0, 1]),
+         "odd": rng.integers(0, 130, 1537)}[lengths].astype(np.int64)
+    rng.shuffle(L)
+    A = synth.random_csr(L, 6000, rng, rng)
+    x = rng.uniform(-1.0, 1.0, A.n_cols)
+    if dtype == 1:
+        x = x.astype(np.float32).astype(np.float64)
+    dev = ac.to_device_csr(A.rp, A.col, A.val, A.n_cols, DEV)
+    xd = torch.from_numpy(x).to(DEV, ac.vector_dtype(dtype))
+    vals = dev.val if dtype == 0 else stored_values(ac, A, dtype)
+    y = ac.csr_spmv_binned(dev, xd, ac.csr_bins(dev), values=vals, dtype=dtype)
+    yn = y.cpu().numpy().astype(np.float64)
+    if dtype == 0:
+        check_f64(A, x, yn)
+    else:
+        check_reduced(A, x, yn, dtype)
+
+
+def test_bins_of_another_matrix_still_cover_the_rows(ac):
+    """Bins are a partition of the rows: a matrix whose rows have other
+    lengths than the ones they were made from gives the right result too."""
+    rng = np.random.default_rng(6)
+    L = rng.integers(0, 90, 3000).astype(np.int64)
+    A = synth.random_csr(L, 4000, rng, rng)
+    B = synth.random_csr(L[::-1].copy(), 4000, rng, rng)
+    x = rng.uniform(-1.0, 1.0, 4000)
+    bins = ac.csr_bins(ac.to_device_csr(A.rp, A.col, A.val, A.n_cols, DEV))
+    dev = ac.to_device_csr(B.rp, B.col, B.val, B.n_cols, DEV)
+    y = ac.csr_spmv_binned(dev, torch.from_numpy(x).to(DEV), bins)
+    check_f64(B, x, y.cpu().numpy())
+
+
 def test_binned_edge_cases(ac):
     E = synth.Csr(0, 0, np.zeros(1, np.int32), np.zeros(0, np.int32), np.zeros(0))
     dev = ac.to_device_csr(E.rp, E.col, E.val, 0, DEV)
