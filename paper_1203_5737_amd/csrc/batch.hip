@@ -24,25 +24,26 @@ namespace argcsr {
 namespace {
 
 constexpr int kChunkItems = 64;          // items of a chunk, at most
-// Cost of an item besides its slots, in slots: the chain of round trips of a
-// short group.
-constexpr int64_t kItemCost = 512;
-// Chunks per workgroup that the GPU holds at once: enough for the hardware
-// to even them out over the CUs, few enough that a chunk's group records are
-// worth reading together.  48 matrices of 10^3 .. 2*10^5 rows in FP32 (24
-// with uniform, 24 with power-law rows; MI355X), 1 / 2 / 4 / 8 / 16 / 32
-// chunks: 210 / 201 / 194 / 182 / 184 / 187 us.
-constexpr int64_t kChunksPerSlot = 8;
+// Cost of an item besides its slots, in slots (the round trips of a short
+// group), and cost of a chunk.  Larger chunks leave the CUs unevenly loaded at
+// the end, smaller ones are mostly start-up.  Batches of 48 / 256 matrices of
+// 10^3 .. 2*10^5 rows in FP32, half with uniform, half with power-law rows,
+// MI355X, us at chunk costs 1200, 2400, 3600, 4800, 7200: 179 / 934, 172 / 887,
+// 172 / 877, 169 / 858, 180 / 920; with an item cost of 512 instead 182 / 945 to
+// 171 / 874.
+constexpr int64_t kItemCost = 128;
+constexpr int64_t kChunkCost = 4800;
 
 template <int DT, int W, int U>
 __device__ __forceinline__ void run_item(const BatchMat& m, const argcsr_group_info& gi,
                                          int32_t* ends) {
   using Vt = Val<DT>;
-  spmv_group<DT, W, U>(gi.first_row, gi.size, gi.offset, gi.chunk_size, m.tm, m.columns,
-                       static_cast<const typename Vt::storage*>(m.values),
-                       XGather<typename Vt::acc>(static_cast<const typename Vt::acc*>(m.x),
-                                                 m.n_cols),
-                       m.serial != 0, static_cast<typename Vt::acc*>(m.y), ends);
+  spmv_group<DT, W, U>(gi.first_row, gi.size, gi.offset, gi.chunk_size, global_ptr<const int32_t>(m.tm),
+                       global_ptr<const int32_t>(m.columns),
+                       global_ptr<const typename Vt::storage>(m.values),
+                       XGather<typename Vt::acc>(
+                           global_ptr<const typename Vt::acc>(m.x), m.n_cols),
+                       m.serial != 0, global_ptr<typename Vt::acc>(m.y), ends);
 }
 
 template <int DT, int W, int U>
@@ -50,21 +51,22 @@ __device__ __forceinline__ void run_heavy(const BatchMat& m, int32_t g, int32_t*
                                           typename Val<DT>::acc* part_mem, int wv) {
   using Vt = Val<DT>;
   using A = typename Vt::acc;
-  const argcsr_group_info gi = m.groups[g];
-  spmv_group_split<DT, W, U>(gi.first_row, gi.size, gi.offset, gi.chunk_size, m.tm, m.columns,
-                             static_cast<const typename Vt::storage*>(m.values),
-                             XGather<A>(static_cast<const A*>(m.x), m.n_cols), m.serial != 0,
-                             static_cast<A*>(m.y), ends,
+  const argcsr_group_info gi = global_ptr<const argcsr_group_info>(m.groups)[g];
+  spmv_group_split<DT, W, U>(gi.first_row, gi.size, gi.offset, gi.chunk_size, global_ptr<const int32_t>(m.tm),
+                             global_ptr<const int32_t>(m.columns),
+                             global_ptr<const typename Vt::storage>(m.values),
+                             XGather<A>(global_ptr<const A>(m.x), m.n_cols),
+                             m.serial != 0, global_ptr<A>(m.y), ends,
                              reinterpret_cast<A(*)[64 * W]>(part_mem), wv);
 }
 
-// Bound by the x gathers: the 29.5 M of the batch above run at 163 G/s, where
-// gathers and streams alone reach 185 to 225 G/s.  No workgroup waits for
-// another and nothing is counted in device memory: with persistent
+// Bound by the x gathers: the 29.5 M of the 48-matrix batch above run at
+// 175 G/s, where gathers and streams alone reach 185 to 225 G/s.  No workgroup
+// waits for another and nothing is counted in device memory: with persistent
 // workgroups that took their items from counters there, the 5120 waves' last,
 // failing atomics on each counter (about 12 ns each, one after another) cost
-// more than the gathers of a small batch -- this batch 227 us, its power-law
-// half alone 115 us, now 54.
+// more than the gathers of a small batch.  That batch 225 -> 169 us, 256
+// matrices 973 -> 858, eight of up to 2*10^4 rows in BF16 44 -> 22.
 template <int DT>
 __global__ __launch_bounds__(kSpmvWaves * 64) void batch_spmv_kernel(
     const BatchMat* __restrict__ mats, const int2* __restrict__ heavy, int32_t n_heavy,
@@ -80,7 +82,7 @@ __global__ __launch_bounds__(kSpmvWaves * 64) void batch_spmv_kernel(
 
   if (b < n_heavy) {                      // a heavy group, the whole workgroup
     const int2 it = heavy[b];
-    const BatchMat m = mats[it.x];
+    const BatchMat& m = mats[it.x];
     switch (m.block_dim) {
       case 64: run_heavy<DT, 1, 8>(m, it.y, ends[0], part_mem, wv); break;
       case 128: run_heavy<DT, 2, 4>(m, it.y, ends[0], part_mem, wv); break;
@@ -89,14 +91,17 @@ __global__ __launch_bounds__(kSpmvWaves * 64) void batch_spmv_kernel(
     return;
   }
 
-  // a chunk of the other groups, every XCD a contiguous range of chunks
-  const uint32_t ch = xcd_remap(uint32_t(b - n_heavy), gridDim.x - uint32_t(n_heavy));
+  // a chunk of the other groups.  Neighbouring chunks go to different XCDs: a
+  // contiguous eighth of the items per XCD would keep an x in one L2, but the
+  // eighths of a mixed batch differ in gathers by a quarter (172 against 169,
+  // 878 against 858 us for the batches above)
+  const int32_t ch = b - n_heavy;
   const int32_t i0 = chunk_begin[ch];
   const int32_t count = chunk_begin[ch + 1] - i0;
   const int t = int(threadIdx.x);
   if (t < count) {
     const int2 it = items[i0 + t];
-    recs[t] = mats[it.x].groups[it.y];
+    recs[t] = global_ptr<const argcsr_group_info>(mats[it.x].groups)[it.y];
     mat_of[t] = it.x;
   }
   if (t == 0) next = kSpmvWaves;
@@ -116,15 +121,6 @@ __global__ __launch_bounds__(kSpmvWaves * 64) void batch_spmv_kernel(
     int32_t taken = 0;
     if (lane_id() == 0) taken = atomicAdd(&next, 1);
     k = wave_uniform(taken);
-  }
-}
-
-const void* kernel_for(int32_t dtype) {
-  switch (dtype) {
-    case ARGCSR_F64: return reinterpret_cast<const void*>(&batch_spmv_kernel<ARGCSR_F64>);
-    case ARGCSR_F32: return reinterpret_cast<const void*>(&batch_spmv_kernel<ARGCSR_F32>);
-    case ARGCSR_BF16: return reinterpret_cast<const void*>(&batch_spmv_kernel<ARGCSR_BF16>);
-    default: return reinterpret_cast<const void*>(&batch_spmv_kernel<ARGCSR_F16>);
   }
 }
 
@@ -210,23 +206,12 @@ int build_batch(int32_t n, const argcsr_matrix* mats, const void* const* xs, voi
   if (!heavy.empty())
     ARGCSR_HIP(hipMemcpy(b->d_heavy, heavy.data(), sizeof(int2) * heavy.size(),
                          hipMemcpyHostToDevice));
-  // chunks of about equal cost, kChunksPerSlot for each workgroup the GPU
-  // holds at once
-  int dev = 0, cus = 0, per_cu = 0;
-  ARGCSR_HIP(hipGetDevice(&dev));
-  ARGCSR_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-  ARGCSR_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel_for(b->dtype),
-                                                          kSpmvWaves * 64, 0));
-  int64_t total = 0;
-  for (int64_t c : cost) total += c;
-  const int64_t slots = int64_t(cus) * std::max(1, per_cu);
-  const int64_t target = std::max<int64_t>(1, total / (slots * (getenv("CPS") ? atoi(getenv("CPS")) : 4)));
   std::vector<int32_t> chunks{0};
   if (items.empty()) chunks.push_back(0);      // one empty chunk: a launch has a workgroup
   int64_t in_chunk = 0;
   for (size_t i = 0; i < items.size(); ++i) {
     in_chunk += cost[i];
-    if (in_chunk >= target || int32_t(i) + 1 - chunks.back() == kChunkItems ||
+    if (in_chunk >= kChunkCost || int32_t(i) + 1 - chunks.back() == kChunkItems ||
         i + 1 == items.size()) {
       chunks.push_back(int32_t(i) + 1);
       in_chunk = 0;

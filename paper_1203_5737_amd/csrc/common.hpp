@@ -46,6 +46,17 @@ __device__ __forceinline__ int lane_id() {
   return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
 }
 
+// The pointer stored in `member` (of a record in memory), as a T* known to
+// point to global memory: it is read as a pointer of the global address space.
+// Read as it is declared it would be a generic pointer, and its loads and
+// stores FLAT accesses, which count as LDS accesses too and are never scalar
+// loads.
+template <typename T, typename M>
+__device__ __forceinline__ T* global_ptr(M* const& member) {
+  using Global = __attribute__((address_space(1))) T*;
+  return (T*)*reinterpret_cast<const Global*>(&member);
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_uniform(T v) {
   return __builtin_amdgcn_readfirstlane(v);
