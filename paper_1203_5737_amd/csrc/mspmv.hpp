@@ -2,8 +2,7 @@
 // prefix tables instead of a per-group work list: the first total_heavy
 // workgroups take heavy item h = heavy_groups_m[h - heavy_begin[m]] each,
 // and then wave i of the rest takes group i - group_begin[m] of the matrix m
-// with group_begin[m] <= i < group_begin[m+1].  The prefix tables are staged
-// in LDS once per workgroup and searched there.  Used by the serving loop,
+// with group_begin[m] <= i < group_begin[m+1].  Used by the serving loop,
 // whose set of matrices changes from step to step: the grid is sized on the
 // host for each step, so no wave takes work from a shared counter.
 #pragma once
@@ -34,15 +33,20 @@ struct MatWork {
   int32_t heavy_begin;
 };
 
-// largest m in [0, n) with begin[m] <= i (begin[0] == 0, begin non-decreasing)
-__device__ __forceinline__ int32_t find_owner(const int32_t* begin, int32_t n, int32_t i) {
-  int32_t lo = 0, hi = n - 1;
-  while (lo < hi) {
-    const int32_t mid = (lo + hi + 1) >> 1;
-    if (begin[mid] <= i) lo = mid;
-    else hi = mid - 1;
+// The largest m in [0, n) with begin of m <= i (the first begin is 0, they do
+// not decrease), by the whole wave: lane m looks at matrix m, 64 at a time.
+// One round trip; a copy of the prefix in LDS, searched there, cost a
+// barrier and a chain of LDS reads more per wave.
+__device__ __forceinline__ int32_t find_owner(const MatWork* __restrict__ mw,
+                                              int32_t MatWork::* begin, int32_t n, int32_t i) {
+  int32_t owner = 0;
+  for (int32_t m0 = 0; m0 < n; m0 += 64) {
+    const int32_t m = m0 + lane_id();
+    const uint64_t at_or_before = __ballot(m < n && mw[m < n ? m : 0].*begin <= i);
+    if (at_or_before == 0) break;
+    owner = m0 + 63 - __clzll((long long)at_or_before);
   }
-  return lo;
+  return owner;
 }
 
 // All matrices of a launch share T = 64*W (the server converts with one
@@ -53,40 +57,34 @@ __global__ __launch_bounds__(kSpmvWaves * 64) void mspmv_kernel(
   using Vt = Val<DT>;
   using S = typename Vt::storage;
   using A = typename Vt::acc;
-  __shared__ int32_t gbeg[kMaxLaunchMats];
-  __shared__ int32_t hbeg[kMaxLaunchMats];
   __shared__ int32_t ends[kSpmvWaves][64 * W];
   __shared__ A part_mem[kSpmvWaves - 1][64 * W];
-  for (int32_t m = threadIdx.x; m < n_mats; m += blockDim.x) {
-    gbeg[m] = mw[m].group_begin;
-    hbeg[m] = mw[m].heavy_begin;
-  }
-  __syncthreads();
   const int wv = wave_uniform(int(threadIdx.x >> 6));
   const int32_t b = int32_t(blockIdx.x);
 
   if (b < total_heavy) {                            // a heavy group, the whole workgroup
-    const int32_t m = find_owner(hbeg, n_mats, b);
+    const int32_t m = find_owner(mw, &MatWork::heavy_begin, n_mats, b);
     const MatWork& w = mw[m];
-    const argcsr_group_info gi = w.groups[w.heavy[b - hbeg[m]]];
-    spmv_group_split<DT, W, U>(gi.first_row, gi.size, gi.offset, gi.chunk_size, w.tm, w.columns,
-                               static_cast<const S*>(w.values),
-                               XGather<A>(static_cast<const A*>(w.x), w.n_cols), w.serial != 0,
-                               static_cast<A*>(w.y), ends[0], part_mem, wv);
+    const argcsr_group_info gi = global_ptr<const argcsr_group_info>(w.groups)[global_ptr<const int32_t>(w.heavy)[b - w.heavy_begin]];
+    spmv_group_split<DT, W, U>(gi.first_row, gi.size, gi.offset, gi.chunk_size, global_ptr<const int32_t>(w.tm),
+                               global_ptr<const int32_t>(w.columns),
+                               global_ptr<const S>(w.values),
+                               XGather<A>(global_ptr<const A>(w.x), w.n_cols), w.serial != 0,
+                               global_ptr<A>(w.y), ends[0], part_mem, wv);
     return;
   }
   // the other groups, one wave each, every XCD a contiguous range of them
   const uint32_t nb = gridDim.x - uint32_t(total_heavy);
   const int32_t i = int32_t(xcd_remap(uint32_t(b - total_heavy), nb)) * kSpmvWaves + wv;
   if (i >= total_groups) return;
-  const int32_t m = find_owner(gbeg, n_mats, i);
+  const int32_t m = find_owner(mw, &MatWork::group_begin, n_mats, i);
   const MatWork& w = mw[m];
-  const argcsr_group_info gi = w.groups[i - gbeg[m]];
+  const argcsr_group_info gi = global_ptr<const argcsr_group_info>(w.groups)[i - w.group_begin];
   if (gi.chunk_size > w.heavy_chunk) return;        // done by a heavy workgroup
-  spmv_group<DT, W, U>(gi.first_row, gi.size, gi.offset, gi.chunk_size, w.tm, w.columns,
-                       static_cast<const S*>(w.values),
-                       XGather<A>(static_cast<const A*>(w.x), w.n_cols), w.serial != 0,
-                       static_cast<A*>(w.y), ends[wv]);
+  spmv_group<DT, W, U>(gi.first_row, gi.size, gi.offset, gi.chunk_size, global_ptr<const int32_t>(w.tm), global_ptr<const int32_t>(w.columns),
+                       global_ptr<const S>(w.values),
+                       XGather<A>(global_ptr<const A>(w.x), w.n_cols), w.serial != 0,
+                       global_ptr<A>(w.y), ends[wv]);
 }
 
 }  // namespace argcsr

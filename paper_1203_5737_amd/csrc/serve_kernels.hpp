@@ -23,6 +23,8 @@
 
 #include <cstdint>
 
+#include "common.hpp"
+
 namespace argcsr {
 
 constexpr int kVecBlock = 256;
@@ -70,28 +72,69 @@ __device__ __forceinline__ bool cg_skip(const CgVec& w, const CgScalars* sc) {
   return w.pass > 1 && sc[w.slot].stop[w.pass - 1] != 0;
 }
 
-// Fixed-order block sum: each thread's values in index order, then a
-// tree over the 256 threads.
+// This workgroup's request.
+__device__ __forceinline__ CgVec cg_request(const CgVec* __restrict__ v,
+                                            const int32_t* __restrict__ tile_req) {
+  const CgVec& in = v[tile_req[blockIdx.x]];
+  return CgVec{global_ptr<const double>(in.b), global_ptr<double>(in.x),
+               global_ptr<double>(in.r),       global_ptr<double>(in.p),
+               global_ptr<double>(in.d),       global_ptr<const double>(in.q64),
+               global_ptr<float>(in.p32),      global_ptr<const float>(in.q32),
+               in.n, in.phase, in.tile_begin, in.slot, in.parity, in.pass, in.stop_rr};
+}
+
+// Fixed-order block sum: a tree over the 256 threads' values, t + 128, + 64,
+// ... + 1 apart.  The first wave adds its four quarters in the tree's order
+// and goes on by shuffles, so the tree costs two barriers.  `red` holds
+// kVecBlock values and may be reused after the caller's next barrier.
 __device__ __forceinline__ double block_sum(double v, double* red) {
-  red[threadIdx.x] = v;
+  const int t = int(threadIdx.x);
+  red[t] = v;
   __syncthreads();
+  if (t < 64) {
+    double s = (red[t] + red[t + 128]) + (red[t + 64] + red[t + 192]);
 #pragma unroll
-  for (int s = kVecBlock / 2; s > 0; s >>= 1) {
-    if (int(threadIdx.x) < s) red[threadIdx.x] = red[threadIdx.x] + red[threadIdx.x + s];
-    __syncthreads();
+    for (int d = 32; d > 0; d >>= 1) s = s + __shfl_down(s, d, 64);
+    if (t == 0) red[0] = s;
   }
+  __syncthreads();
   return red[0];
+}
+
+// Element k of this thread in a tile, and the tile's loads: every element of a
+// tile is loaded before the first is used or stored.  Loads that follow a
+// store to another of the request's vectors wait for it in turn, which made a
+// tile eight round trips long.  On the eight solves of a burst (670 000 rows
+// in all, MI355X) dot, update and direction took 6.5, 10.2 and 6.8 us, now
+// 3.9, 7.6 and 5.9; update moves 30 MB and direction 19, mostly from the
+// Infinity Cache.  Past the end of the vector the last element is loaded and
+// not used.
+__device__ __forceinline__ int32_t tile_element(int32_t base, int k) {
+  return base + k * kVecBlock + int32_t(threadIdx.x);
+}
+template <typename T>
+__device__ __forceinline__ void load_tile(const T* __restrict__ v, int32_t base, int32_t n,
+                                          T (&out)[kVecPerThread]) {
+#pragma unroll
+  for (int k = 0; k < kVecPerThread; ++k) {
+    const int32_t i = tile_element(base, k);
+    out[k] = v[i < n ? i : n - 1];
+  }
 }
 
 // x += d for requests entering the outer phase (before the FP64 SpMV reads x).
 static __global__ __launch_bounds__(kVecBlock) void cg_pre_kernel(const CgVec* __restrict__ v,
                                                           const int32_t* __restrict__ tile_req) {
-  const CgVec w = v[tile_req[blockIdx.x]];
+  const CgVec w = cg_request(v, tile_req);
   if (w.phase != kPhaseOuter) return;
   const int32_t base = (int32_t(blockIdx.x) - w.tile_begin) * kTile;
+  double x[kVecPerThread], d[kVecPerThread];
+  load_tile(w.x, base, w.n, x);
+  load_tile(w.d, base, w.n, d);
+#pragma unroll
   for (int k = 0; k < kVecPerThread; ++k) {
-    const int32_t i = base + k * kVecBlock + int32_t(threadIdx.x);
-    if (i < w.n) w.x[i] = w.x[i] + w.d[i];
+    const int32_t i = tile_element(base, k);
+    if (i < w.n) w.x[i] = x[k] + d[k];
   }
 }
 
@@ -101,14 +144,17 @@ static __global__ __launch_bounds__(kVecBlock) void cg_dot_kernel(const CgVec* _
                                                           const CgScalars* __restrict__ sc,
                                                           double* __restrict__ partial) {
   __shared__ double red[kVecBlock];
-  const CgVec w = v[tile_req[blockIdx.x]];
+  const CgVec w = cg_request(v, tile_req);
   if (w.phase != kPhaseInner || cg_skip(w, sc)) return;
   const int32_t base = (int32_t(blockIdx.x) - w.tile_begin) * kTile;
+  double p[kVecPerThread];
+  float q[kVecPerThread];
+  load_tile(w.p, base, w.n, p);
+  load_tile(w.q32, base, w.n, q);
   double s = 0.0;
-  for (int k = 0; k < kVecPerThread; ++k) {
-    const int32_t i = base + k * kVecBlock + int32_t(threadIdx.x);
-    if (i < w.n) s = __builtin_fma(w.p[i], double(w.q32[i]), s);
-  }
+#pragma unroll
+  for (int k = 0; k < kVecPerThread; ++k)
+    if (tile_element(base, k) < w.n) s = __builtin_fma(p[k], double(q[k]), s);
   s = block_sum(s, red);
   if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
@@ -137,12 +183,19 @@ static __global__ __launch_bounds__(kVecBlock) void cg_update_kernel(const CgVec
                                                              const double* __restrict__ pq_partial,
                                                              double* __restrict__ rr_partial) {
   __shared__ double red[kVecBlock];
-  const CgVec w = v[tile_req[blockIdx.x]];
+  const CgVec w = cg_request(v, tile_req);
   if (cg_skip(w, sc)) return;                       // uniform: one request per workgroup
   const int32_t local = int32_t(blockIdx.x) - w.tile_begin;
   const int32_t base = local * kTile;
   double s = 0.0;
   if (w.phase == kPhaseInner) {
+    // the vectors do not wait for the sums
+    double p[kVecPerThread], d[kVecPerThread], r[kVecPerThread];
+    float q[kVecPerThread];
+    load_tile(w.p, base, w.n, p);
+    load_tile(w.d, base, w.n, d);
+    load_tile(w.r, base, w.n, r);
+    load_tile(w.q32, base, w.n, q);
     const double pq = tiles_sum(pq_partial, w.tile_begin, w.n, red);
     const double alpha = pq > 0.0 ? sc[w.slot].rr[w.parity] / pq : 0.0;   // pq <= 0: no step
     if (local == 0 && threadIdx.x == 0) {                                  // (host leaves the cycle)
@@ -150,21 +203,26 @@ static __global__ __launch_bounds__(kVecBlock) void cg_update_kernel(const CgVec
       sc[w.slot].alpha = alpha;
       host_sc[w.slot].pq = pq;
     }
+#pragma unroll
     for (int k = 0; k < kVecPerThread; ++k) {
-      const int32_t i = base + k * kVecBlock + int32_t(threadIdx.x);
+      const int32_t i = tile_element(base, k);
       if (i < w.n) {
-        w.d[i] = __builtin_fma(alpha, w.p[i], w.d[i]);
-        const double ri = __builtin_fma(-alpha, double(w.q32[i]), w.r[i]);
+        w.d[i] = __builtin_fma(alpha, p[k], d[k]);
+        const double ri = __builtin_fma(-alpha, double(q[k]), r[k]);
         w.r[i] = ri;
         s = __builtin_fma(ri, ri, s);
       }
     }
   } else {
     const bool outer = w.phase == kPhaseOuter;
+    double b[kVecPerThread], q[kVecPerThread];
+    load_tile(w.b, base, w.n, b);
+    if (outer) load_tile(w.q64, base, w.n, q);
+#pragma unroll
     for (int k = 0; k < kVecPerThread; ++k) {
-      const int32_t i = base + k * kVecBlock + int32_t(threadIdx.x);
+      const int32_t i = tile_element(base, k);
       if (i < w.n) {
-        const double ri = outer ? w.b[i] - w.q64[i] : w.b[i];
+        const double ri = outer ? b[k] - q[k] : b[k];
         w.r[i] = ri;
         w.p[i] = ri;
         w.p32[i] = float(ri);
@@ -187,13 +245,22 @@ static __global__ __launch_bounds__(kVecBlock) void cg_direction_kernel(const Cg
                                                                 CgScalars* __restrict__ host_sc,
                                                                 const double* __restrict__ rr_partial) {
   __shared__ double red[kVecBlock];
-  const CgVec w = v[tile_req[blockIdx.x]];
+  const CgVec w = cg_request(v, tile_req);
   const int32_t local = int32_t(blockIdx.x) - w.tile_begin;
   if (cg_skip(w, sc)) {        // this pass's kernels read stop[pass - 1] only, never stop[pass]
     if (local == 0 && threadIdx.x == 0) sc[w.slot].stop[w.pass] = 1;
     return;
   }
+  const bool inner = w.phase == kPhaseInner;
+  const int32_t base = local * kTile;
+  double p[kVecPerThread], r[kVecPerThread], rr = 0.0;
+  if (inner) {
+    load_tile(w.p, base, w.n, p);
+    load_tile(w.r, base, w.n, r);
+    rr = sc[w.slot].rr[w.parity];
+  }
   const double rr_new = tiles_sum(rr_partial, w.tile_begin, w.n, red);
+  const double beta = rr > 0.0 ? rr_new / rr : 0.0;
   if (local == 0 && threadIdx.x == 0) {
     sc[w.slot].rr[1 - w.parity] = rr_new;
     host_sc[w.slot].rr[1 - w.parity] = rr_new;
@@ -201,20 +268,18 @@ static __global__ __launch_bounds__(kVecBlock) void cg_direction_kernel(const Cg
       sc[w.slot].bnorm2 = rr_new;
       host_sc[w.slot].bnorm2 = rr_new;
     }
-    if (w.phase == kPhaseInner) {
+    if (inner) {
       sc[w.slot].stop[w.pass] = (sc[w.slot].pq <= 0.0 || rr_new <= w.stop_rr) ? 1 : 0;
       host_sc[w.slot].passes = w.pass;
+      sc[w.slot].beta = beta;
     }
   }
-  if (w.phase != kPhaseInner) return;
-  const double rr = sc[w.slot].rr[w.parity];
-  const double beta = rr > 0.0 ? rr_new / rr : 0.0;
-  if (local == 0 && threadIdx.x == 0) sc[w.slot].beta = beta;
-  const int32_t base = local * kTile;
+  if (!inner) return;
+#pragma unroll
   for (int k = 0; k < kVecPerThread; ++k) {
-    const int32_t i = base + k * kVecBlock + int32_t(threadIdx.x);
+    const int32_t i = tile_element(base, k);
     if (i < w.n) {
-      const double pi = __builtin_fma(beta, w.p[i], w.r[i]);
+      const double pi = __builtin_fma(beta, p[k], r[k]);
       w.p[i] = pi;
       w.p32[i] = float(pi);
     }
