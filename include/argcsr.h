@@ -203,8 +203,8 @@ int argcsr_choose_region_desired(int32_t n_rows, const int32_t* row_ptr_host,
  * next-group-start function of the rows; see argcsr_convert).
  *   row_ptr  device int32[n_rows+1]
  *   other arguments as for argcsr_plan (n_heavy may be NULL)
- * Synchronous (reads the counts back).  Uses stream-ordered device scratch
- * of about 22 bytes a row.  Errors: EINVAL (bad sizes,
+ * Synchronous (reads the counts back).  Uses device scratch of about
+ * 22 bytes a row, from the library's cache of at most 2 GiB a GPU.  Errors: EINVAL (bad sizes,
  * row_ptr not starting at 0 or decreasing), EOVERFLOW, ENOMEM, EHIP.
  */
 int argcsr_plan_device(int32_t n_rows, const int32_t* row_ptr, int32_t block_dim,
@@ -245,8 +245,8 @@ int argcsr_convert_planned(const argcsr_device_plan* plan, int32_t n_cols, const
                            const int32_t* col, const double* val, argcsr_matrix* out,
                            void* stream);
 
-/* Frees a device plan (NULL is a no-op), in the order of the stream it was
- * planned on.  No conversion may be running with it. */
+/* Frees a device plan (NULL is a no-op).  No conversion may be running with
+ * it. */
 int argcsr_device_plan_destroy(argcsr_device_plan* plan);
 
 /*
@@ -286,10 +286,10 @@ int argcsr_convert(int32_t n_rows, int32_t n_cols, const int32_t* row_ptr_host,
  * device memory (tight serving loops, harnesses that forbid hipMalloc): it
  * calls no hipMalloc, hipFree or other allocating routine.  Like
  * argcsr_convert it waits for its stream (it reads back the validation
- * flag), so it cannot itself be recorded into a HIP graph.  Its scratch (status words, scan partials and the
- * fill's long-row list) is a fixed array of 16 MiB and 32 KiB in device memory, one copy
- * per GPU, held by the library until the process ends; the caller still
- * passes every input and output, as for argcsr_convert, and the result is
+ * flag), so it cannot itself be recorded into a HIP graph.  Its scratch
+ * (status words, scan partials and the fill's long-row list) is a fixed array
+ * of 16 MiB and 32 KiB in device memory, one copy per GPU, held by the library
+ * until the process ends; the caller still passes every input and output, as for argcsr_convert, and the result is
  * byte for byte the same.
  *   arguments as for argcsr_convert, except that row_ptr_host is required
  *   (step 1 runs on the host; device grouping needs scratch proportional to
@@ -353,7 +353,7 @@ int argcsr_csr_spmv(int32_t n_rows, int32_t n_cols, int64_t nnz,
  *              within a bin
  *   bin_start  host int32[ARGCSR_CSR_BINS+1], out: bin k's rows are
  *              rows[bin_start[k] .. bin_start[k+1])
- * Synchronous; uses stream-ordered scratch of 32 bytes per 256 rows.
+ * Synchronous; uses device scratch of 32 bytes per 256 rows.
  * Errors: EINVAL, EHIP.
  */
 int argcsr_csr_bin_rows(int32_t n_rows, const int32_t* row_ptr, int32_t* rows,

@@ -20,6 +20,7 @@ SOURCES = [
     "library.cpp",
     "plan.cpp",
     "mailbox.cpp",
+    "scratch.cpp",
     "convert.hip",
     "group.hip",
     "spmv.hip",

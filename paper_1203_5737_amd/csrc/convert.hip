@@ -9,7 +9,7 @@
 //                   step 3: inclusive per-group prefix sum of t_r -> threadsMapping
 //   offsets_kernel  exclusive scan of c_g*T over the groups -> groupInfo.offset,
 //                   and the sizes the host checks
-//   heavy_scatter   the launch schedule: ascending indices of groups whose
+//   schedule_kernel the launch schedule: ascending indices of groups whose
 //                   chunk loop is long (compaction by an exclusive scan)
 //   fill_kernel     step 4: every slot (j, k) of a group -- element j of chunk
 //   fill_long_kernel k at offset + j*T + k -- is written exactly once: the
@@ -17,7 +17,7 @@
 //                   otherwise the artificial zero (0, -1); the CSR elements
 //                   pass through LDS so that reads and writes are coalesced
 //                   (fill_long_kernel takes the blocks of long rows, tile by
-//                   tile, from a list the fill kernel makes); every CSR element
+//                   tile, from a list schedule_kernel makes); every CSR element
 //                   passes through one of the two, which also check its column
 //                   index against [0, n_cols).
 #include <hip/hip_runtime.h>
@@ -32,6 +32,7 @@
 #include "mailbox.hpp"
 #include "plan.hpp"
 #include "schedule.hpp"
+#include "scratch.hpp"
 #include "values.hpp"
 
 namespace argcsr {
@@ -46,6 +47,7 @@ constexpr int kScanShare = kChunkBlocks / kScanBlocks;   // shares of groups eac
 constexpr int kMinStage = 256;        // CSR elements one fill wave stages in LDS
 constexpr int kMaxStage = 2048;
 constexpr int kMaxFillWaves = 4;
+constexpr size_t kMaxFillLds = size_t(64) << 10;
 constexpr int kLongSteps = 16;        // steps per LDS tile in fill_long_kernel
 constexpr int kLongGrid = 4096;       // one-wave workgroups of fill_long_kernel
 
@@ -53,14 +55,15 @@ constexpr int kLongGrid = 4096;       // one-wave workgroups of fill_long_kernel
 // `groups`, which step 1 on the device fills in).
 struct Status {
   GroupCount groups;                  // step 1's, when it runs on the device
-  int32_t long_items;                 // entries of the fill's long-row work list
   int32_t scans_done;                 // workgroups of offsets_kernel that have finished
+  int32_t pad;
   unsigned long long heavy;           // heavy groups of those
+  unsigned long long long_tiles;      // and tiles of long groups (see fill_kernel)
 };
 
 // Words the kernels hand to the host (a pinned slot, or device memory).
 constexpr int kBoxGroups = 0, kBoxSlots = 1, kBoxHeavy = 2, kBoxBadRowPtr = 3, kBoxBadColumn = 4,
-              kBoxNnz = 5;
+              kBoxNnz = 5, kBoxLong = 6;
 constexpr int kBoxWords = Mailbox::kWords;
 
 __global__ __launch_bounds__(64) void clear_words_kernel(int32_t* __restrict__ p, int32_t n) {
@@ -68,25 +71,40 @@ __global__ __launch_bounds__(64) void clear_words_kernel(int32_t* __restrict__ p
 }
 
 // A device plan's tables into the caller's buffers: group records as 4
-// words, then the threads mapping; and a zero work list count for the fill.
+// words, then the threads mapping.
 __global__ __launch_bounds__(256) void adopt_plan_kernel(const int32_t* __restrict__ groups,
                                                          int64_t group_words,
                                                          const int32_t* __restrict__ tm,
                                                          int64_t n_rows,
                                                          int32_t* __restrict__ out_groups,
-                                                         int32_t* __restrict__ out_tm,
-                                                         Status* __restrict__ st) {
+                                                         int32_t* __restrict__ out_tm) {
   const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x, stride = int64_t(gridDim.x) * 256;
   for (int64_t i = t; i < group_words; i += stride) out_groups[i] = groups[i];
   for (int64_t i = t; i < n_rows; i += stride) out_tm[i] = tm[i];
-  if (t == 0) st->long_items = 0;
 }
 
-// LDS of one fill wave: chunk starts and lengths, then the staged columns and
-// values (the byte count keeps the next wave's region 8-byte aligned)
+// CSR elements a fill wave stages in LDS: the blocks of chunks up to twice
+// the matrix's mean chunk size (at least 4 and at most 32 elements a chunk).
+__host__ __device__ inline int32_t fill_stage(int32_t T, int64_t n_slots, int32_t n_groups) {
+  const int64_t chunks = int64_t(n_groups) * T;
+  const int64_t mean_chunk = (n_slots + chunks - 1) / chunks;
+  int32_t stage = kMinStage;
+  while (stage < kMaxStage && stage < 128 * mean_chunk) stage *= 2;
+  return stage;
+}
+
+// Tiles of kLongSteps steps that a group leaves to fill_long_kernel: a group
+// whose chunks are longer than stage/64 elements may have blocks whose CSR
+// range does not fit the stage.
+__host__ __device__ inline int32_t long_tiles(int32_t c, int32_t stage) {
+  return int64_t(c) * 64 > stage ? (c - 1) / kLongSteps + 1 : 0;
+}
+
+// LDS of one fill wave: the group's rows (RowTables), then the staged columns
+// and values (the byte count keeps the next wave's region 8-byte aligned)
 template <typename S>
 __host__ __device__ inline size_t fill_lds_bytes(int32_t T, int32_t stage) {
-  const size_t b = sizeof(int32_t) * (2 * size_t(T) + size_t(stage)) + sizeof(S) * size_t(stage);
+  const size_t b = sizeof(int32_t) * (3 * size_t(T) + size_t(stage)) + sizeof(S) * size_t(stage);
   return (b + 7) & ~size_t(7);
 }
 
@@ -259,17 +277,17 @@ __device__ void split_sums(const int64_t* __restrict__ v, int32_t at, int32_t n,
   (void)block_exclusive_scan(r, rest);
 }
 
-// Offsets (an exclusive scan of c_g*T over the groups), the heavy groups of
-// every workgroup's part, and, by the workgroup that finishes last, the sizes
-// for the host.  A workgroup takes kScanShare consecutive shares of
+// Offsets (an exclusive scan of c_g*T over the groups), the heavy groups and
+// the long tiles of every workgroup's part, and, by the workgroup that
+// finishes last, the sizes for the host.  A workgroup takes kScanShare consecutive shares of
 // chunks_kernel and sums the shares before them itself, so the scan is one
-// launch.  Few workgroups: each adds to the two counters of `st`, and atomics
-// on one cache line take turns at about 12 ns each.
+// launch.  Few workgroups: each adds to the counters of `st`, and atomics on
+// one cache line take turns at about 12 ns each.
 __global__ __launch_bounds__(kScanBlock) void offsets_kernel(
     argcsr_group_info* __restrict__ groups, int32_t n_host, const GroupCount* __restrict__ n_dev,
     int32_t T, const int64_t* __restrict__ share_slots, int64_t* __restrict__ heavy_parts,
-    Status* __restrict__ st, const int32_t* __restrict__ rp, int32_t n_rows,
-    int64_t* __restrict__ box) {
+    int64_t* __restrict__ long_parts, Status* __restrict__ st, const int32_t* __restrict__ rp,
+    int32_t n_rows, int64_t* __restrict__ box) {
   const int32_t n_groups = n_dev ? n_dev->n_groups : n_host;
   const int32_t b = int32_t(blockIdx.x);
   int64_t off, rest;
@@ -278,7 +296,9 @@ __global__ __launch_bounds__(kScanBlock) void offsets_kernel(
   const int32_t heavy_chunk = heavy_chunk_for(T, slots, n_groups);
   const int32_t g0 = share_begin(n_groups, b * kScanShare, kChunkBlocks);
   const int32_t g1 = share_begin(n_groups, (b + 1) * kScanShare, kChunkBlocks);
+  const int32_t stage = fill_stage(T, slots > 0 ? slots : 1, n_groups > 0 ? n_groups : 1);
   int32_t heavy = 0;
+  int64_t tiles = 0;
   for (int32_t i = g0; i < g1; i += kScanBlock) {
     const int32_t g = i + int32_t(threadIdx.x);
     const int32_t c = g < g1 ? groups[g].chunk_size : 0;
@@ -286,69 +306,130 @@ __global__ __launch_bounds__(kScanBlock) void offsets_kernel(
     const int64_t mine = off + block_exclusive_scan(int64_t(c) * T, &all);
     if (g < g1) groups[g].offset = int32_t(mine);    // the host checks the total
     heavy += c > heavy_chunk;
+    tiles += long_tiles(c, stage);
     off += all;
   }
-  int64_t part_heavy;
+  int64_t part_heavy, part_tiles;
   (void)block_exclusive_scan(heavy, &part_heavy);
+  (void)block_exclusive_scan(tiles, &part_tiles);
   if (threadIdx.x == 0) {
     heavy_parts[b] = part_heavy;
+    long_parts[b] = part_tiles;
     if (part_heavy) atomicAdd(&st->heavy, (unsigned long long)part_heavy);
+    if (part_tiles) atomicAdd(&st->long_tiles, (unsigned long long)part_tiles);
     __threadfence();
     if (atomicAdd(&st->scans_done, 1) == kScanBlocks - 1) {
       __threadfence();
       box[kBoxGroups] = n_groups;
       box[kBoxSlots] = slots;
       box[kBoxHeavy] = int64_t(atomicAdd(&st->heavy, 0ull));
+      box[kBoxLong] = int64_t(atomicAdd(&st->long_tiles, 0ull));
       box[kBoxBadRowPtr] = n_dev ? n_dev->bad : 0;
       box[kBoxNnz] = n_dev ? rp[n_rows] : 0;
     }
   }
 }
 
-// The launch schedule: every part of offsets_kernel writes the indices of
-// its heavy groups, ascending, behind those of the parts before it.
-__global__ __launch_bounds__(kScanBlock) void heavy_scatter_kernel(
+// The launch schedule and the fill's list of long tiles: every part of
+// offsets_kernel writes the indices of its heavy groups (`heavy` may be NULL)
+// and the (group, first step) of its long tiles, ascending, behind those of
+// the parts before it.  7 us on the power-law matrix of 10^6 rows (29 000
+// tiles).  When fill_kernel appended the tiles with one device atomic per
+// group, those took turns on their cache line: it took 59 us there, without
+// them 53.
+constexpr int32_t kLaneTiles = 8;
+__global__ __launch_bounds__(kScanBlock) void schedule_kernel(
     const argcsr_group_info* __restrict__ groups, int32_t n_groups, int32_t heavy_chunk,
-    const int64_t* __restrict__ heavy_parts, int32_t* __restrict__ heavy) {
+    int32_t stage, const int64_t* __restrict__ heavy_parts,
+    const int64_t* __restrict__ long_parts, int32_t* __restrict__ heavy,
+    int2* __restrict__ long_list) {
   const int32_t b = int32_t(blockIdx.x);
-  if (heavy_parts[b] == 0) return;
-  int64_t pos, rest;
-  split_sums(heavy_parts, b, kScanBlocks, &pos, &rest);
+  const bool any_heavy = heavy && heavy_parts[b] != 0, any_long = long_parts[b] != 0;
+  if (!any_heavy && !any_long) return;
+  int64_t at_heavy = 0, at_long = 0, rest;
+  if (any_heavy) split_sums(heavy_parts, b, kScanBlocks, &at_heavy, &rest);
+  if (any_long) split_sums(long_parts, b, kScanBlocks, &at_long, &rest);
   const int32_t g0 = share_begin(n_groups, b * kScanShare, kChunkBlocks);
   const int32_t g1 = share_begin(n_groups, (b + 1) * kScanShare, kChunkBlocks);
   for (int32_t i = g0; i < g1; i += kScanBlock) {
     const int32_t g = i + int32_t(threadIdx.x);
-    const bool is = g < g1 && groups[g].chunk_size > heavy_chunk;
+    const int32_t c = g < g1 ? groups[g].chunk_size : 0;
     int64_t all;
-    const int64_t at = pos + block_exclusive_scan(is ? 1 : 0, &all);
-    if (is) heavy[at] = g;
-    pos += all;
+    if (any_heavy) {
+      const int64_t at = at_heavy + block_exclusive_scan(c > heavy_chunk ? 1 : 0, &all);
+      if (c > heavy_chunk) heavy[at] = g;
+      at_heavy += all;
+    }
+    if (any_long) {
+      const int32_t tiles = long_tiles(c, stage);
+      const int64_t at = at_long + block_exclusive_scan(tiles, &all);
+      // a lane writes a few entries itself, the wave those of a longer group
+      if (tiles <= kLaneTiles)
+        for (int32_t t = 0; t < tiles; ++t) long_list[at + t] = int2{g, t * kLongSteps};
+      for (uint64_t big = __ballot(tiles > kLaneTiles); big; big &= big - 1) {
+        const int from = __builtin_ctzll(big);
+        const int32_t n = __builtin_amdgcn_readlane(tiles, from);
+        const int32_t first = __builtin_amdgcn_readlane(int32_t(at), from);
+        const int32_t group = __builtin_amdgcn_readlane(g, from);
+        for (int32_t t = lane_id(); t < n; t += 64)
+          long_list[first + t] = int2{group, t * kLongSteps};
+      }
+      at_long += all;
+    }
   }
 }
 
-// For every chunk k of the group: where its elements start in the CSR arrays
-// and how many there are (0 for free chunks), in the wave's LDS tables.
-__device__ inline void chunk_sources(const argcsr_group_info& gi, const int32_t* __restrict__ rp,
-                                     const int32_t* __restrict__ tm, int32_t T, int lane,
-                                     int32_t* src_start, int32_t* src_len) {
-  const int32_t c = gi.chunk_size;
-  for (int k = lane; k < T; k += 64) src_len[k] = 0;
+// The rows of a group in the wave's LDS: where each starts in the CSR arrays
+// and its length, and per chunk a mark where a row's chunks begin.
+struct RowTables {
+  int32_t* start;     // [T]
+  int32_t* len;       // [T]
+  int32_t* mark;      // [T]: chunk << kRowBits | row at a row's first chunk, else 0
+};
+constexpr int kRowBits = 10;
+static_assert(kMaxBlockDim <= 1 << kRowBits, "marks hold a chunk and a row");
+
+__device__ __forceinline__ RowTables row_tables(int32_t* lds, int32_t T) {
+  return RowTables{lds, lds + T, lds + 2 * T};
+}
+
+__device__ __forceinline__ void load_rows(const argcsr_group_info& gi,
+                                          const int32_t* __restrict__ rp,
+                                          const int32_t* __restrict__ tm, int32_t T, int lane,
+                                          const RowTables& t) {
+  for (int k = lane; k < T; k += 64) t.mark[k] = 0;
   wave_lds_sync();
   for (int l = lane; l < gi.size; l += 64) {
     const int32_t r = gi.first_row + l;
     const int32_t begin = l == 0 ? 0 : tm[r - 1];
-    const int32_t end = tm[r];
-    const int32_t row_start = rp[r];
-    const int32_t L = rp[r + 1] - row_start;
-    for (int32_t k = begin; k < end; ++k) {
-      const int32_t q = k - begin;                    // chunk q of row r
-      const int32_t first_elem = q * c;
-      src_start[k] = row_start + first_elem;
-      const int32_t left = L - first_elem;
-      src_len[k] = left < 0 ? 0 : (left < c ? left : c);
-    }
+    const int32_t first = rp[r];
+    t.start[l] = first;
+    t.len[l] = rp[r + 1] - first;
+    t.mark[begin] = begin << kRowBits | l;
   }
   wave_lds_sync();
+}
+
+// Where the elements of chunk k of the group start in the CSR arrays and how
+// many there are (0 for free chunks, k >= n_mapped).  The last mark at or
+// before a chunk names its row and the row's first chunk: a running maximum
+// over the chunks, `carry` taking it from one block of 64 to the next.  A loop
+// over the chunks of each row, by the row's lane, runs as long as the group's
+// row of most chunks, with one lane at work: fill_kernel took 53 us with it on
+// the power-law matrix of 10^6 rows and fill_long_kernel 25, now 37 and 19.
+struct ChunkSource {
+  int32_t start, len;
+};
+__device__ __forceinline__ ChunkSource chunk_source(const RowTables& t, int32_t k, int32_t T,
+                                                    int32_t n_mapped, int32_t c, int32_t* carry) {
+  int32_t m = wave_inclusive_max(k < T ? t.mark[k] : 0);
+  m = m > *carry ? m : *carry;
+  *carry = __builtin_amdgcn_readlane(m, 63);
+  const int32_t row = m & ((1 << kRowBits) - 1);
+  if (k >= n_mapped) return ChunkSource{0, 0};
+  const int32_t skip = (k - (m >> kRowBits)) * c;     // elements of the row's chunks before
+  const int32_t left = t.len[row] - skip;
+  return ChunkSource{t.start[row] + skip, left < 0 ? 0 : left < c ? left : c};
 }
 
 // The CSR range [lo, lo + extent) that holds the elements of the wave's 64
@@ -360,57 +441,44 @@ __device__ inline int32_t block_extent(int32_t start, int32_t len, int32_t* lo_o
   return hi > lo ? hi - lo : 0;
 }
 
-// Step 4, one wave per group.  For every chunk k the wave first records in
-// LDS where its elements start in the CSR arrays and how many there are (0 for
-// free chunks).  It then takes the chunks 64 at a time.  The elements of 64
-// consecutive chunks form one contiguous CSR range (a row's chunks follow each
-// other, and so do the rows), so when that range fits the wave's stage of
-// `stage` elements the wave copies it into LDS with coalesced loads,
+// Step 4, one wave per group.  The wave takes the group's chunks 64 at a
+// time.  The elements of 64 consecutive chunks form one contiguous CSR range
+// (a row's chunks follow each other, and so do the rows), so when that range
+// fits the wave's stage of `stage` elements the wave copies it into LDS with coalesced loads,
 // converting the values to their storage type, and then writes the block's
 // slots step by step, 64 consecutive slots per store, each lane taking its
 // chunk's element from LDS.  Blocks whose range is longer than the stage are
-// left to fill_long_kernel: a group whose chunks are longer than stage/64
-// elements, the only kind that can have such blocks, appends one work item per
-// tile of kLongSteps steps to a list.  Every staged column index is checked
+// left to fill_long_kernel.  Every staged column index is checked
 // against [0, n_cols) (a negative one wraps above the limit as unsigned).
 template <int DT>
 __global__ __launch_bounds__(kMaxFillWaves * 64) void fill_kernel(
     const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
     const double* __restrict__ val, const argcsr_group_info* __restrict__ groups,
     int32_t n_groups, int32_t n_cols, int32_t T, const int32_t* __restrict__ tm, int32_t stage,
-    Status* __restrict__ st, int64_t* __restrict__ box, int32_t* __restrict__ long_list,
-    int32_t* __restrict__ columns, typename Val<DT>::storage* __restrict__ values) {
+    int64_t* __restrict__ box, int32_t* __restrict__ columns,
+    typename Val<DT>::storage* __restrict__ values) {
   using S = typename Val<DT>::storage;
-  extern __shared__ int32_t fill_lds[];   // per wave: [T] starts, [T] lengths, stage
+  extern __shared__ int32_t fill_lds[];   // per wave: RowTables, stage
   const int lane = lane_id();
   const int w = wave_uniform(int(threadIdx.x >> 6));
   const size_t wave_bytes = fill_lds_bytes<S>(T, stage);
-  int32_t* src_start = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(fill_lds) + w * wave_bytes);
-  int32_t* src_len = src_start + T;
-  int32_t* stage_col = src_start + 2 * T;
+  int32_t* lds = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(fill_lds) + w * wave_bytes);
+  const RowTables rows = row_tables(lds, T);
+  int32_t* stage_col = lds + 3 * T;
   S* stage_val = reinterpret_cast<S*>(stage_col + stage);
   const int g = blockIdx.x * (blockDim.x >> 6) + w;
   if (g >= n_groups) return;
   const argcsr_group_info gi = groups[g];
   const int32_t c = gi.chunk_size;
-  if (int64_t(c) * 64 > stage) {   // one work item per tile of kLongSteps steps
-    const int32_t n_items = (c + kLongSteps - 1) / kLongSteps;
-    int32_t base = 0;
-    if (lane == 0) base = atomicAdd(&st->long_items, n_items);
-    base = __shfl(base, 0, 64);
-    for (int32_t t = lane; t < n_items; t += 64) {
-      long_list[2 * int64_t(base + t)] = g;
-      long_list[2 * int64_t(base + t) + 1] = t * kLongSteps;
-    }
-  }
-  chunk_sources(gi, rp, tm, T, lane, src_start, src_len);
+  const int32_t n_mapped = tm[gi.first_row + gi.size - 1];
+  load_rows(gi, rp, tm, T, lane, rows);
   const uint32_t limit = uint32_t(n_cols);
   bool bad = false;
+  int32_t carry = 0;
   for (int32_t k0 = 0; k0 < T; k0 += 64) {
     const int32_t k = k0 + lane;
     const bool mine = k < T;
-    const int32_t start = mine ? src_start[k] : 0;
-    const int32_t len = mine ? src_len[k] : 0;
+    const auto [start, len] = chunk_source(rows, k, T, n_mapped, c, &carry);
     int32_t lo;
     const int32_t extent = block_extent(start, len, &lo);
     const int64_t dst0 = int64_t(gi.offset) + k;
@@ -442,9 +510,8 @@ __global__ __launch_bounds__(kMaxFillWaves * 64) void fill_kernel(
 }
 
 // Step 4 for the blocks fill_kernel leaves: those whose CSR range is longer
-// than the stage, from the list of (group, first step) work items (in any
-// order: every slot belongs to one block and one tile).  One-wave workgroups
-// stride over the list; an item moves kLongSteps steps of the group's long
+// than the stage, from the list of (group, first step) tiles that
+// schedule_kernel made.  One-wave workgroups stride over the list; an item moves kLongSteps steps of the group's long
 // blocks through LDS: each load instruction reads kLongSteps consecutive
 // elements of each of 64/kLongSteps chunks (a lane past its chunk's end reads
 // an element of the block and keeps the padding value, so the loads carry no
@@ -456,40 +523,43 @@ __global__ __launch_bounds__(64) void fill_long_kernel(
     const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
     const double* __restrict__ val, const argcsr_group_info* __restrict__ groups,
     int32_t n_cols, int32_t T, const int32_t* __restrict__ tm, int32_t stage,
-    const Status* __restrict__ st, int64_t* __restrict__ box,
-    const int32_t* __restrict__ long_list, int32_t* __restrict__ columns,
-    typename Val<DT>::storage* __restrict__ values) {
+    int64_t* __restrict__ box, const int2* __restrict__ long_list, int32_t n_items,
+    int32_t* __restrict__ columns, typename Val<DT>::storage* __restrict__ values) {
   using S = typename Val<DT>::storage;
   constexpr int kPer = 64 / kLongSteps;           // chunks per load instruction
   __shared__ int32_t tile_col[kLongSteps][65];    // [step][chunk], padded rows
   __shared__ S tile_val[kLongSteps][65];
-  extern __shared__ int32_t long_tables[];        // [T] starts, [T] lengths
-  int32_t* src_start = long_tables;
-  int32_t* src_len = long_tables + T;
+  __shared__ int32_t src_start[64], src_len[64];  // of the block's chunks
+  extern __shared__ int32_t long_tables[];        // RowTables
+  const RowTables rows = row_tables(long_tables, T);
   const int lane = lane_id();
   const int jj = lane % kLongSteps, kq = lane / kLongSteps;
-  const int32_t n_items = st->long_items;
   const uint32_t limit = uint32_t(n_cols);
   bool bad = false;
   for (int32_t i = blockIdx.x; i < n_items; i += gridDim.x) {
-    const argcsr_group_info gi = groups[long_list[2 * int64_t(i)]];
-    const int32_t j0 = long_list[2 * int64_t(i) + 1];
+    const argcsr_group_info gi = groups[long_list[i].x];
+    const int32_t j0 = long_list[i].y;
     const int32_t c = gi.chunk_size;
-    chunk_sources(gi, rp, tm, T, lane, src_start, src_len);
+    const int32_t n_mapped = tm[gi.first_row + gi.size - 1];
+    load_rows(gi, rp, tm, T, lane, rows);
+    int32_t carry = 0;
     for (int32_t k0 = 0; k0 < T; k0 += 64) {
       const int32_t k = k0 + lane;
+      const auto [start, len] = chunk_source(rows, k, T, n_mapped, c, &carry);
       int32_t lo;
-      if (block_extent(k < T ? src_start[k] : 0, k < T ? src_len[k] : 0, &lo) <= stage) continue;
+      if (block_extent(start, len, &lo) <= stage) continue;
+      src_start[lane] = start;
+      src_len[lane] = len;
+      wave_lds_sync();
       int32_t cv[kLongSteps];
       double v[kLongSteps];
       bool ok[kLongSteps];
 #pragma unroll
       for (int it = 0; it < kLongSteps; ++it) {
-        const int32_t kk = k0 + it * kPer + kq;
-        const int32_t kc = kk < T ? kk : T - 1;
+        const int32_t kl = it * kPer + kq;          // a chunk at or past T has no elements
         const int32_t j = j0 + jj;
-        ok[it] = kk < T && j < src_len[kc];
-        const int32_t e = ok[it] ? src_start[kc] + j : lo;
+        ok[it] = j < src_len[kl];
+        const int32_t e = ok[it] ? src_start[kl] + j : lo;
         cv[it] = col[e];
         v[it] = val[e];
         bad |= ok[it] && uint32_t(cv[it]) >= limit;
@@ -515,29 +585,27 @@ __global__ __launch_bounds__(64) void fill_long_kernel(
   if (__ballot(bad) != 0 && lane == 0) box[kBoxBadColumn] = 1;
 }
 
-// The stage holds the blocks of chunks up to twice the matrix's mean chunk
-// size (at least 4 and at most 32 elements per chunk); small stages leave room
-// for 4 waves per workgroup, which the many short groups of irregular
-// matrices need to hide their latency.
+// Small stages leave room for 4 waves per workgroup, which the many short
+// groups of irregular matrices need to hide their latency, as long as the
+// waves' LDS stays within the 64 KB any launch may ask for (T = 1024: 2).
 template <int DT>
-void launch_fill(int32_t n_groups, hipStream_t s, const int32_t* rp, const int32_t* col,
-                 const double* val, Status* st, int64_t* box, int32_t* long_list,
+void launch_fill(hipStream_t s, const int32_t* rp, const int32_t* col, const double* val,
+                 int32_t stage, int64_t* box, const int2* long_list, int32_t n_long,
                  const argcsr_matrix* out) {
   using S = typename Val<DT>::storage;
-  const int64_t T = out->block_dim;
-  const int64_t mean_chunk = (out->n_slots + int64_t(n_groups) * T - 1) / (int64_t(n_groups) * T);
-  int32_t stage = kMinStage;
-  while (stage < kMaxStage && stage < 128 * mean_chunk) stage *= 2;
-  const int waves = stage <= 512 ? kMaxFillWaves : 1;
-  const size_t lds = fill_lds_bytes<S>(int32_t(T), stage) * size_t(waves);
-  const uint32_t blocks = uint32_t((int64_t(n_groups) + waves - 1) / waves);
+  const int32_t T = out->block_dim;
+  int waves = stage <= 512 ? kMaxFillWaves : 1;
+  while (waves > 1 && fill_lds_bytes<S>(T, stage) * size_t(waves) > kMaxFillLds) waves /= 2;
+  const size_t lds = fill_lds_bytes<S>(T, stage) * size_t(waves);
+  const uint32_t blocks = uint32_t((int64_t(out->n_groups) + waves - 1) / waves);
   fill_kernel<DT><<<dim3(blocks), 64 * waves, lds, s>>>(
-      rp, col, val, out->groups, out->n_groups, out->n_cols, out->block_dim, out->threads_mapping,
-      stage, st, box, long_list, out->columns, static_cast<S*>(out->values));
-  const int64_t long_blocks = std::min<int64_t>(n_groups, kLongGrid);
-  fill_long_kernel<DT><<<dim3(uint32_t(long_blocks)), 64, sizeof(int32_t) * 2 * size_t(T), s>>>(
-      rp, col, val, out->groups, out->n_cols, out->block_dim, out->threads_mapping, stage, st,
-      box, long_list, out->columns, static_cast<S*>(out->values));
+      rp, col, val, out->groups, out->n_groups, out->n_cols, T, out->threads_mapping, stage, box,
+      out->columns, static_cast<S*>(out->values));
+  if (n_long > 0)
+    fill_long_kernel<DT><<<dim3(uint32_t(std::min(n_long, kLongGrid))), 64,
+                           sizeof(int32_t) * 3 * size_t(T), s>>>(
+        rp, col, val, out->groups, out->n_cols, T, out->threads_mapping, stage, box, long_list,
+        n_long, out->columns, static_cast<S*>(out->values));
 }
 
 }  // namespace
@@ -545,29 +613,26 @@ void launch_fill(int32_t n_groups, hipStream_t s, const int32_t* rp, const int32
 
 // A device plan (argcsr_plan_device_keep): steps 1-3 of one matrix kept on
 // the device for argcsr_convert_planned, and the sizes of the result.
-// Its buffers are stream-ordered allocations on the planning stream (freed
-// on it too: every conversion with the plan has waited for its own work).
+// Its buffers are one block of scratch, unused on the device whenever the plan
+// is (planning and every conversion with it wait for their own work).
 // The group table has room for one group a row, because the number of groups
 // is only known to the device while the plan is made.
 struct argcsr_device_plan {
   int32_t n_rows = 0, block_dim = 0, desired_chunk_size = 0, format = 0;
   int32_t n_groups = 0, n_heavy = 0;
-  int64_t n_slots = 0, nnz = 0;
+  int64_t n_slots = 0, nnz = 0, n_long = 0;
   argcsr_group_info* groups = nullptr;    // complete, offsets included
   int32_t* tm = nullptr;                  // threads mapping
-  int64_t* heavy_parts = nullptr;         // heavy groups per part of offsets_kernel
-  void* block = nullptr;                  // the one allocation holding them
-  hipStream_t stream = nullptr;
-  ~argcsr_device_plan() {
-    if (block) (void)hipFreeAsync(block, stream);
-  }
+  int64_t* heavy_parts = nullptr;         // heavy groups per part of offsets_kernel,
+                                          // then long tiles per part
+  argcsr::DeviceScratch block;            // holds them
 };
 
 // Fixed scratch of argcsr_convert_noalloc: one copy per GPU (this process's
 // code object), held until the process ends.  Host code reaches it only
 // through the address hipGetSymbolAddress returns for the current device.
-constexpr size_t kHeadBytes = 256;      // Status and the result words
-constexpr size_t kNoAllocExtra = 32768;   // head and shares
+constexpr size_t kHeadBytes = 256;        // Status and the result words
+constexpr size_t kNoAllocExtra = 32768;   // head, shares and parts
 constexpr size_t kNoAllocScratchBytes = size_t(16) << 20;
 static __device__ __align__(256) unsigned char scratch[kNoAllocExtra + kNoAllocScratchBytes];
 
@@ -576,16 +641,16 @@ namespace {
 
 // Device scratch of one conversion: a head of kHeadBytes (Status and, for
 // argcsr_convert_noalloc, the result words), the slots of the shares of
-// chunks_kernel and the heavy groups of the parts of offsets_kernel, and the
-// fill's long-row list.  Items of that
+// chunks_kernel, the heavy groups and long tiles of the parts of
+// offsets_kernel, and the fill's list of long tiles.  Entries of that
 // list: a group makes them only when its chunk size c exceeds
 // stage/64 >= kMinStage/64 = 4, and then ceil(c/16) <= c/4 of them, so all
 // groups together make at most n_slots/(4T).
 static_assert(kMinStage / 64 >= 4 && kLongSteps == 16, "long-list bound");
 static_assert(sizeof(Status) + sizeof(int64_t) * kBoxWords <= kHeadBytes, "head of the scratch");
-static_assert(kHeadBytes + sizeof(int64_t) * (kChunkBlocks + kScanBlocks) <= kNoAllocExtra,
+static_assert(kHeadBytes + sizeof(int64_t) * (kChunkBlocks + 2 * kScanBlocks) <= kNoAllocExtra,
               "head and shares of the fixed scratch");
-constexpr size_t kShareBytes = sizeof(int64_t) * (kChunkBlocks + kScanBlocks);
+constexpr size_t kShareBytes = sizeof(int64_t) * (kChunkBlocks + 2 * kScanBlocks);
 
 int64_t long_capacity(int64_t n_slots, int32_t T) { return n_slots / (4 * int64_t(T)) + 1; }
 
@@ -634,25 +699,30 @@ int build_plan(int32_t n_rows, const int32_t* row_ptr, int32_t T, int32_t desire
   ResultBox box;
   int rc = box.init(nullptr);
   if (rc) return rc;
-  p->stream = s;
-  rc = scratch_alloc_async(&p->block, groups_b + tm_b + kShareBytes + sizeof(Status), s);
+  DeviceScratch work;
+  rc = p->block.alloc(groups_b + tm_b + kShareBytes + sizeof(Status), s);
+  if (rc == ARGCSR_OK)
+    rc = work.alloc(group_work_bytes(n_rows, T, format, region_rows, regions), s);
   if (rc) return rc;
-  char* base = static_cast<char*>(p->block);
+  char* base = static_cast<char*>(p->block.ptr());
   p->groups = reinterpret_cast<argcsr_group_info*>(base);
   p->tm = reinterpret_cast<int32_t*>(base + groups_b);
   auto* share_slots = reinterpret_cast<int64_t*>(base + groups_b + tm_b);
   p->heavy_parts = share_slots + kChunkBlocks;
-  auto* st = reinterpret_cast<Status*>(p->heavy_parts + kScanBlocks);
+  auto* st = reinterpret_cast<Status*>(p->heavy_parts + 2 * kScanBlocks);
   rc = group_on_device(n_rows, row_ptr, T, desired, format, region_rows, regions, p->groups,
                        &st->groups, reinterpret_cast<int32_t*>(st),
-                       int64_t(sizeof(Status) / sizeof(int32_t)), s);
+                       int64_t(sizeof(Status) / sizeof(int32_t)), work.ptr(), s);
   if (rc) return rc;
   launch_chunks(row_ptr, p->groups, 0, &st->groups, T, format, p->tm, share_slots, s);
   offsets_kernel<<<kScanBlocks, kScanBlock, 0, s>>>(p->groups, 0, &st->groups, T, share_slots,
-                                                    p->heavy_parts, st, row_ptr, n_rows, box.dev);
+                                                    p->heavy_parts, p->heavy_parts + kScanBlocks, st,
+                                                    row_ptr, n_rows, box.dev);
   ARGCSR_HIP(hipGetLastError());
   rc = box.read(s);
   if (rc) return rc;
+  p->block.idle();
+  work.idle();
   if (box.word[kBoxBadRowPtr])
     return fail(ARGCSR_EINVAL, "row_ptr does not start at 0 or decreases");
   p->n_rows = n_rows;
@@ -663,6 +733,7 @@ int build_plan(int32_t n_rows, const int32_t* row_ptr, int32_t T, int32_t desire
   p->n_slots = box.word[kBoxSlots];
   p->n_heavy = int32_t(box.word[kBoxHeavy]);
   p->nnz = box.word[kBoxNnz];
+  p->n_long = box.word[kBoxLong];
   return ARGCSR_OK;
 }
 
@@ -810,29 +881,30 @@ int convert_impl(int32_t n_rows, int32_t n_cols, const int32_t* row_ptr_host,
       (nnz > 0 && (!col || !val)))
     return fail(ARGCSR_EINVAL, "NULL device buffer");
 
-  StreamScratch ws;
+  DeviceScratch ws;
   void* base = fixed_ptr;
   if (!fixed) {
     rc = ws.alloc(convert_scratch(out->n_slots, T), s);
     if (rc) return rc;
-    base = ws.ptr;
+    base = ws.ptr();
   }
-  Status* st = static_cast<Status*>(base);
+  auto* st = static_cast<Status*>(base);
   auto* share_slots = reinterpret_cast<int64_t*>(static_cast<char*>(base) + kHeadBytes);
   const int64_t* heavy_parts = share_slots + kChunkBlocks;
   // (group, first step) per tile of the fill's long blocks
-  int32_t* long_list = reinterpret_cast<int32_t*>(share_slots + kChunkBlocks + kScanBlocks);
+  int2* long_list = reinterpret_cast<int2*>(share_slots + kChunkBlocks + 2 * kScanBlocks);
   ResultBox box;
   rc = box.init(fixed ? reinterpret_cast<int64_t*>(st + 1) : nullptr);
   if (rc) return rc;
   // uses the caller's slot count; it is checked against the device total
   // before anything is written to the caller's heavy_groups buffer
   const int32_t heavy_chunk = out->heavy_chunk;
-  int64_t slots = 0, heavy = 0;
+  int64_t slots = 0, heavy = 0, n_long = 0;
 
   if (planned) {
     slots = planned->n_slots;
     heavy = planned->n_heavy;
+    n_long = planned->n_long;
   } else {
     clear_words_kernel<<<1, 64, 0, s>>>(static_cast<int32_t*>(base),
                                         int32_t(kHeadBytes / sizeof(int32_t)));
@@ -841,14 +913,16 @@ int convert_impl(int32_t n_rows, int32_t n_cols, const int32_t* row_ptr_host,
                                 sizeof(argcsr_group_info) * size_t(G), hipMemcpyHostToDevice, s));
     launch_chunks(row_ptr, out->groups, G, nullptr, T, out->format, out->threads_mapping,
                   share_slots, s);
+    int64_t* parts = share_slots + kChunkBlocks;
     offsets_kernel<<<kScanBlocks, kScanBlock, 0, s>>>(out->groups, G, nullptr, T, share_slots,
-                                                      share_slots + kChunkBlocks, st, row_ptr,
+                                                      parts, parts + kScanBlocks, st, row_ptr,
                                                       n_rows, box.dev);
     ARGCSR_HIP(hipGetLastError());
     rc = box.read(s);
     if (rc) return rc;
     slots = box.word[kBoxSlots];
     heavy = box.word[kBoxHeavy];
+    n_long = box.word[kBoxLong];
   }
   if (slots > INT32_MAX)
     return fail(ARGCSR_EOVERFLOW, "%lld slots exceed INT32_MAX", (long long)slots);
@@ -864,29 +938,32 @@ int convert_impl(int32_t n_rows, int32_t n_cols, const int32_t* row_ptr_host,
     const int64_t blocks = std::min<int64_t>((4 * int64_t(G) + n_rows + 255) / 256, 2048);
     adopt_plan_kernel<<<dim3(uint32_t(blocks)), 256, 0, s>>>(
         reinterpret_cast<const int32_t*>(planned->groups), 4 * int64_t(G), planned->tm, n_rows,
-        reinterpret_cast<int32_t*>(out->groups), out->threads_mapping, st);
+        reinterpret_cast<int32_t*>(out->groups), out->threads_mapping);
   }
-  if (out->heavy_groups && out->n_heavy > 0)
-    heavy_scatter_kernel<<<kScanBlocks, kScanBlock, 0, s>>>(out->groups, G, heavy_chunk,
-                                                            heavy_parts, out->heavy_groups);
+  const int32_t stage = fill_stage(T, out->n_slots, G);
+  if ((out->heavy_groups && out->n_heavy > 0) || n_long > 0)
+    schedule_kernel<<<kScanBlocks, kScanBlock, 0, s>>>(
+        out->groups, G, heavy_chunk, stage, heavy_parts, heavy_parts + kScanBlocks,
+        out->n_heavy > 0 ? out->heavy_groups : nullptr, long_list);
 
   switch (out->dtype) {
     case ARGCSR_F64:
-      launch_fill<ARGCSR_F64>(G, s, row_ptr, col, val, st, box.dev, long_list, out);
+      launch_fill<ARGCSR_F64>(s, row_ptr, col, val, stage, box.dev, long_list, int32_t(n_long), out);
       break;
     case ARGCSR_F32:
-      launch_fill<ARGCSR_F32>(G, s, row_ptr, col, val, st, box.dev, long_list, out);
+      launch_fill<ARGCSR_F32>(s, row_ptr, col, val, stage, box.dev, long_list, int32_t(n_long), out);
       break;
     case ARGCSR_BF16:
-      launch_fill<ARGCSR_BF16>(G, s, row_ptr, col, val, st, box.dev, long_list, out);
+      launch_fill<ARGCSR_BF16>(s, row_ptr, col, val, stage, box.dev, long_list, int32_t(n_long), out);
       break;
     default:
-      launch_fill<ARGCSR_F16>(G, s, row_ptr, col, val, st, box.dev, long_list, out);
+      launch_fill<ARGCSR_F16>(s, row_ptr, col, val, stage, box.dev, long_list, int32_t(n_long), out);
       break;
   }
   ARGCSR_HIP(hipGetLastError());
   rc = box.read(s);
   if (rc) return rc;
+  ws.idle();
   if (box.word[kBoxBadColumn])
     return fail(ARGCSR_EINVAL, "a column index lies outside [0, %d)", n_cols);
   return ARGCSR_OK;

@@ -15,7 +15,7 @@
 #include <vector>
 
 #include "common.hpp"
-#include "group.hpp"
+#include "scratch.hpp"
 #include "values.hpp"
 
 namespace argcsr {
@@ -386,17 +386,15 @@ extern "C" int argcsr_csr_bin_rows(int32_t n_rows, const int32_t* row_ptr, int32
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int64_t blocks = (int64_t(n_rows) + kCsrBlock - 1) / kCsrBlock;
   const size_t bytes = sizeof(int32_t) * size_t(blocks) * kBins;
-  int32_t* d_counts = nullptr;
-  int rc = scratch_alloc_async(reinterpret_cast<void**>(&d_counts), bytes, s);
+  DeviceScratch ws;
+  const int rc = ws.alloc(bytes, s);
   if (rc) return rc;
+  int32_t* d_counts = static_cast<int32_t*>(ws.ptr());
   bin_count_kernel<<<dim3(uint32_t(blocks)), kCsrBlock, 0, s>>>(n_rows, row_ptr, d_counts);
   std::vector<int32_t> h(size_t(blocks) * kBins);
   hipError_t e = hipMemcpyAsync(h.data(), d_counts, bytes, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) {
-    (void)hipFreeAsync(d_counts, s);
-    return fail(ARGCSR_EHIP, "binning counts: %s", hipGetErrorString(e));
-  }
+  if (e != hipSuccess) return fail(ARGCSR_EHIP, "binning counts: %s", hipGetErrorString(e));
   // offsets: bin by bin, workgroup by workgroup (rows ascend within a bin)
   int64_t total = 0;
   for (int k = 0; k < kBins; ++k) {
@@ -414,9 +412,9 @@ extern "C" int argcsr_csr_bin_rows(int32_t n_rows, const int32_t* row_ptr, int32
                                                                    rows);
     e = hipGetLastError();
   }
-  (void)hipFreeAsync(d_counts, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return fail(ARGCSR_EHIP, "binning: %s", hipGetErrorString(e));
+  ws.idle();
   return ARGCSR_OK;
 }
 

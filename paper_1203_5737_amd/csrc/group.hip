@@ -28,8 +28,6 @@
 // written) took 75 us.
 #include <hip/hip_runtime.h>
 
-#include <mutex>
-
 #include "common.hpp"
 #include "group.hpp"
 
@@ -256,74 +254,54 @@ __global__ __launch_bounds__(kGroupBlock) void group_emit_kernel(
 
 }  // namespace
 
-int scratch_alloc_async(void** p, size_t bytes, hipStream_t s) {
-  constexpr int kMaxDevices = 64;
-  static std::mutex mu;
-  static hipMemPool_t pools[kMaxDevices] = {};
-  int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices)
-    return fail(ARGCSR_EHIP, "no current device");
-  hipMemPool_t pool = nullptr;
-  {
-    std::lock_guard<std::mutex> lock(mu);
-    if (!pools[dev]) {
-      hipMemPoolProps props{};
-      props.allocType = hipMemAllocationTypePinned;
-      props.location.type = hipMemLocationTypeDevice;
-      props.location.id = dev;
-      hipMemPool_t created = nullptr;
-      if (hipMemPoolCreate(&created, &props) != hipSuccess)
-        return fail(ARGCSR_ENOMEM, "memory pool of device %d could not be created", dev);
-      uint64_t keep_all = UINT64_MAX;
-      (void)hipMemPoolSetAttribute(created, hipMemPoolAttrReleaseThreshold, &keep_all);
-      pools[dev] = created;
-    }
-    pool = pools[dev];
-  }
-  if (hipMallocFromPoolAsync(p, bytes < 256 ? 256 : bytes, pool, s) != hipSuccess) {
-    *p = nullptr;
-    return fail(ARGCSR_ENOMEM, "device scratch of %zu bytes could not be allocated", bytes);
-  }
-  return ARGCSR_OK;
+namespace {
+
+// The work area: maps | entries | regions | bad flags | steps.
+struct Work {
+  int64_t n_blocks, n_regions;
+  size_t entries, regions, bad, steps, bytes;       // byte offsets, and the end
+};
+
+Work work_of(int32_t n, int32_t block_dim, int32_t format, int32_t region_rows,
+             const int32_t* region_desired) {
+  Work w;
+  w.n_blocks = (int64_t(n) + kGroupRows - 1) / kGroupRows;
+  w.n_regions = region_desired && format != ARGCSR_FORMAT_RG
+                    ? (int64_t(n) + region_rows - 1) / region_rows : 0;
+  w.entries = (sizeof(uint32_t) * size_t(w.n_blocks) * size_t(block_dim) + 7) & ~size_t(7);
+  w.regions = w.entries + sizeof(int2) * size_t(w.n_blocks);
+  w.bad = w.regions + sizeof(int32_t) * size_t(w.n_regions);
+  w.steps = w.bad + sizeof(int32_t) * size_t(w.n_blocks);
+  w.bytes = w.steps + sizeof(uint16_t) * size_t(n);
+  return w;
 }
 
-int StreamScratch::alloc(size_t bytes, hipStream_t s) {
-  stream = s;
-  if (scratch_alloc_async(&ptr, bytes, s) != ARGCSR_OK) {
-    ptr = nullptr;
-    return fail(ARGCSR_ENOMEM, "device scratch of %zu bytes could not be allocated", bytes);
-  }
-  return ARGCSR_OK;
+}  // namespace
+
+size_t group_work_bytes(int32_t n, int32_t block_dim, int32_t format, int32_t region_rows,
+                        const int32_t* region_desired) {
+  return work_of(n, block_dim, format, region_rows, region_desired).bytes;
 }
 
 int group_on_device(int32_t n, const int32_t* row_ptr, int32_t block_dim, int32_t desired,
                     int32_t format, int32_t region_rows, const int32_t* region_desired,
                     argcsr_group_info* groups, GroupCount* count, int32_t* clear,
-                    int64_t clear_words, hipStream_t s) {
+                    int64_t clear_words, void* work, hipStream_t s) {
   const bool row_grouped = format == ARGCSR_FORMAT_RG;
-  const int64_t n_blocks = (int64_t(n) + kGroupRows - 1) / kGroupRows;
-  const int64_t n_regions =
-      region_desired && !row_grouped ? (int64_t(n) + region_rows - 1) / region_rows : 0;
-  // maps | entries | regions | bad flags | steps
-  const size_t maps_b = sizeof(uint32_t) * size_t(n_blocks) * size_t(block_dim);
-  const size_t entries_b = sizeof(int2) * size_t(n_blocks);
-  const size_t regions_b = sizeof(int32_t) * size_t(n_regions);
-  StreamScratch ws;
-  const size_t maps_up = (maps_b + 7) & ~size_t(7);
-  int rc = ws.alloc(maps_up + entries_b + regions_b + sizeof(int32_t) * size_t(n_blocks) +
-                    sizeof(uint16_t) * size_t(n), s);
-  if (rc) return rc;
-  char* p = static_cast<char*>(ws.ptr);
+  const Work w = work_of(n, block_dim, format, region_rows, region_desired);
+  char* p = static_cast<char*>(work);
   auto* maps = reinterpret_cast<uint32_t*>(p);
-  auto* entries = reinterpret_cast<int2*>(p + maps_up);
-  auto* regions = reinterpret_cast<int32_t*>(p + maps_up + entries_b);
-  auto* bad = reinterpret_cast<int32_t*>(p + maps_up + entries_b + regions_b);
-  auto* steps = reinterpret_cast<uint16_t*>(bad + n_blocks);
-  if (n_regions)
-    ARGCSR_HIP(hipMemcpyAsync(regions, region_desired, regions_b, hipMemcpyHostToDevice, s));
+  auto* entries = reinterpret_cast<int2*>(p + w.entries);
+  auto* regions = reinterpret_cast<int32_t*>(p + w.regions);
+  auto* bad = reinterpret_cast<int32_t*>(p + w.bad);
+  auto* steps = reinterpret_cast<uint16_t*>(p + w.steps);
+  const int64_t n_blocks = w.n_blocks;
+  if (w.n_regions)
+    ARGCSR_HIP(hipMemcpyAsync(regions, region_desired, sizeof(int32_t) * size_t(w.n_regions),
+                              hipMemcpyHostToDevice, s));
   group_map_kernel<<<dim3(uint32_t(n_blocks)), kGroupBlock, 0, s>>>(
       n, row_ptr, block_dim, row_grouped ? INT64_MAX / 2 : int64_t(desired) * block_dim,
-      region_rows > 0 ? region_rows : 1, n_regions ? regions : nullptr, steps, maps, bad);
+      region_rows > 0 ? region_rows : 1, w.n_regions ? regions : nullptr, steps, maps, bad);
   group_entry_kernel<<<1, kEntryBlock, 0, s>>>(int32_t(n_blocks), block_dim, maps, entries, bad,
                                                count, clear, clear_words);
   group_emit_kernel<<<dim3(uint32_t(n_blocks)), kGroupBlock, 0, s>>>(n, steps, entries, groups);

@@ -1,5 +1,4 @@
-// Conversion step 1 (grouping) on the GPU (group.hip), and the library's
-// stream-ordered device scratch.
+// Conversion step 1 (grouping) on the GPU (group.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -27,29 +26,13 @@ struct GroupCount {
 // format ARGCSR_FORMAT_RG: groups of block_dim rows (no nonzero budget);
 // region_desired (host, checked by the caller): a desiredChunkSize per region
 // of region_rows rows, taken from the region of a group's first row.
+// `work` is device scratch of group_work_bytes, in use until the stream has
+// been waited for.
+size_t group_work_bytes(int32_t n, int32_t block_dim, int32_t format, int32_t region_rows,
+                        const int32_t* region_desired);
 int group_on_device(int32_t n, const int32_t* row_ptr, int32_t block_dim, int32_t desired,
                     int32_t format, int32_t region_rows, const int32_t* region_desired,
                     argcsr_group_info* groups, GroupCount* count, int32_t* clear,
-                    int64_t clear_words, hipStream_t s);
-
-// Stream-ordered device allocation from the library's own memory pool on
-// the current device (created on first use, one per device, with a release
-// threshold that keeps freed memory in the pool: repeated conversions reuse
-// their scratch instead of mapping it again at every synchronisation).  The
-// pool holds at most the largest scratch any call needed until the process
-// ends.  Free with hipFreeAsync.
-int scratch_alloc_async(void** p, size_t bytes, hipStream_t s);
-
-// Device scratch allocated and freed in stream order (scratch_alloc_async /
-// hipFreeAsync): work queued on the stream may still use it after the
-// owner goes out of scope, and concurrent conversions never share it.
-struct StreamScratch {
-  void* ptr = nullptr;
-  hipStream_t stream = nullptr;
-  int alloc(size_t bytes, hipStream_t s);
-  ~StreamScratch() {
-    if (ptr) (void)hipFreeAsync(ptr, stream);
-  }
-};
+                    int64_t clear_words, void* work, hipStream_t s);
 
 }  // namespace argcsr

@@ -6,6 +6,8 @@ row (exact where that sum is 0).  Reduced-precision SpMV (FP32 accumulation)
 is checked against the FP64 oracle evaluated on the stored (rounded) values
 with the worst-case bound gamma_{L+1}(2^-24) * sum_j |a_ij x_j|.
 """
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -284,6 +286,48 @@ def test_default_conversion_around_its_grouping_rule(ac, n):
     A = csr_from_lengths(np.random.default_rng(n).integers(0, 9, n), 500, n)
     compare_conversion(ac, A, 64, 1, oracle.F64)
     compare_conversion(ac, A, 128, 3, oracle.F32, fmt=ac.FORMAT_RG)
+
+
+@pytest.mark.parametrize("T", [1, 33, 64, 130, 1024])
+def test_conversion_of_long_tiles(ac, T):
+    """Groups with none, a few (one lane lists them) and many (a wave does) of
+    the fill's tiles of 16 steps, chunk sizes around a stage of 64 chunks and
+    around one tile, and rows of one chunk between rows of many."""
+    L = [1] * 300 + [64 * T] * 2 + [0] * T + [5 * T, 15 * T, 16 * T, 17 * T, 32 * T + 1]
+    L += [8 * 16 * T, 8 * 16 * T + 1, 3] + ([66 * 16 * T] if T <= 130 else []) + [2] * 70
+    A = csr_from_lengths(L, 200_000, T)
+    for dt in (oracle.F64, oracle.BF16):
+        compare_conversion(ac, A, T, 1, dt)
+        compare_conversion(ac, A, T, 1, dt, device_grouping=True, keep_plan=True)
+    if T <= 64:
+        compare_conversion(ac, A, T, 1, oracle.F32, fmt=ac.FORMAT_RG, device_grouping=True)
+
+
+def test_conversions_on_two_streams_share_no_scratch(ac):
+    """Threads that convert matrices of different sizes, each on its own
+    stream, over and over."""
+    mats = [csr_from_lengths(np.random.default_rng(i).integers(0, 9 + 200 * (i == 2), n), 900, i)
+            for i, n in enumerate([20_000, 60_000, 9_000])]
+    refs = [oracle.convert(A.rp, A.col, A.val, 64, 1) for A in mats]
+    bad = []
+
+    def work(i):
+        A, ref, stream = mats[i], refs[i], torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            dev = ac.to_device_csr(A.rp, A.col, A.val, A.n_cols, DEV)
+            for _ in range(12):
+                M = ac.convert(dev, 64, 1, device_grouping=True)
+                got = (M.groups, M.threads_mapping, M.columns)
+                want = (ref.groups, ref.tm, ref.columns)
+                if not all(np.array_equal(g.cpu().numpy(), w) for g, w in zip(got, want)):
+                    bad.append(i)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
 
 
 def test_device_grouping_random(ac):
