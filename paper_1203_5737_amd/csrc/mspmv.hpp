@@ -65,12 +65,13 @@ __global__ __launch_bounds__(kSpmvWaves * 64) void mspmv_kernel(
   if (b < total_heavy) {                            // a heavy group, the whole workgroup
     const int32_t m = find_owner(mw, &MatWork::heavy_begin, n_mats, b);
     const MatWork& w = mw[m];
-    const argcsr_group_info gi = global_ptr<const argcsr_group_info>(w.groups)[global_ptr<const int32_t>(w.heavy)[b - w.heavy_begin]];
-    spmv_group_split<DT, W, U>(gi.first_row, gi.size, gi.offset, gi.chunk_size, global_ptr<const int32_t>(w.tm),
-                               global_ptr<const int32_t>(w.columns),
-                               global_ptr<const S>(w.values),
-                               XGather<A>(global_ptr<const A>(w.x), w.n_cols), w.serial != 0,
-                               global_ptr<A>(w.y), ends[0], part_mem, wv);
+    const int32_t g = global_ptr<const int32_t>(w.heavy)[b - w.heavy_begin];
+    const argcsr_group_info gi = global_ptr<const argcsr_group_info>(w.groups)[g];
+    spmv_group_split<DT, W, U, false>(
+        gi.first_row, gi.size, gi.offset, gi.chunk_size, global_ptr<const int32_t>(w.tm),
+        global_ptr<const int32_t>(w.columns), global_ptr<const S>(w.values),
+        XGather<A>(global_ptr<const A>(w.x), w.n_cols), w.serial != 0, global_ptr<A>(w.y), ends[0],
+        part_mem, wv);
     return;
   }
   // the other groups, one wave each, every XCD a contiguous range of them
@@ -81,10 +82,10 @@ __global__ __launch_bounds__(kSpmvWaves * 64) void mspmv_kernel(
   const MatWork& w = mw[m];
   const argcsr_group_info gi = global_ptr<const argcsr_group_info>(w.groups)[i - w.group_begin];
   if (gi.chunk_size > w.heavy_chunk) return;        // done by a heavy workgroup
-  spmv_group<DT, W, U>(gi.first_row, gi.size, gi.offset, gi.chunk_size, global_ptr<const int32_t>(w.tm), global_ptr<const int32_t>(w.columns),
-                       global_ptr<const S>(w.values),
-                       XGather<A>(global_ptr<const A>(w.x), w.n_cols), w.serial != 0,
-                       global_ptr<A>(w.y), ends[wv]);
+  spmv_group<DT, W, U, false>(
+      gi.first_row, gi.size, gi.offset, gi.chunk_size, global_ptr<const int32_t>(w.tm),
+      global_ptr<const int32_t>(w.columns), global_ptr<const S>(w.values),
+      XGather<A>(global_ptr<const A>(w.x), w.n_cols), w.serial != 0, global_ptr<A>(w.y), ends[wv]);
 }
 
 }  // namespace argcsr

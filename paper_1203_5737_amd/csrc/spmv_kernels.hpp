@@ -41,15 +41,26 @@ struct XGather {
   }
 };
 
+// The matrix is read non-temporally when one product reads it once (STREAM:
+// L2 stays with the x gathers), and with ordinary loads where the same
+// matrices are read again within microseconds, by other requests and the next
+// iteration (mspmv_kernel: a burst of solves on 670 000 resident rows took
+// 3400 us streamed, 3300 us so).
+template <bool STREAM, typename T>
+__device__ __forceinline__ T load_matrix(const T* p) {
+  if constexpr (STREAM) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+
 // This lane's threads-mapping entries (rows l = 64*w + lane of the group).
-template <int W>
+template <int W, bool STREAM = true>
 __device__ __forceinline__ void load_mapping(int32_t first, int32_t size,
                                              const int32_t* __restrict__ tm, int32_t (&tmv)[W]) {
   const int lane = lane_id();
 #pragma unroll
   for (int w = 0; w < W; ++w) {
     const int l = w * 64 + lane;
-    tmv[w] = l < size ? __builtin_nontemporal_load(tm + first + l) : 0;
+    tmv[w] = l < size ? load_matrix<STREAM>(tm + first + l) : 0;
   }
 }
 
@@ -82,7 +93,7 @@ __device__ __forceinline__ void row_end_mask(const int32_t (&tmv)[W], int32_t* e
 // issued one at a time, each followed by its FMA: measured faster for
 // 8-byte values with long chunk loops, where the stream, not the gathers,
 // is the limit (see gather_mode).  The sums are the same in both modes.
-template <int DT, int W, int U>
+template <int DT, int W, int U, bool STREAM = true>
 __device__ __forceinline__ void chunk_partials(
     int32_t offset, int32_t j0, int32_t j1, const int32_t* __restrict__ columns,
     const typename Val<DT>::storage* __restrict__ values,
@@ -97,16 +108,15 @@ __device__ __forceinline__ void chunk_partials(
   for (int w = 0; w < W; ++w) { acc[w] = A(0); alive[w] = true; }
   const int32_t* cb = columns + offset + lane;
   const S* vb = values + offset + lane;
-  // steps j .. j+U-1 (steps past j1 read as padding); streamed once:
-  // non-temporal, keeping L2 for the x gathers
+  // steps j .. j+U-1 (steps past j1 read as padding)
   auto load = [&](int32_t j, int32_t (&c)[U][W], S (&v)[U][W]) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
 #pragma unroll
       for (int w = 0; w < W; ++w) {
         if (j + u < j1) {
-          c[u][w] = __builtin_nontemporal_load(cb + (j + u) * T + w * 64);
-          v[u][w] = __builtin_nontemporal_load(vb + (j + u) * T + w * 64);
+          c[u][w] = load_matrix<STREAM>(cb + (j + u) * T + w * 64);
+          v[u][w] = load_matrix<STREAM>(vb + (j + u) * T + w * 64);
         } else {
           c[u][w] = -1;
           v[u][w] = S(0);
@@ -224,7 +234,7 @@ __device__ __forceinline__ void row_sums(int32_t first, int32_t size, int32_t n_
 }
 
 // One whole group with the calling wave.
-template <int DT, int W, int U>
+template <int DT, int W, int U, bool STREAM = true>
 __device__ __forceinline__ void spmv_group(
     int32_t first, int32_t size, int32_t offset, int32_t c,
     const int32_t* __restrict__ tm, const int32_t* __restrict__ columns,
@@ -233,10 +243,10 @@ __device__ __forceinline__ void spmv_group(
     int32_t* ends) {
   using A = typename Val<DT>::acc;
   int32_t tmv[W];
-  load_mapping<W>(first, size, tm, tmv);           // in flight with the first chunk loads
+  load_mapping<W, STREAM>(first, size, tm, tmv);           // in flight with the first chunk loads
   const int32_t n_mapped = tm[first + size - 1];    // chunks in use; the rest are free
   A acc[W];
-  chunk_partials<DT, W, U>(offset, 0, c, columns, values, gx, serial, acc);
+  chunk_partials<DT, W, U, STREAM>(offset, 0, c, columns, values, gx, serial, acc);
   uint64_t emask[W];
   row_end_mask<W>(tmv, ends, emask);
   row_sums<DT, W>(first, size, n_mapped, emask, acc, y);
@@ -246,7 +256,7 @@ __device__ __forceinline__ void spmv_group(
 // steps [q*share, (q+1)*share); waves 1.. leave their partials in LDS and
 // wave 0 adds them in wave order (a fixed order: results are deterministic),
 // then forms the row sums.  Every wave of the block must call this.
-template <int DT, int W, int U>
+template <int DT, int W, int U, bool STREAM = true>
 __device__ __forceinline__ void spmv_group_split(
     int32_t first, int32_t size, int32_t offset, int32_t c,
     const int32_t* __restrict__ tm, const int32_t* __restrict__ columns,
@@ -258,9 +268,9 @@ __device__ __forceinline__ void spmv_group_split(
   const int32_t share = (c + kSpmvWaves - 1) / kSpmvWaves;
   const int32_t j0 = min(c, wv * share), j1 = min(c, j0 + share);
   int32_t tmv[W];
-  load_mapping<W>(first, size, tm, tmv);
+  load_mapping<W, STREAM>(first, size, tm, tmv);
   A acc[W];
-  chunk_partials<DT, W, U>(offset, j0, j1, columns, values, gx, serial, acc);
+  chunk_partials<DT, W, U, STREAM>(offset, j0, j1, columns, values, gx, serial, acc);
   if (wv > 0) {
 #pragma unroll
     for (int w = 0; w < W; ++w) part[wv - 1][w * 64 + lane] = acc[w];
