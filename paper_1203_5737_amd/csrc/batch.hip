@@ -51,7 +51,7 @@ __device__ __forceinline__ void run_heavy(const BatchMat& m, int32_t g, int32_t*
                                           typename Val<DT>::acc* part_mem, int wv) {
   using Vt = Val<DT>;
   using A = typename Vt::acc;
-  const argcsr_group_info gi = global_ptr<const argcsr_group_info>(m.groups)[g];
+  const argcsr_group_info gi = load_group(global_ptr<const argcsr_group_info>(m.groups) + g);
   spmv_group_split<DT, W, U>(gi.first_row, gi.size, gi.offset, gi.chunk_size, global_ptr<const int32_t>(m.tm),
                              global_ptr<const int32_t>(m.columns),
                              global_ptr<const typename Vt::storage>(m.values),

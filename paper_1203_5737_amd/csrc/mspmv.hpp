@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kSpmvWaves * 64) void mspmv_kernel(
     const int32_t m = find_owner(mw, &MatWork::heavy_begin, n_mats, b);
     const MatWork& w = mw[m];
     const int32_t g = global_ptr<const int32_t>(w.heavy)[b - w.heavy_begin];
-    const argcsr_group_info gi = global_ptr<const argcsr_group_info>(w.groups)[g];
+    const argcsr_group_info gi = load_group(global_ptr<const argcsr_group_info>(w.groups) + g);
     spmv_group_split<DT, W, U, false>(
         gi.first_row, gi.size, gi.offset, gi.chunk_size, global_ptr<const int32_t>(w.tm),
         global_ptr<const int32_t>(w.columns), global_ptr<const S>(w.values),
@@ -80,7 +80,8 @@ __global__ __launch_bounds__(kSpmvWaves * 64) void mspmv_kernel(
   if (i >= total_groups) return;
   const int32_t m = find_owner(mw, &MatWork::group_begin, n_mats, i);
   const MatWork& w = mw[m];
-  const argcsr_group_info gi = global_ptr<const argcsr_group_info>(w.groups)[i - w.group_begin];
+  const argcsr_group_info gi =
+      load_group(global_ptr<const argcsr_group_info>(w.groups) + (i - w.group_begin));
   if (gi.chunk_size > w.heavy_chunk) return;        // done by a heavy workgroup
   spmv_group<DT, W, U, false>(
       gi.first_row, gi.size, gi.offset, gi.chunk_size, global_ptr<const int32_t>(w.tm),

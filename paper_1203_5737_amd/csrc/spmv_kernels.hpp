@@ -52,7 +52,23 @@ __device__ __forceinline__ T load_matrix(const T* p) {
   else return *p;
 }
 
+// A group's record (the same for the whole wave) in one scalar load.  Left to
+// itself the compiler fetches the chunk size first, for the heavy test, and the
+// other members in one or two more round trips where they are used; the empty
+// asm keeps the four together.
+__device__ __forceinline__ argcsr_group_info load_group(const argcsr_group_info* p) {
+  typedef int32_t record __attribute__((ext_vector_type(4), aligned(4)));
+  const record r = *reinterpret_cast<const record*>(p);
+  int32_t first = wave_uniform(r.x), size = wave_uniform(r.y);
+  int32_t offset = wave_uniform(r.z), chunk = wave_uniform(r.w);
+  asm("" : "+s"(first), "+s"(size), "+s"(offset), "+s"(chunk));
+  return argcsr_group_info{first, size, offset, chunk};
+}
+
 // This lane's threads-mapping entries (rows l = 64*w + lane of the group).
+// Every lane loads, past the end of the group its last entry: a load under a
+// condition is waited for where the condition ends, before the chunk loads go
+// out, one round trip for each w.
 template <int W, bool STREAM = true>
 __device__ __forceinline__ void load_mapping(int32_t first, int32_t size,
                                              const int32_t* __restrict__ tm, int32_t (&tmv)[W]) {
@@ -60,7 +76,7 @@ __device__ __forceinline__ void load_mapping(int32_t first, int32_t size,
 #pragma unroll
   for (int w = 0; w < W; ++w) {
     const int l = w * 64 + lane;
-    tmv[w] = l < size ? load_matrix<STREAM>(tm + first + l) : 0;
+    tmv[w] = load_matrix<STREAM>(tm + first + (l < size ? l : size - 1));
   }
 }
 
@@ -78,7 +94,7 @@ __device__ __forceinline__ void row_end_mask(const int32_t (&tmv)[W], int32_t* e
   wave_lds_sync();
 #pragma unroll
   for (int w = 0; w < W; ++w) {
-    const uint32_t e = uint32_t(tmv[w] - 1);        // rows beyond `size` hold 0 -> skipped
+    const uint32_t e = uint32_t(tmv[w] - 1);        // lanes past `size` mark the last row's again
     if (e < uint32_t(T)) ends[e] = 1;
   }
   wave_lds_sync();
@@ -188,10 +204,12 @@ __device__ __forceinline__ void chunk_partials(
     }
   } else {
     // 8-byte values: one batch of U steps at a time (double buffering would
-    // cost occupancy)
+    // cost occupancy).  The first stands before the loop: a load at the loop's
+    // head first waits for all that are in flight, here the threads mapping.
+    if (j0 < j1) load(j0, cc, vv);
     for (int j = j0; j < j1; j += U) {
-      load(j, cc, vv);
       if (!consume(cc, vv)) break;               // every chunk reached its padding
+      if (j + U < j1) load(j + U, cc, vv);
     }
   }
 }
@@ -306,7 +324,7 @@ __global__ __launch_bounds__(kSpmvWaves * 64) void argcsr_spmv_kernel(
   const XGather<A> gx(x, n_cols);
   const int32_t b = int32_t(blockIdx.x);
   if (b < n_heavy) {
-    const argcsr_group_info gi = groups[heavy[b]];
+    const argcsr_group_info gi = load_group(groups + heavy[b]);
     spmv_group_split<DT, W, U>(gi.first_row, gi.size, gi.offset, gi.chunk_size, tm, columns,
                                values, gx, serial != 0, y, ends[0], part, wv);
     return;
@@ -314,7 +332,7 @@ __global__ __launch_bounds__(kSpmvWaves * 64) void argcsr_spmv_kernel(
   const uint32_t nb = gridDim.x - uint32_t(n_heavy);
   const int g = int(xcd_remap(uint32_t(b - n_heavy), nb)) * kSpmvWaves + wv;
   if (g >= n_groups) return;
-  const argcsr_group_info gi = groups[g];
+  const argcsr_group_info gi = load_group(groups + g);
   if (gi.chunk_size > heavy_chunk) return;          // processed by a heavy block
   spmv_group<DT, W, U>(gi.first_row, gi.size, gi.offset, gi.chunk_size, tm, columns, values,
                        gx, serial != 0, y, ends[wv]);

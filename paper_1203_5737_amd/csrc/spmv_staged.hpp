@@ -217,7 +217,7 @@ __global__ __launch_bounds__(kSpmvWaves * 64) void argcsr_spmv_staged_kernel(
     split = false;
     if (g >= n_groups) return;
   }
-  const argcsr_group_info gi = groups[g];
+  const argcsr_group_info gi = load_group(groups + g);
   if (!split && gi.chunk_size > heavy_chunk) return;   // processed by a heavy block
   const int32_t tp = tile_ptr[g];
   // at most the tiles this wave's LDS region holds (all, for a staging made
