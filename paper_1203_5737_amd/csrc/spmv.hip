@@ -65,16 +65,22 @@ int launch_staged(const argcsr_matrix* A, const void* x, void* y, hipStream_t s)
   return ARGCSR_OK;
 }
 
-// Steps per load batch of the staged kernel with x in LDS, chosen by a
-// sweep on the 27-point stencil (MI355X, cold): FP64 x at W = 1 takes 16
-// (124.0 us against 126.5 with 8), at W = 2 and 4 fewer steps than the plain
-// kernel (139.5 us with 2 against 149.3 with 4 at W = 2; 137.5 with 1
-// against 152.6 with 2 at W = 4); 4- and 2-byte values at W = 2 take 2
-// (FP32 71.2 against 73.2 us, BF16 56.0 against 56.6).
+// Steps per load batch of the staged kernel, chosen by a sweep (MI355X, x in
+// LDS): large batches put a small matrix's few waves through fewer round trips
+// but cost registers, and a group shorter than a batch goes step by step.  us
+// for the 27-point stencil of 128^3 and 70^3 rows and the 5-point one of 900^2,
+// the choice first:
+//   FP64  W = 1:  8 101 / 20 / 13.3, 16 102 / 21 / 16.5, 4 102 / 22 / 12.2
+//         W = 2:  3 97 / 19 / 11.8, 2 97 / 19 / 11.9, 4 98 / 20 / 11.9
+//         W = 4:  2 95 / 21 / 13.1, 1 97 / 24 / 12.9
+//   BF16  W = 1:  5 52 / 12 / 8.5, 8 52 / 13 / 11.7, 4 55 / 13 / 9.1
+//         W = 2:  3 48 / 13 / 8.6, 2 47 / 15 / 8.0, 4 49 / 13 / 8.7
+//         W = 4:  2 47 / 17 / 8.9, 3 45 / 15 / 10.7, 4 51 / 17 / 10.2
+// FP32 orders them the same.
 template <int DT, int W>
 constexpr int staged_steps() {
-  if (sizeof(typename Val<DT>::acc) == 8) return W == 1 ? 16 : W == 2 ? 2 : 1;
-  return W == 1 ? 8 : W == 2 ? 2 : 2;
+  if (sizeof(typename Val<DT>::acc) == 8) return W == 1 ? 8 : W == 2 ? 3 : 2;
+  return W == 1 ? 5 : W == 2 ? 3 : 2;
 }
 
 template <int DT, int W, int U>
@@ -83,8 +89,9 @@ int launch_w(const argcsr_matrix* A, const void* x, void* y, hipStream_t s) {
     launch<DT, W, U>(A, x, y, s);
     return ARGCSR_OK;
   }
-  return A->stage_lds ? launch_staged<DT, W, staged_steps<DT, W>(), true>(A, x, y, s)
-                      : launch_staged<DT, W, U, false>(A, x, y, s);
+  constexpr int kSteps = staged_steps<DT, W>();
+  return A->stage_lds ? launch_staged<DT, W, kSteps, true>(A, x, y, s)
+                      : launch_staged<DT, W, kSteps, false>(A, x, y, s);
 }
 
 template <int DT>

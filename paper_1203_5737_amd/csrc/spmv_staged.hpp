@@ -20,6 +20,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "spmv_kernels.hpp"
 #include "stage.hpp"
 
@@ -78,16 +80,24 @@ __device__ __forceinline__ void stage_tiles(const A* __restrict__ x, int32_t n_c
 }
 
 // Partial sums of this lane's W chunks over steps [j0, j1) of a staged
-// group: as chunk_partials, with positions instead of columns.
-template <int DT, int W, int U, bool XLDS>
+// group: as chunk_partials, with positions instead of columns.  `stage_x`
+// makes x ready (and waits); the first loads of positions and values are in
+// flight by then.  Bound by how much of the streams a wave keeps in flight: with
+// the first loads behind the staging of x, and with waits between the loads of
+// a batch (below), the 27-point stencil of 128^3 rows took, at T = 64 / 128 /
+// 256, in FP64 105 / 129 / 126 us, now 101 / 97 / 95, and in BF16 87 / 49 / 51,
+// now 52 / 48 / 47; that of 70^3 rows in FP32 15.2 / 17.7 / 20.4, now 13.8 /
+// 13.1 / 17.3.
+template <int DT, int W, int U, bool XLDS, typename F>
 __device__ __forceinline__ void chunk_partials_staged(
     int32_t offset, int32_t j0, int32_t j1, const uint16_t* __restrict__ local,
     const typename Val<DT>::storage* __restrict__ values, const typename Val<DT>::acc* xs,
-    const TileTable& tt, const XGather<typename Val<DT>::acc>& gx,
+    const TileTable& tt, const XGather<typename Val<DT>::acc>& gx, F stage_x,
     typename Val<DT>::acc (&acc)[W]) {
   using Vt = Val<DT>;
   using S = typename Vt::storage;
   using A = typename Vt::acc;
+  using Held = std::conditional_t<sizeof(S) == 2, uint32_t, S>;
   constexpr int T = 64 * W;
   const int lane = lane_id();
   bool alive[W];
@@ -95,29 +105,33 @@ __device__ __forceinline__ void chunk_partials_staged(
   for (int w = 0; w < W; ++w) { acc[w] = A(0); alive[w] = true; }
   const uint16_t* pb = local + offset + lane;
   const S* vb = values + offset + lane;
-  auto load = [&](int32_t j, uint16_t (&p)[U][W], S (&v)[U][W]) {
+  // A position or 2-byte value has a 32-bit register of its own, and a step
+  // past j1 a value with more than 16 bits: 16-bit ones, or ones the compiler
+  // can narrow to 16 bits, are packed or masked right behind their loads, and
+  // so waited for one by one.
+  auto load = [&](int32_t j, uint32_t (&p)[U][W], Held (&v)[U][W], int32_t end) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
 #pragma unroll
       for (int w = 0; w < W; ++w) {
-        if (j + u < j1) {
+        if (j + u < end) {
           p[u][w] = __builtin_nontemporal_load(pb + (j + u) * T + w * 64);
           v[u][w] = __builtin_nontemporal_load(vb + (j + u) * T + w * 64);
         } else {
-          p[u][w] = kStagePad;
-          v[u][w] = S(0);
+          p[u][w] = ~0u;
+          v[u][w] = Held(~0u);
         }
       }
     }
   };
-  auto consume = [&](const uint16_t (&p)[U][W], const S (&v)[U][W]) {
+  auto consume = [&](const uint32_t (&p)[U][W], const Held (&v)[U][W], int32_t steps) {
     bool live[U][W];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
 #pragma unroll
       for (int w = 0; w < W; ++w) {
-        alive[w] = alive[w] && (p[u][w] != kStagePad);
-        live[u][w] = alive[w];
+        alive[w] = alive[w] && (p[u][w] < kStagePad || u >= steps);
+        live[u][w] = alive[w] && u < steps;
       }
     }
     A xv[U][W];
@@ -138,7 +152,7 @@ __device__ __forceinline__ void chunk_partials_staged(
     for (int u = 0; u < U; ++u) {
 #pragma unroll
       for (int w = 0; w < W; ++w) {
-        const A prod = __builtin_fma(Vt::load(v[u][w]), xv[u][w], acc[w]);
+        const A prod = __builtin_fma(Vt::load(S(v[u][w])), xv[u][w], acc[w]);
         acc[w] = live[u][w] ? prod : acc[w];
       }
     }
@@ -147,28 +161,32 @@ __device__ __forceinline__ void chunk_partials_staged(
     for (int w = 0; w < W; ++w) any |= alive[w];
     return __ballot(any) != 0;
   };
-  uint16_t pp[U][W];
-  S vv[U][W];
-  if constexpr (sizeof(S) < 8) {
-    if (j0 < j1) load(j0, pp, vv);
-    for (int j = j0; j < j1; j += U) {
-      uint16_t np[U][W];
-      S nv[U][W];
-      const bool more = j + U < j1;
-      if (more) load(j + U, np, nv);
-      if (!consume(pp, vv) || !more) break;
+  uint32_t pp[U][W];
+  Held vv[U][W];
+  // The steps left over from whole batches come first, and whole batches load
+  // without a condition, so that the wait for one leaves the next one's loads
+  // in flight: behind loads that may not have been issued the compiler has to
+  // wait for all.
+  const int32_t whole = (j1 - j0) / U;
+  const int32_t rest = (j1 - j0) - whole * U;
+  uint32_t np[U][W];
+  Held nv[U][W];
+  load(j0, np, nv, j0 + rest);
+  int32_t j = j0 + rest;
+  if (whole > 0) load(j, pp, vv, j + U);
+  stage_x();
+  if (rest > 0 && !consume(np, nv, rest)) return;
+  if (whole == 0) return;
+  for (; j + U < j1; j += U) {
+    load(j + U, np, nv, j + 2 * U);
+    if (!consume(pp, vv, U)) return;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < U; ++u) {
 #pragma unroll
-        for (int w = 0; w < W; ++w) { pp[u][w] = np[u][w]; vv[u][w] = nv[u][w]; }
-      }
-    }
-  } else {
-    for (int j = j0; j < j1; j += U) {
-      load(j, pp, vv);
-      if (!consume(pp, vv)) break;
+      for (int w = 0; w < W; ++w) { pp[u][w] = np[u][w]; vv[u][w] = nv[u][w]; }
     }
   }
+  consume(pp, vv, U);
 }
 
 // LDS bytes of one wave of the staged kernel: its x tiles (XLDS), reused
@@ -226,12 +244,14 @@ __global__ __launch_bounds__(kSpmvWaves * 64) void argcsr_spmv_staged_kernel(
   int32_t tmv[W];
   load_mapping<W>(gi.first_row, gi.size, tm, tmv);
   const TileTable tt = load_tile_table(tile_start, tile_len, tp, nt);
-  if constexpr (XLDS) stage_tiles<A>(x, n_cols, tt, nt, xs);
+  auto stage_x = [&] {
+    if constexpr (XLDS) stage_tiles<A>(x, n_cols, tt, nt, xs);
+  };
   A acc[W];
   if (!split) {
     const int32_t n_mapped = tm[gi.first_row + gi.size - 1];
     chunk_partials_staged<DT, W, U, XLDS>(gi.offset, 0, gi.chunk_size, local, values, xs, tt, gx,
-                                         acc);
+                                         stage_x, acc);
     wave_lds_sync();                                   // x tiles read: the region is free
     uint64_t emask[W];
     row_end_mask<W>(tmv, ends, emask);
@@ -244,7 +264,8 @@ __global__ __launch_bounds__(kSpmvWaves * 64) void argcsr_spmv_staged_kernel(
   const int32_t c = gi.chunk_size;
   const int32_t share = (c + kSpmvWaves - 1) / kSpmvWaves;
   const int32_t j0 = min(c, wv * share), j1 = min(c, j0 + share);
-  chunk_partials_staged<DT, W, U, XLDS>(gi.offset, j0, j1, local, values, xs, tt, gx, acc);
+  chunk_partials_staged<DT, W, U, XLDS>(gi.offset, j0, j1, local, values, xs, tt, gx,
+                                       stage_x, acc);
   wave_lds_sync();
   if (wv > 0) {
 #pragma unroll

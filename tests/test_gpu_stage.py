@@ -216,6 +216,27 @@ def test_stage_group_lengths(ac, T, per_row):
             assert np.array_equal(Ms.local.cpu().numpy().view(np.uint16), ref.local)
 
 
+@pytest.mark.parametrize("dtype", [0, 1, 2, 3])
+@pytest.mark.parametrize("T", [64, 128, 256])
+def test_staged_batches_of_steps(ac, T, dtype):
+    """Groups of T rows with 1 to 18 entries each (every remainder of a batch of
+    steps, shorter than one batch and longer than two), groups whose rows
+    differ (chunks end before the group's last step), and rows long enough for
+    a whole workgroup, whose waves take shares of any length."""
+    rng = np.random.default_rng(T + dtype)
+    lengths = np.concatenate([np.repeat(np.arange(1, 19), T), rng.integers(0, 19, 2 * T),
+                              [0] * T, [40 * T, 67 * T, 3]]).astype(np.int64)
+    n = lengths.size
+    rp = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    rows = np.repeat(np.arange(n), lengths)
+    k = np.arange(rp[-1]) - rp[rows]
+    w = min(n, 2048)                      # the long rows' columns: at most 32 tiles
+    col = np.where(lengths[rows] > 18, n - w + k % w,
+                   np.minimum(rows, n - 18) + k).astype(np.int32)
+    A = synth.Csr(n, n, rp, col, rng.uniform(-1.0, 1.0, rp[-1]))
+    run_case(ac, A, T, 18, dtype, 8, vec(n, 3, dtype))
+
+
 def test_stage_limits(ac):
     # 100 random columns over 10^5 per row: every group (one row) needs 100
     # one-column tiles, more than 64
