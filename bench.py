@@ -47,7 +47,7 @@ DTYPE_NAMES = {v: k for k, v in DTYPES.items()}
 VALUE_BYTES = {0: 8, 1: 4, 2: 2, 3: 2}
 # Sources each measured kernel's HBM traffic depends on: the SpMV kernels;
 # with staging of x, the staged kernel and the tile tables; in a batch, the
-# batch kernel, its work queue and the member choices of the autotuner.
+# batch kernel and the member choices of the autotuner.
 _CSRC = "paper_1203_5737_amd/csrc/"
 SOURCE_SETS = {
     "spmv": [_CSRC + f for f in ("spmv_kernels.hpp", "spmv.hip", "values.hpp", "common.hpp",
@@ -406,8 +406,7 @@ def batch_record(torch, ac, count, dtype, steps, warmup, cold=True, extras=True)
     per row, half clip(Zipf(2.2), 1, min(5000, n))), (T, D, format) chosen
     per matrix by argcsr_autotune_member (the batch-throughput model); a step
     is ONE replay of the
-    batch's hipGraph (queue reset + persistent kernel over all matrices'
-    groups)."""
+    batch's hipGraph (one kernel over all matrices' groups)."""
     import synth
     mats = synth.workload_batch(count)
     vdt = ac.vector_dtype(dtype)

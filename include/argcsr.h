@@ -204,8 +204,8 @@ int argcsr_choose_region_desired(int32_t n_rows, const int32_t* row_ptr_host,
  *   row_ptr  device int32[n_rows+1]
  *   other arguments as for argcsr_plan (n_heavy may be NULL)
  * Synchronous (reads the counts back).  Uses device scratch of about
- * 22 bytes a row, from the library's cache of at most 2 GiB a GPU.  Errors: EINVAL (bad sizes,
- * row_ptr not starting at 0 or decreasing), EOVERFLOW, ENOMEM, EHIP.
+ * 22 bytes a row, from the library's cache of at most 2 GiB a GPU.  Errors:
+ * EINVAL (bad sizes, row_ptr not starting at 0 or decreasing), EOVERFLOW, ENOMEM, EHIP.
  */
 int argcsr_plan_device(int32_t n_rows, const int32_t* row_ptr, int32_t block_dim,
                        int32_t desired_chunk_size, int32_t format, int32_t* n_groups,
@@ -419,10 +419,10 @@ typedef struct argcsr_batch argcsr_batch;
 
 /*
  * argcsr_batch_create -- prepares y_m = A_m x_m for m = 0..n_mats-1 as ONE
- * persistent kernel over a global queue of (matrix, group) work items
- * (groups with long chunk loops go to whole workgroups first, the others to
- * single waves in matrix and row order), and captures [queue reset, kernel] in a
- * hipGraph.  The same per-group computation as argcsr_spmv is used, so each
+ * kernel over a global list of (matrix, group) work items (groups with long
+ * chunk loops go to whole workgroups first, the others, in matrix and row
+ * order, in chunks of about equal cost to a workgroup each), and captures it
+ * in a hipGraph.  The same per-group computation as argcsr_spmv is used, so each
  * y_m is bitwise identical to argcsr_spmv on A_m alone.
  *   mats   host array of n_mats converted matrices, all of one dtype; block
  *          dims may differ (64, 128, 256)
@@ -441,7 +441,7 @@ int argcsr_batch_graph_launch(argcsr_batch* b, void* stream);
 /* Runs the batch on `stream` with ordinary kernel launches (asynchronous). */
 int argcsr_batch_launch(argcsr_batch* b, void* stream);
 
-/* Work-list sizes and persistent grid of a batch (any pointer may be NULL). */
+/* Work-list sizes and grid of a batch (any pointer may be NULL). */
 int argcsr_batch_info(const argcsr_batch* b, int32_t* n_items, int32_t* n_heavy, int32_t* grid);
 
 /* Waits for the batch's most recent launch (an event recorded on the stream
@@ -497,7 +497,7 @@ int argcsr_autotune(int32_t n_rows, int32_t n_cols, const int32_t* row_ptr_host,
 
 /*
  * argcsr_autotune_member -- the (T, D, format) for a matrix that will run as
- * one member of a batch (argcsr_batch_create), where the persistent kernel
+ * one member of a batch (argcsr_batch_create), where one kernel
  * overlaps the members and a member's cost is its share of the batch's
  * throughput rather than the time of its own launch.  The same candidates as
  * argcsr_autotune are ranked, without timing, by a model fitted to

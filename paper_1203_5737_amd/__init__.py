@@ -197,11 +197,11 @@ def plan_device(row_ptr: torch.Tensor, block_dim: int, desired_chunk_size: int, 
 # Rows from which convert() groups on the device although the host has the
 # row offsets: the host scans them for the sizes and again for the groups, the
 # device takes five launches and one wait.  Whole conversions on MI355X, host /
-# device grouping, us: 8281 rows of a 5-point Laplacian 123 / 122, 16 384 rows
-# 156 / 123, 10^6 rows 1799 / 181; power-law rows 8192 119 / 135, 16 384
-# 153 / 137, 10^6 2781 / 216; 27-point stencil 15 625 rows 118 / 124, 32 768
-# 139 / 124, 10^6 1362 / 264.
-_DEVICE_GROUPING_ROWS = 16384
+# device grouping, us: 5-point Laplacian of 4096 rows 74 / 79, 8281 91 / 79,
+# 16 384 120 / 79, 40 000 200 / 80; power-law rows 6000 81 / 87, 8192 89 / 90,
+# 16 384 107 / 91, 60 000 333 / 93; 27-point stencil of 6859 rows 73 / 78, 9261
+# 75 / 78; uniform rows 8192 113 / 85, 12 000 120 / 80.
+_DEVICE_GROUPING_ROWS = 8192
 
 
 def _groups_on_device(A: DeviceCsr) -> bool:
@@ -419,7 +419,7 @@ def csr_spmv_binned(A: DeviceCsr, x: torch.Tensor, bins: CsrBins,
 
 
 class Batch:
-    """Several converted matrices computed by one persistent launch
+    """Several converted matrices computed by one launch
     (argcsr_batch_create); y_m = A_m x_m for every member.  The x and y
     tensors are bound at creation and must stay alive (the batch keeps
     references)."""

@@ -9,7 +9,7 @@
 
 namespace argcsr {
 
-// One matrix of a batch as the persistent kernel sees it.
+// One matrix of a batch as the kernel sees it.
 struct BatchMat {
   const argcsr_group_info* groups;
   const int32_t* tm;

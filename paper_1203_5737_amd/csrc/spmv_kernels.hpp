@@ -1,5 +1,5 @@
 // Device routines for ARG-CSR SpMV, shared by the single-matrix kernel and
-// the batched work-queue kernel (Sec. 4 semantics: chunk partial sums, then
+// the batched kernels (Sec. 4 semantics: chunk partial sums, then
 // per-row sums of the partial sums).
 #pragma once
 

@@ -83,11 +83,11 @@ double model_us(int32_t dtype, int32_t n_rows, int32_t n_cols, int32_t G, int64_
 
 // Cost of a matrix as one member of a batch (argcsr_batch_create), in
 // microseconds of the batch's time, fitted to whole-batch cold timings of
-// the 256-matrix FP32 batch under 21 uniform (T, D) choices: the persistent
+// the 256-matrix FP32 batch under 21 uniform (T, D) choices: one
 // kernel overlaps the members, so only throughput counts -- the bytes of the
 // member's slots and groups at a rate that falls with the block size (a
-// group's wave streams more slots per step) and a cost per group (the work
-// queue hands out groups one by one).  The part that does not depend on the
+// group's wave streams more slots per step) and a cost per group (the
+// kernel of that time handed out groups one by one).  The part that does not depend on the
 // choice (x gathers, y, the row offsets) is left out.
 constexpr double kMemberBytesPerUs[3] = {5.25e6, 4.9e6, 4.0e6};  // T = 64, 128, 256
 constexpr double kMemberUsPerGroup = 3.5e-4;

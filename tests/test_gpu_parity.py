@@ -279,7 +279,7 @@ def test_device_grouping_blocks(ac, kind, n, T):
         assert ac.plan_device(rpd, T, 1, fmt=fmt) == ac.plan(rp, T, 1, fmt)
 
 
-@pytest.mark.parametrize("n", [16383, 16384, 16385, 40_000])
+@pytest.mark.parametrize("n", [8191, 8192, 8193, 16384, 40_000])
 def test_default_conversion_around_its_grouping_rule(ac, n):
     """convert() groups small matrices on the host and larger ones on the
     device; both give the oracle's bytes."""
