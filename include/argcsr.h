@@ -342,8 +342,7 @@ int argcsr_csr_spmv(int32_t n_rows, int32_t n_cols, int64_t nnz,
  * 2^(k-1) < L <= 2^k nonzeros (bin 0: L <= 1), bin 7 the rows longer than
  * 64; argcsr_csr_spmv_binned gives bin k < 7 2^k lanes per row (each such
  * row summed exactly as argcsr_csr_spmv with lanes_per_row = 2^k), each row
- * of bin 7 a wave of 64 lanes (up to 1024 nonzeros) or a workgroup of 256,
- * all in one launch. */
+ * of bin 7 a workgroup of 256 lanes, all in one launch. */
 #define ARGCSR_CSR_BINS 8
 
 /*

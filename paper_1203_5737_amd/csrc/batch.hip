@@ -61,11 +61,12 @@ __device__ __forceinline__ void run_heavy(const BatchMat& m, int32_t g, int32_t*
 }
 
 // Bound by the x gathers: the 29.5 M of the 48-matrix batch above run at
-// 175 G/s, where gathers and streams alone reach 185 to 225 G/s.  No workgroup
+// 179 G/s, where gathers and streams alone reach 185 to 225 G/s.  No workgroup
 // waits for another and nothing is counted in device memory: with persistent
 // workgroups that took their items from counters there, the 5120 waves' last,
 // failing atomics on each counter (about 12 ns each, one after another) cost
-// more than the gathers of a small batch.  That batch 225 -> 169 us, 256
+// more than the gathers of a small batch.  That batch 225 -> 169 us
+// (165 with the records and mappings of spmv_kernels.hpp loaded ahead), 256
 // matrices 973 -> 858, eight of up to 2*10^4 rows in BF16 44 -> 22.
 template <int DT>
 __global__ __launch_bounds__(kSpmvWaves * 64) void batch_spmv_kernel(

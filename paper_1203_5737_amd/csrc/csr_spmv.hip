@@ -7,9 +7,9 @@
 // Binned variant (still plain CSR, no other storage): the rows are grouped
 // by length once (argcsr_csr_bin_rows: bin k < 7 holds the rows of at most
 // 2^k nonzeros and more than 2^(k-1), bin 7 the longer ones), and one launch
-// gives each bin its own width: 2^k lanes per row, and for bin 7 a wave per
-// row of up to 1024 nonzeros, a 256-lane workgroup per longer row.  A row of bin k < 7 is summed exactly as by
-// the uniform kernel with V = 2^k.
+// gives each bin its own width: 2^k lanes per row, and for bin 7 a 256-lane
+// workgroup per row.  A row of bin k < 7 is summed exactly as by the uniform
+// kernel with V = 2^k.
 #include <hip/hip_runtime.h>
 
 #include <vector>
@@ -22,7 +22,6 @@ namespace argcsr {
 namespace {
 
 constexpr int kCsrBlock = 256;
-constexpr int kWaveRow = 1024;              // bin 7: longest row of one wave
 constexpr int kBins = ARGCSR_CSR_BINS;      // 8: widths 1, 2, 4, ..., 64, then a workgroup
 
 // sum plus fma(val, x[col], ...) over elements k, k + stride, ... below end, in that
@@ -162,9 +161,9 @@ __device__ __forceinline__ void binned_rows(const BinLaunch& bl, int k, int32_t 
 }
 
 // Bound by the x gathers on power-law rows and by the CSR stream on regular
-// ones.  MI355X: power-law rows of 10^6 FP64 125 us -> 90 (long rows first and
-// loaded eight elements at a time a lane 105, regions 90), 27-point stencil
-// 100^3 FP64 171 -> 105.
+// ones.  MI355X: power-law rows of 10^6 FP64 125 us -> 82 (long rows first and
+// loaded eight elements at a time a lane, regions, a workgroup per long row),
+// 27-point stencil 100^3 FP64 171 -> 105.
 template <int DT, int R>
 __global__ __launch_bounds__(kCsrBlock) void csr_binned_kernel(
     BinLaunch bl, const int32_t* __restrict__ rows, const int32_t* __restrict__ rp,
@@ -198,45 +197,26 @@ __global__ __launch_bounds__(kCsrBlock) void csr_binned_kernel(
     case 6: binned_rows<DT, 64, R>(bl, k, b, rows, rp, col, val, x, y); return;
     default: break;
   }
-  // bin 7: four rows, a wave each where the row is short enough for one
-  // (512, 1024 and 4096 measured within 3% on power-law rows); the others by
-  // the workgroup's 256 lanes together, wave sums added in wave order
+  // bin 7: a row by the workgroup's 256 lanes, wave sums added in wave order.
+  // (Four rows a workgroup, a wave each up to 1024 nonzeros: power-law rows, us
+  // so / now, in FP64 10^6 rows 88.5 / 81.3, 7*10^5 60 / 56, 1.3*10^5 26 / 20,
+  // 3*10^4 14 / 11; FP32 66.8 / 60.3, 48 / 45, 21 / 16, 12 / 10.)  A row of 10^4
+  // takes one CU 10 to 20 us, at 2.4 to 5 cycles a gather; sizes at which two
+  // of them share a CU, as 2.4*10^5 (FP64 38 us), take 5 to 10 us more than their neighbours.
   __shared__ A part[kBlockWaves];
   const int wv = wave_uniform(int(threadIdx.x >> 6));
-  const int lane = lane_id();
-  const int32_t i0 = bl.row_start[k] + b * kBlockWaves;
-  const int32_t n = min(kBlockWaves, bl.row_start[k + 1] - i0);
-  int32_t row[kBlockWaves], begin[kBlockWaves], end[kBlockWaves];
+  const int32_t row = rows[bl.row_start[k] + b];
+  A sum = strided_sum<DT, 8, true>(rp[row] + int32_t(threadIdx.x), rp[row + 1], kCsrBlock, col, val,
+                                   x);
 #pragma unroll
-  for (int q = 0; q < kBlockWaves; ++q) row[q] = q < n ? rows[i0 + q] : -1;
+  for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
+  if (lane_id() == 0) part[wv] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    A t = part[0];
 #pragma unroll
-  for (int q = 0; q < kBlockWaves; ++q) {
-    begin[q] = q < n ? rp[row[q]] : 0;
-    end[q] = q < n ? rp[row[q] + 1] : 0;
-  }
-#pragma unroll
-  for (int q = 0; q < kBlockWaves; ++q) {
-    if (q != wv || q >= n || end[q] - begin[q] > kWaveRow) continue;
-    A sum = strided_sum<DT, 8, true>(begin[q] + lane, end[q], 64, col, val, x);
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
-    if (lane == 0) y[row[q]] = sum;
-  }
-#pragma unroll
-  for (int q = 0; q < kBlockWaves; ++q) {
-    if (end[q] - begin[q] <= kWaveRow) continue;             // the same for all waves
-    A sum = strided_sum<DT, 8, true>(begin[q] + int32_t(threadIdx.x), end[q], kCsrBlock, col, val, x);
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
-    if (lane == 0) part[wv] = sum;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      A t = part[0];
-#pragma unroll
-      for (int w = 1; w < kBlockWaves; ++w) t += part[w];
-      y[row[q]] = t;
-    }
-    __syncthreads();
+    for (int w = 1; w < kBlockWaves; ++w) t += part[w];
+    y[row] = t;
   }
 }
 
@@ -438,7 +418,7 @@ extern "C" int argcsr_csr_spmv_binned(int32_t n_rows, int32_t n_cols, int64_t nn
   for (int k = 0; k < kBins; ++k) {
     bl.row_start[k] = bin_start[k];
     const int64_t cnt = bin_start[k + 1] - bin_start[k];
-    const int64_t per = k < kBins - 1 ? team * (kCsrBlock >> k) : kCsrBlock / 64;  // rows per workgroup
+    const int64_t per = k < kBins - 1 ? team * (kCsrBlock >> k) : 1;   // rows per workgroup
     bl.blocks[k] = int32_t((cnt + per - 1) / per);
     if (k < kBins - 1) blocks += bl.blocks[k];
   }

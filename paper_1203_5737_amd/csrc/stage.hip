@@ -147,20 +147,20 @@ __device__ __forceinline__ void window_starts(uint32_t b, int bit0, int prev, in
   }
 }
 
-// What bounds it: reading the columns (4 bytes a slot) and, with FILL,
-// writing the positions (2 bytes a slot); the rest is the group's chain of
-// load, marking, scans and lookup, hidden by the other groups of a CU.  A
+// What bounds it: VALU issue, 514 instructions a wave in the count pass
+// and 790 with FILL, for reading the columns (4 bytes a slot), marking, scans
+// and lookup, and writing the positions (2 bytes a slot); the group's chain is
+// hidden by the other groups of a CU.  A
 // thread holds up to kHeldSlots columns in registers, so a group that fits
 // its workgroup's registers is read once; a longer one is read again (from
 // L2) in each of the three phases.  The bitmap covers 2^15 columns at a time
 // (a span beyond that takes more rounds of marking), which keeps the LDS of a
 // workgroup near 5 KB and the CU full of waves.  Measured on MI355X on the
-// 100^3 27-point stencil (T = 128: 7813 groups of 3424 slots): 46 us the count
-// pass (2.3 TB/s) and 66 us the fill pass (2.4 TB/s), against 690 and 815 us
+// 100^3 27-point stencil (T = 128: 7813 groups of 3424 slots): 36 us the count
+// pass (3.0 TB/s) and 58 us the fill pass (2.8 TB/s), against 690 and 815 us
 // of a kernel with one wave per group, a 32-KB bitmap and slots read one at
 // a time in each phase.  One atomic for a thread's four columns instead of
-// one each, and the window search skipped inside a window, gave 53 -> 46 and
-// 75 -> 66 us.
+// one each, and the window search skipped inside a window, gave 13% each.
 template <bool FILL, int NT>
 __global__ __launch_bounds__(NT) void stage_kernel(
     const argcsr_group_info* __restrict__ groups, int32_t n_groups, int32_t T,
