@@ -22,13 +22,18 @@ namespace argcsr {
 namespace {
 
 constexpr int kCsrBlock = 256;
+// Elements of a row of bin 7 a lane loads at a time: 16 with up to kFewLongRows
+// of them, when the longest row's round trips are what the launch takes, else
+// 8, whose registers leave the CU more waves.  Power-law rows, us with 16 / 8:
+// FP32 2.4*10^5 rows (2300 of bin 7) 27.5 / 31.9, 4.5*10^5 (4200) 27 / 33, 10^6
+// (9400) 63.7 / 59.4; FP64 27.7 / 35.0, 37 / 39, 83.6 / 81.2.
+constexpr int32_t kFewLongRows = 4096;
 constexpr int kBins = ARGCSR_CSR_BINS;      // 8: widths 1, 2, 4, ..., 64, then a workgroup
 
 // sum plus fma(val, x[col], ...) over elements k, k + stride, ... below end, in that
 // order, U of them loaded at a time: a long row is not one chain of column,
-// x and sum after the other.  STREAM: the elements are read once and by this
-// wave alone (non-temporal loads: L2 stays for x).
-template <int DT, int U, bool STREAM>
+// x and sum after the other.
+template <int DT, int U>
 __device__ __forceinline__ typename Val<DT>::acc strided_sum(
     int32_t k, int32_t end, int32_t stride, const int32_t* __restrict__ col,
     const typename Val<DT>::storage* __restrict__ val,
@@ -41,18 +46,66 @@ __device__ __forceinline__ typename Val<DT>::acc strided_sum(
     A xv[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      c[u] = STREAM ? __builtin_nontemporal_load(col + k + u * stride) : col[k + u * stride];
-      v[u] = STREAM ? __builtin_nontemporal_load(val + k + u * stride) : val[k + u * stride];
+      c[u] = col[k + u * stride];
+      v[u] = val[k + u * stride];
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) xv[u] = x[c[u]];
 #pragma unroll
     for (int u = 0; u < U; ++u) sum = __builtin_fma(Vt::load(v[u]), xv[u], sum);
   }
-  for (; k < end; k += stride) {
-    const int32_t c = STREAM ? __builtin_nontemporal_load(col + k) : col[k];
-    const typename Vt::storage v = STREAM ? __builtin_nontemporal_load(val + k) : val[k];
-    sum = __builtin_fma(Vt::load(v), x[c], sum);
+  for (; k < end; k += stride) sum = __builtin_fma(Vt::load(val[k]), x[col[k]], sum);
+  return sum;
+}
+
+// As strided_sum over elements k0 + lane, + kCsrBlock, ... below end (k0 the same
+// for the wave), the elements left over from whole batches in one batch too:
+// one by one, their chains of column and x were most of a row of less than
+// U * kCsrBlock elements and half of one of 10^4.  Lanes past the end load the
+// row's last element and do not use it.  The elements are read once and by
+// this wave alone (non-temporal loads: L2 stays for x).
+template <int DT, int U>
+__device__ __forceinline__ typename Val<DT>::acc long_row_sum(
+    int32_t k0, int32_t end, const int32_t* __restrict__ col,
+    const typename Val<DT>::storage* __restrict__ val,
+    const typename Val<DT>::acc* __restrict__ x) {
+  using Vt = Val<DT>;
+  using A = typename Vt::acc;
+  const int lane = lane_id();
+  A sum = A(0);
+  int32_t c[U];
+  typename Vt::storage v[U];
+  A xv[U];
+  for (; end - k0 > (U - 1) * kCsrBlock + 63; k0 += U * kCsrBlock) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      c[u] = __builtin_nontemporal_load(col + k0 + lane + u * kCsrBlock);
+      v[u] = __builtin_nontemporal_load(val + k0 + lane + u * kCsrBlock);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) xv[u] = x[c[u]];
+#pragma unroll
+    for (int u = 0; u < U; ++u) sum = __builtin_fma(Vt::load(v[u]), xv[u], sum);
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    c[u] = 0;
+    v[u] = 0;
+    if (end - k0 > u * kCsrBlock) {
+      const int32_t k = min(k0 + lane + u * kCsrBlock, end - 1);
+      c[u] = __builtin_nontemporal_load(col + k);
+      v[u] = __builtin_nontemporal_load(val + k);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    xv[u] = A(0);
+    if (end - k0 > u * kCsrBlock) xv[u] = x[c[u]];
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const A t = __builtin_fma(Vt::load(v[u]), xv[u], sum);
+    sum = end - k0 > u * kCsrBlock + lane ? t : sum;
   }
   return sum;
 }
@@ -66,7 +119,7 @@ __device__ __forceinline__ typename Val<DT>::acc csr_row_sum(
     const typename Val<DT>::acc* __restrict__ x) {
   using A = typename Val<DT>::acc;
   A sum = A(0);
-  if (valid) sum = strided_sum<DT, 4, false>(rp[row] + sub, rp[row + 1], V, col, val, x);
+  if (valid) sum = strided_sum<DT, 4>(rp[row] + sub, rp[row + 1], V, col, val, x);
 #pragma unroll
   for (int d = V / 2; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
   return sum;
@@ -153,7 +206,7 @@ __device__ __forceinline__ void binned_rows(const BinLaunch& bl, int k, int32_t 
     if (c[r] >= 0) sum = __builtin_fma(Vt::load(v[r]), xv[r], sum);
     // rows of bin k have at most V nonzeros; bins made for another matrix
     // may hold longer ones
-    if (end[r] - at[r] > V) sum = strided_sum<DT, 1, false>(at[r] + V, end[r], V, col, val, x, sum);
+    if (end[r] - at[r] > V) sum = strided_sum<DT, 1>(at[r] + V, end[r], V, col, val, x, sum);
 #pragma unroll
     for (int d = V / 2; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
     if (row[r] >= 0 && sub == 0) y[row[r]] = sum;
@@ -161,10 +214,10 @@ __device__ __forceinline__ void binned_rows(const BinLaunch& bl, int k, int32_t 
 }
 
 // Bound by the x gathers on power-law rows and by the CSR stream on regular
-// ones.  MI355X: power-law rows of 10^6 FP64 125 us -> 82 (long rows first and
+// ones.  MI355X: power-law rows of 10^6 FP64 125 us -> 81 (long rows first and
 // loaded eight elements at a time a lane, regions, a workgroup per long row),
 // 27-point stencil 100^3 FP64 171 -> 105.
-template <int DT, int R>
+template <int DT, int R, int L>
 __global__ __launch_bounds__(kCsrBlock) void csr_binned_kernel(
     BinLaunch bl, const int32_t* __restrict__ rows, const int32_t* __restrict__ rp,
     const int32_t* __restrict__ col, const typename Val<DT>::storage* __restrict__ val,
@@ -198,16 +251,13 @@ __global__ __launch_bounds__(kCsrBlock) void csr_binned_kernel(
     default: break;
   }
   // bin 7: a row by the workgroup's 256 lanes, wave sums added in wave order.
-  // (Four rows a workgroup, a wave each up to 1024 nonzeros: power-law rows, us
-  // so / now, in FP64 10^6 rows 88.5 / 81.3, 7*10^5 60 / 56, 1.3*10^5 26 / 20,
-  // 3*10^4 14 / 11; FP32 66.8 / 60.3, 48 / 45, 21 / 16, 12 / 10.)  A row of 10^4
-  // takes one CU 10 to 20 us, at 2.4 to 5 cycles a gather; sizes at which two
-  // of them share a CU, as 2.4*10^5 (FP64 38 us), take 5 to 10 us more than their neighbours.
+  // (Four rows a workgroup, a wave each up to 1024 nonzeros, took a third longer
+  // on power-law rows of 4*10^4 to 4*10^5.)  A row of 10^4 takes one CU 10 to 20
+  // us, at 2.4 to 5 cycles a gather.
   __shared__ A part[kBlockWaves];
   const int wv = wave_uniform(int(threadIdx.x >> 6));
   const int32_t row = rows[bl.row_start[k] + b];
-  A sum = strided_sum<DT, 8, true>(rp[row] + int32_t(threadIdx.x), rp[row + 1], kCsrBlock, col, val,
-                                   x);
+  A sum = long_row_sum<DT, L>(rp[row] + wv * 64, rp[row + 1], col, val, x);
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
   if (lane_id() == 0) part[wv] = sum;
@@ -345,7 +395,9 @@ void launch_binned(const BinLaunch& bl, int team, int32_t blocks, const int32_t*
                    const int32_t* rp, const int32_t* col, const void* val, const void* x, void* y,
                    hipStream_t s) {
   using Vt = Val<DT>;
-  auto* kern = team == 4 ? &csr_binned_kernel<DT, 4> : &csr_binned_kernel<DT, 1>;
+  const bool few = bl.blocks[kBins - 1] <= kFewLongRows;
+  auto* kern = team == 4 ? few ? &csr_binned_kernel<DT, 4, 16> : &csr_binned_kernel<DT, 4, 8>
+                         : few ? &csr_binned_kernel<DT, 1, 16> : &csr_binned_kernel<DT, 1, 8>;
   kern<<<blocks, kCsrBlock, 0, s>>>(
       bl, rows, rp, col, static_cast<const typename Vt::storage*>(val),
       static_cast<const typename Vt::acc*>(x), static_cast<typename Vt::acc*>(y));

@@ -133,6 +133,34 @@ def test_binned_launch_shapes(ac, lengths, dtype):
         check_reduced(A, x, yn, dtype)
 
 
+# both batch sizes of bin 7 (16 elements a lane up to 4096 such rows, 8 beyond)
+# at the edges of a wave, a round of 256 lanes and a whole batch
+@pytest.mark.parametrize("rows", [60, 4096, 4097])
+@pytest.mark.parametrize("dtype", [0, 2])
+def test_binned_long_row_batches(ac, rows, dtype):
+    rng = np.random.default_rng(rows)
+    edges = [65, 127, 128, 129, 255, 256, 257, 511, 512, 513]
+    for batch in (8 * 256, 16 * 256):
+        edges += [batch - 193, batch - 192, batch - 1, batch, batch + 1, batch + 63, batch + 64,
+                  batch + 65, batch + 257]
+    edges += [2 * 8 * 256 + 8 * 256 - 1, 2 * 16 * 256 - 193, 2 * 16 * 256 + 300]
+    L = np.full(rows, 65, np.int64)
+    L[:len(edges)] = edges
+    rng.shuffle(L)
+    L = np.concatenate([L, [0, 1, 64, 3]])
+    A = synth.random_csr(L, 9000, rng, rng)
+    x = rng.uniform(-1.0, 1.0, A.n_cols).astype(np.float32).astype(np.float64)
+    dev = ac.to_device_csr(A.rp, A.col, A.val, A.n_cols, DEV)
+    xd = torch.from_numpy(x).to(DEV, ac.vector_dtype(dtype))
+    vals = dev.val if dtype == 0 else stored_values(ac, A, dtype)
+    y = ac.csr_spmv_binned(dev, xd, ac.csr_bins(dev), values=vals, dtype=dtype)
+    yn = y.cpu().numpy().astype(np.float64)
+    if dtype == 0:
+        check_f64(A, x, yn)
+    else:
+        check_reduced(A, x, yn, dtype)
+
+
 def test_bins_of_another_matrix_still_cover_the_rows(ac):
     """Bins are a partition of the rows: a matrix whose rows have other
     lengths than the ones they were made from gives the right result too."""
