@@ -1,5 +1,5 @@
-// Shared helpers of libargcsr: status/error reporting, HIP call checking,
-// and wave-level device primitives.
+// Shared helpers of libargcsr: status reporting (status.hpp) and wave-level
+// device primitives.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -8,21 +8,9 @@
 #include <cstdio>
 #include <string>
 
-#include "argcsr.h"
+#include "status.hpp"
 
 namespace argcsr {
-
-// Records a message for argcsr_last_error() and returns `code`.
-int fail(int code, const char* fmt, ...);
-void clear_error();
-
-#define ARGCSR_HIP(call)                                                       \
-  do {                                                                         \
-    hipError_t e_ = (call);                                                    \
-    if (e_ != hipSuccess)                                                      \
-      return ::argcsr::fail(ARGCSR_EHIP, "%s failed: %s (%s:%d)", #call,       \
-                            hipGetErrorString(e_), __FILE__, __LINE__);        \
-  } while (0)
 
 // XCD-aware block remap: hardware dispatches consecutive workgroups round-robin
 // over the 8 XCDs; give every XCD a contiguous range of logical blocks so that

@@ -665,29 +665,28 @@ struct ResultBox {
   int64_t* dev = nullptr;
   int64_t word[kBoxWords] = {};
   bool fixed = false;
-  int init(int64_t* fixed_words) {
+  int init(int64_t* fixed_words, hipStream_t s) {
     fixed = fixed_words != nullptr;
     if (fixed) {
       dev = fixed_words;
       return ARGCSR_OK;
     }
-    const int rc = mail.init();
+    const int rc = mail.init(s);
     dev = mail.device();
     return rc;
   }
-  // waits for the stream and reads the words
+  // waits for the stream and reads the words (kernels queued later may write
+  // them again; idle() after the last read)
   int read(hipStream_t s) {
     hipError_t e = hipSuccess;
     if (fixed) e = hipMemcpyAsync(word, dev, sizeof(word), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) {
-      mail.abandon();
-      return fail(ARGCSR_EHIP, "conversion: %s", hipGetErrorString(e));
-    }
+    if (e != hipSuccess) return fail(ARGCSR_EHIP, "conversion: %s", hipGetErrorString(e));
     if (!fixed)
       for (int i = 0; i < kBoxWords; ++i) word[i] = mail.word(i);
     return ARGCSR_OK;
   }
+  void idle() { mail.idle(); }
 };
 
 // Steps 1-3 of n_rows > 0 rows on the device, and the sizes of the result
@@ -697,7 +696,7 @@ int build_plan(int32_t n_rows, const int32_t* row_ptr, int32_t T, int32_t desire
   const size_t groups_b = sizeof(argcsr_group_info) * size_t(n_rows);
   const size_t tm_b = (sizeof(int32_t) * size_t(n_rows) + 15) / 16 * 16;
   ResultBox box;
-  int rc = box.init(nullptr);
+  int rc = box.init(nullptr, s);
   if (rc) return rc;
   DeviceScratch work;
   rc = p->block.alloc(groups_b + tm_b + kShareBytes + sizeof(Status), s);
@@ -723,6 +722,7 @@ int build_plan(int32_t n_rows, const int32_t* row_ptr, int32_t T, int32_t desire
   if (rc) return rc;
   p->block.idle();
   work.idle();
+  box.idle();
   if (box.word[kBoxBadRowPtr])
     return fail(ARGCSR_EINVAL, "row_ptr does not start at 0 or decreases");
   p->n_rows = n_rows;
@@ -894,7 +894,7 @@ int convert_impl(int32_t n_rows, int32_t n_cols, const int32_t* row_ptr_host,
   // (group, first step) per tile of the fill's long blocks
   int2* long_list = reinterpret_cast<int2*>(share_slots + kChunkBlocks + 2 * kScanBlocks);
   ResultBox box;
-  rc = box.init(fixed ? reinterpret_cast<int64_t*>(st + 1) : nullptr);
+  rc = box.init(fixed ? reinterpret_cast<int64_t*>(st + 1) : nullptr, s);
   if (rc) return rc;
   // uses the caller's slot count; it is checked against the device total
   // before anything is written to the caller's heavy_groups buffer
@@ -964,6 +964,7 @@ int convert_impl(int32_t n_rows, int32_t n_cols, const int32_t* row_ptr_host,
   rc = box.read(s);
   if (rc) return rc;
   ws.idle();
+  box.idle();
   if (box.word[kBoxBadColumn])
     return fail(ARGCSR_EINVAL, "a column index lies outside [0, %d)", n_cols);
   return ARGCSR_OK;

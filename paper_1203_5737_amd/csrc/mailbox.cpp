@@ -5,7 +5,7 @@
 #include <mutex>
 #include <vector>
 
-#include "common.hpp"
+#include "status.hpp"
 
 namespace argcsr {
 namespace {
@@ -21,7 +21,7 @@ std::vector<int64_t*> g_free;         // guarded by g_mu
 
 }  // namespace
 
-int Mailbox::init() {
+int Mailbox::init(hipStream_t s) {
   {
     std::lock_guard<std::mutex> lock(g_mu);
     if (!g_block) {
@@ -48,12 +48,16 @@ int Mailbox::init() {
   if (hipHostGetDevicePointer(&d, host_, 0) != hipSuccess)
     return fail(ARGCSR_EHIP, "pinned result slot is not mapped on this device");
   dev_ = static_cast<int64_t*>(d);
+  stream_ = s;
+  idle_ = false;
   for (int i = 0; i < kWords; ++i) static_cast<volatile int64_t*>(host_)[i] = 0;
   return ARGCSR_OK;
 }
 
 Mailbox::~Mailbox() {
-  if (!host_ || lost_) return;
+  if (!host_) return;
+  // an owner that left early may have kernels queued that write the slot
+  if (!idle_ && hipStreamSynchronize(stream_) != hipSuccess) return;
   if (own_) {
     (void)hipHostFree(host_);
     return;

@@ -4,7 +4,7 @@
 #include <mutex>
 #include <vector>
 
-#include "common.hpp"
+#include "status.hpp"
 
 namespace argcsr {
 namespace {

@@ -446,8 +446,10 @@ void launch_stage(const argcsr_matrix* A, int32_t gap, int32_t* tile_ptr, int64_
 int wait_for(Mailbox& box, hipStream_t s) {
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e == hipSuccess) return ARGCSR_OK;
-  box.abandon();
+  if (e == hipSuccess) {
+    box.idle();
+    return ARGCSR_OK;
+  }
   return fail(ARGCSR_EHIP, "staging: %s", hipGetErrorString(e));
 }
 
@@ -482,7 +484,7 @@ extern "C" int argcsr_stage_plan(const argcsr_matrix* A, int32_t gap, int32_t* t
     return ARGCSR_OK;
   }
   Mailbox box;
-  rc = box.init();
+  rc = box.init(s);
   if (rc) return rc;
   launch_stage<false>(A, gap, tile_ptr, box.device(), s);
   stage_scan_kernel<<<1, 1024, 0, s>>>(tile_ptr, A->n_groups, box.device());
@@ -510,7 +512,7 @@ extern "C" int argcsr_stage(argcsr_matrix* A, void* stream) {
     return fail(ARGCSR_EINVAL, "NULL staging buffer");
   hipStream_t s = static_cast<hipStream_t>(stream);
   Mailbox box;
-  rc = box.init();
+  rc = box.init(s);
   if (rc) return rc;
   launch_stage<true>(A, A->stage_gap, A->tile_ptr, box.device(), s);
   rc = wait_for(box, s);
