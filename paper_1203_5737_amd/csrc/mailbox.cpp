@@ -5,7 +5,7 @@
 #include <mutex>
 #include <vector>
 
-#include "status.hpp"
+#include "capture.hpp"
 
 namespace argcsr {
 namespace {
@@ -22,12 +22,17 @@ std::vector<int64_t*> g_free;         // guarded by g_mu
 }  // namespace
 
 int Mailbox::init(hipStream_t s) {
+  const int rc = refuse_capture(s);
+  if (rc) return rc;
   {
     std::lock_guard<std::mutex> lock(g_mu);
     if (!g_block) {
+      const RelaxedCapture relaxed;
       void* p = nullptr;
-      if (hipHostMalloc(&p, kSlots * kSlotBytes, kFlags) != hipSuccess)
+      if (hipHostMalloc(&p, kSlots * kSlotBytes, kFlags) != hipSuccess) {
+        (void)hipGetLastError();
         return fail(ARGCSR_ENOMEM, "pinned result slots could not be allocated");
+      }
       g_block = static_cast<int64_t*>(p);
       g_free.reserve(kSlots);
       for (int i = kSlots - 1; i >= 0; --i) g_free.push_back(g_block + i * kWords);
@@ -38,9 +43,12 @@ int Mailbox::init(hipStream_t s) {
     }
   }
   if (!host_) {
+    const RelaxedCapture relaxed;
     void* p = nullptr;
-    if (hipHostMalloc(&p, kSlotBytes, kFlags) != hipSuccess)
+    if (hipHostMalloc(&p, kSlotBytes, kFlags) != hipSuccess) {
+      (void)hipGetLastError();
       return fail(ARGCSR_ENOMEM, "pinned result slot could not be allocated");
+    }
     host_ = static_cast<int64_t*>(p);
     own_ = true;
   }
@@ -57,8 +65,15 @@ int Mailbox::init(hipStream_t s) {
 Mailbox::~Mailbox() {
   if (!host_) return;
   // an owner that left early may have kernels queued that write the slot
-  if (!idle_ && hipStreamSynchronize(stream_) != hipSuccess) return;
+  if (!idle_) {
+    const RelaxedCapture relaxed;
+    if (hipStreamSynchronize(stream_) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+  }
   if (own_) {
+    const RelaxedCapture relaxed;
     (void)hipHostFree(host_);
     return;
   }

@@ -4,7 +4,7 @@
 #include <mutex>
 #include <vector>
 
-#include "status.hpp"
+#include "capture.hpp"
 
 namespace argcsr {
 namespace {
@@ -38,6 +38,8 @@ size_t rounded(size_t bytes) {
 
 int DeviceScratch::alloc(size_t bytes, hipStream_t s) {
   release();
+  int rc = refuse_capture(s);
+  if (rc) return rc;
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices)
     return fail(ARGCSR_EHIP, "no current device");
@@ -60,19 +62,23 @@ int DeviceScratch::alloc(size_t bytes, hipStream_t s) {
     }
   }
   if (!ptr_) {
-    if (hipMalloc(&ptr_, want) != hipSuccess) {
+    const RelaxedCapture relaxed;
+    hipError_t e = hipMalloc(&ptr_, want);
+    if (e == hipErrorOutOfMemory) {
       {
         std::lock_guard<std::mutex> lock(c.mu);
         drop.swap(c.blocks);
         c.bytes = 0;
       }
       for (const Block& b : drop) (void)hipFree(b.p);
+      e = hipMalloc(&ptr_, want);
+    }
+    if (e != hipSuccess) {
       (void)hipGetLastError();
-      if (hipMalloc(&ptr_, want) != hipSuccess) {
-        (void)hipGetLastError();
-        ptr_ = nullptr;
-        return fail(ARGCSR_ENOMEM, "device scratch of %zu bytes could not be allocated", bytes);
-      }
+      ptr_ = nullptr;
+      return fail(e == hipErrorOutOfMemory ? ARGCSR_ENOMEM : ARGCSR_EHIP,
+                  "device scratch of %zu bytes could not be allocated: %s", bytes,
+                  hipGetErrorString(e));
     }
     bytes_ = want;
   }
@@ -88,7 +94,13 @@ void DeviceScratch::release() {
   ptr_ = nullptr;
   // an owner that left early may have work queued that uses the block; if
   // waiting fails, the block is not handed out again
-  if (!idle_ && hipStreamSynchronize(stream_) != hipSuccess) return;
+  if (!idle_) {
+    const RelaxedCapture relaxed;
+    if (hipStreamSynchronize(stream_) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+  }
   Cache& c = cache_of(device_);
   std::vector<Block> drop;
   {
@@ -101,7 +113,10 @@ void DeviceScratch::release() {
       c.blocks.erase(c.blocks.begin());
     }
   }
-  for (const Block& b : drop) (void)hipFree(b.p);
+  if (!drop.empty()) {
+    const RelaxedCapture relaxed;
+    for (const Block& b : drop) (void)hipFree(b.p);
+  }
 }
 
 }  // namespace argcsr

@@ -15,7 +15,11 @@ CSRC = os.path.join(ROOT, "paper_1203_5737_amd", "csrc")
 HIP = r"""
 #pragma once
 #include <cstddef>
-enum hipError_t { hipSuccess = 0, hipErrorOutOfMemory = 2, hipErrorUnknown = 999 };
+enum hipError_t { hipSuccess = 0, hipErrorOutOfMemory = 2, hipErrorCapture = 900,
+                  hipErrorUnknown = 999 };
+enum hipStreamCaptureMode { hipStreamCaptureModeGlobal, hipStreamCaptureModeThreadLocal,
+                            hipStreamCaptureModeRelaxed };
+enum hipStreamCaptureStatus { hipStreamCaptureStatusNone, hipStreamCaptureStatusActive };
 typedef struct ihipStream_t* hipStream_t;
 constexpr unsigned hipHostMallocMapped = 2, hipHostMallocPortable = 1,
                    hipHostMallocCoherent = 0x40000000;
@@ -26,6 +30,8 @@ hipError_t hipHostMalloc(void**, size_t, unsigned);
 hipError_t hipHostFree(void*);
 hipError_t hipHostGetDevicePointer(void**, void*, unsigned);
 hipError_t hipStreamSynchronize(hipStream_t);
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus*);
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode*);
 hipError_t hipGetLastError();
 inline const char* hipGetErrorString(hipError_t) { return ""; }
 """
@@ -46,8 +52,27 @@ static int g_syncs, g_mallocs, g_frees;
 static hipError_t g_sync_result = hipSuccess, g_malloc_result = hipSuccess;
 static size_t g_room = size_t(1) << 40;              // device memory there is
 
+static hipStream_t g_capturing = nullptr;            // a stream that is capturing a graph
+static bool g_global = false;                        // another thread is, in the global mode
+static hipStreamCaptureMode g_mode = hipStreamCaptureModeGlobal;
+static int g_refused;                                // calls that mode forbade
+static bool forbidden() {
+  const bool no = g_global && g_mode == hipStreamCaptureModeGlobal;
+  g_refused += no;
+  return no;
+}
+
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
+  *st = s && s == g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* m) {
+  std::swap(*m, g_mode);
+  return hipSuccess;
+}
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipMalloc(void** p, size_t n) {
+  if (forbidden()) return hipErrorCapture;
   ++g_mallocs;
   if (g_malloc_result != hipSuccess) return g_malloc_result;
   size_t used = 0;
@@ -58,23 +83,30 @@ hipError_t hipMalloc(void** p, size_t n) {
   return hipSuccess;
 }
 hipError_t hipFree(void* p) {
+  if (forbidden()) return hipErrorCapture;
   if (!g_dev.erase(p)) std::abort();
   ++g_frees;
   std::free(p);
   return hipSuccess;
 }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+  if (forbidden()) return hipErrorCapture;
   *p = std::malloc(n);
   g_pinned[*p] = n;
   return hipSuccess;
 }
 hipError_t hipHostFree(void* p) {
+  if (forbidden()) return hipErrorCapture;
   if (!g_pinned.erase(p)) std::abort();
   std::free(p);
   return hipSuccess;
 }
 hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned) { *d = h; return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { ++g_syncs; return g_sync_result; }
+hipError_t hipStreamSynchronize(hipStream_t) {
+  if (forbidden()) return hipErrorCapture;
+  ++g_syncs;
+  return g_sync_result;
+}
 hipError_t hipGetLastError() { return hipSuccess; }
 namespace argcsr {
 int fail(int code, const char*, ...) { return code; }
@@ -129,6 +161,108 @@ int main() {
 """
 
 
+BLOCKS = r"""
+constexpr size_t kMB = size_t(1) << 20;
+static size_t live() {
+  size_t n = 0;
+  for (auto& b : g_dev) n += b.second;
+  return n;
+}
+int main() {
+  hipStream_t s = reinterpret_cast<hipStream_t>(0x10);
+  void* first;
+  {                                     // a block comes back for a call of its size
+    DeviceScratch a, b;
+    CHECK(a.alloc(100 * kMB, s) == ARGCSR_OK && b.alloc(100 * kMB, s) == ARGCSR_OK);
+    first = a.ptr();
+    CHECK(first != b.ptr());
+    a.idle();
+    a.release();
+    CHECK(g_syncs == 0);
+    DeviceScratch c;
+    CHECK(c.alloc(100 * kMB - 5, s) == ARGCSR_OK && c.ptr() == first && g_mallocs == 2);
+    c.release();                        // its owner has not said idle
+    CHECK(g_syncs == 1);
+    DeviceScratch d;
+    CHECK(d.alloc(24 * kMB, s) == ARGCSR_OK && d.ptr() != first);   // four times too large
+    d.idle();
+    b.idle();
+  }
+  CHECK(g_dev.size() == 3 && g_frees == 0);
+  {                                     // more blocks than are kept: the oldest go
+    std::vector<std::unique_ptr<DeviceScratch>> many;
+    for (int i = 0; i < DeviceScratch::kKeepBlocks; ++i) {
+      many.emplace_back(new DeviceScratch);
+      CHECK(many.back()->alloc((5 + size_t(i) / 8) * kMB, s) == ARGCSR_OK);
+      many.back()->idle();
+    }
+  }
+  CHECK(int(g_dev.size()) == DeviceScratch::kKeepBlocks && g_dev.count(first) == 0);
+  {                                     // more bytes than are kept
+    DeviceScratch a;
+    CHECK(a.alloc(DeviceScratch::kKeepBytes - 8 * kMB, s) == ARGCSR_OK);
+    a.idle();
+  }
+  CHECK(live() <= DeviceScratch::kKeepBytes && g_dev.size() == 2);
+  {                                     // out of memory: what is cached goes, then again
+    g_room = live() + kMB;
+    DeviceScratch a;
+    CHECK(a.alloc(64 * kMB, s) == ARGCSR_OK && g_dev.size() == 1);
+    DeviceScratch b;
+    CHECK(b.alloc(DeviceScratch::kKeepBytes, s) == ARGCSR_ENOMEM && !b.ptr());
+    g_room = size_t(1) << 40;
+    a.idle();
+  }
+  CHECK(g_dev.size() == 1);
+  {                                     // any other failure is no lack of memory: the cache stays
+    g_malloc_result = hipErrorUnknown;
+    DeviceScratch a;
+    CHECK(a.alloc(256 * kMB, s) == ARGCSR_EHIP && !a.ptr());
+    g_malloc_result = hipSuccess;
+    CHECK(g_dev.size() == 1);
+  }
+  {                                     // another thread captures in the global mode: blocks are
+    g_global = true;                    // taken, waited for, kept and freed as before
+    const int frees = g_frees;
+    DeviceScratch a, b, c;
+    CHECK(a.alloc(64 * kMB, s) == ARGCSR_OK && b.alloc(DeviceScratch::kKeepBytes, s) == ARGCSR_OK);
+    a.release();
+    CHECK(c.alloc(64 * kMB, s) == ARGCSR_OK);
+    c.release();
+    b.release();
+    CHECK(g_dev.size() == 1 && g_frees == frees + 1);
+    Mailbox m;
+    CHECK(m.init(s) == ARGCSR_OK);
+    CHECK(g_refused == 0 && g_mode == hipStreamCaptureModeGlobal);
+    g_global = false;
+  }
+  {                                     // the stream itself is capturing: refused, nothing taken
+    g_capturing = s;
+    const size_t blocks = g_dev.size();
+    const int syncs = g_syncs;
+    DeviceScratch a;
+    Mailbox m;
+    CHECK(a.alloc(64 * kMB, s) == ARGCSR_EHIP && m.init(s) == ARGCSR_EHIP);
+    CHECK(!a.ptr() && g_dev.size() == blocks && g_syncs == syncs);
+    g_capturing = nullptr;
+  }
+  {                                     // a stream that cannot be waited for: the block is lost
+    DeviceScratch a, b;
+    CHECK(a.alloc(kMB, s) == ARGCSR_OK);
+    void* p = a.ptr();
+    g_sync_result = hipErrorUnknown;
+    a.release();
+    g_sync_result = hipSuccess;
+    CHECK(b.alloc(kMB, s) == ARGCSR_OK && b.ptr() != p);
+    b.idle();
+  }
+  std::puts("ok");
+  std::fflush(stdout);
+  std::_Exit(0);
+}
+"""
+
+
 def run(tmp_path, main):
     (tmp_path / "hip").mkdir()
     (tmp_path / "hip" / "hip_runtime.h").write_text(HIP)
@@ -149,3 +283,10 @@ def run(tmp_path, main):
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 def test_result_slots_wait_for_their_stream(tmp_path):
     run(tmp_path, SLOTS)
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_device_scratch_cache(tmp_path):
+    """Reuse, eviction by number and by size, lack of memory, other failures,
+    and graph capture by this and by another thread."""
+    run(tmp_path, BLOCKS)
