@@ -3,7 +3,6 @@
 #include <hip/hip_runtime.h>
 
 #include <mutex>
-#include <vector>
 
 #include "capture.hpp"
 
@@ -17,7 +16,8 @@ constexpr unsigned kFlags = hipHostMallocMapped | hipHostMallocPortable | hipHos
 
 std::mutex g_mu;
 int64_t* g_block = nullptr;           // kSlots slots, guarded by g_mu
-std::vector<int64_t*> g_free;         // guarded by g_mu
+int64_t* g_free[kSlots];              // free ones, the first g_n_free; guarded by g_mu
+int g_n_free = 0;
 
 }  // namespace
 
@@ -34,13 +34,9 @@ int Mailbox::init(hipStream_t s) {
         return fail(ARGCSR_ENOMEM, "pinned result slots could not be allocated");
       }
       g_block = static_cast<int64_t*>(p);
-      g_free.reserve(kSlots);
-      for (int i = kSlots - 1; i >= 0; --i) g_free.push_back(g_block + i * kWords);
+      for (int i = kSlots - 1; i >= 0; --i) g_free[g_n_free++] = g_block + i * kWords;
     }
-    if (!g_free.empty()) {
-      host_ = g_free.back();
-      g_free.pop_back();
-    }
+    if (g_n_free > 0) host_ = g_free[--g_n_free];
   }
   if (!host_) {
     const RelaxedCapture relaxed;
@@ -78,7 +74,7 @@ Mailbox::~Mailbox() {
     return;
   }
   std::lock_guard<std::mutex> lock(g_mu);
-  g_free.push_back(host_);              // reserved above: never allocates
+  g_free[g_n_free++] = host_;
 }
 
 }  // namespace argcsr

@@ -2,7 +2,6 @@
 
 #include <algorithm>
 #include <mutex>
-#include <vector>
 
 #include "capture.hpp"
 
@@ -16,17 +15,24 @@ struct Block {
   size_t bytes;
 };
 
+// Blocks are kept in fixed arrays: nothing here allocates host memory, so
+// neither a destructor nor a C entry can throw.
 struct Cache {
   std::mutex mu;
-  std::vector<Block> blocks;      // oldest first; guarded by mu
+  Block blocks[DeviceScratch::kKeepBlocks + 1];   // oldest first; guarded by mu
+  int n = 0;
   size_t bytes = 0;               // of blocks
-};
 
-// Never destroyed: the runtime may be gone when static objects are.
-Cache& cache_of(int device) {
-  static Cache* const caches = new Cache[kMaxDevices];
-  return caches[device];
-}
+  Block take(int i) {
+    const Block b = blocks[i];
+    std::copy(blocks + i + 1, blocks + n, blocks + i);
+    --n;
+    bytes -= b.bytes;
+    return b;
+  }
+};
+// (a mutex and plain words: constant to construct, nothing to destroy)
+Cache g_caches[kMaxDevices];
 
 // Sizes are rounded so that calls of about the same size share blocks.
 size_t rounded(size_t bytes) {
@@ -44,33 +50,32 @@ int DeviceScratch::alloc(size_t bytes, hipStream_t s) {
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices)
     return fail(ARGCSR_EHIP, "no current device");
   const size_t want = rounded(bytes);
-  Cache& c = cache_of(dev);
-  std::vector<Block> drop;
+  Cache& c = g_caches[dev];
   {
     std::lock_guard<std::mutex> lock(c.mu);
     // the smallest block that fits, but none four times too large
     int best = -1;
-    for (int i = 0; i < int(c.blocks.size()); ++i) {
-      const size_t b = c.blocks[size_t(i)].bytes;
-      if (b >= want && b / 4 <= want && (best < 0 || b < c.blocks[size_t(best)].bytes)) best = i;
+    for (int i = 0; i < c.n; ++i) {
+      const size_t b = c.blocks[i].bytes;
+      if (b >= want && b / 4 <= want && (best < 0 || b < c.blocks[best].bytes)) best = i;
     }
     if (best >= 0) {
-      ptr_ = c.blocks[size_t(best)].p;
-      bytes_ = c.blocks[size_t(best)].bytes;
-      c.bytes -= bytes_;
-      c.blocks.erase(c.blocks.begin() + best);
+      const Block b = c.take(best);
+      ptr_ = b.p;
+      bytes_ = b.bytes;
     }
   }
   if (!ptr_) {
     const RelaxedCapture relaxed;
     hipError_t e = hipMalloc(&ptr_, want);
     if (e == hipErrorOutOfMemory) {
+      Block drop[DeviceScratch::kKeepBlocks + 1];
+      int n_drop = 0;
       {
         std::lock_guard<std::mutex> lock(c.mu);
-        drop.swap(c.blocks);
-        c.bytes = 0;
+        while (c.n > 0) drop[n_drop++] = c.take(c.n - 1);
       }
-      for (const Block& b : drop) (void)hipFree(b.p);
+      for (int i = 0; i < n_drop; ++i) (void)hipFree(drop[i].p);
       e = hipMalloc(&ptr_, want);
     }
     if (e != hipSuccess) {
@@ -101,21 +106,18 @@ void DeviceScratch::release() {
       return;
     }
   }
-  Cache& c = cache_of(device_);
-  std::vector<Block> drop;
+  Cache& c = g_caches[device_];
+  Block drop[DeviceScratch::kKeepBlocks + 1];
+  int n_drop = 0;
   {
     std::lock_guard<std::mutex> lock(c.mu);
-    c.blocks.push_back(Block{p, bytes_});
+    c.blocks[c.n++] = Block{p, bytes_};
     c.bytes += bytes_;
-    while (c.bytes > kKeepBytes || int(c.blocks.size()) > kKeepBlocks) {
-      drop.push_back(c.blocks.front());
-      c.bytes -= c.blocks.front().bytes;
-      c.blocks.erase(c.blocks.begin());
-    }
+    while (c.bytes > kKeepBytes || c.n > kKeepBlocks) drop[n_drop++] = c.take(0);
   }
-  if (!drop.empty()) {
+  if (n_drop > 0) {
     const RelaxedCapture relaxed;
-    for (const Block& b : drop) (void)hipFree(b.p);
+    for (int i = 0; i < n_drop; ++i) (void)hipFree(drop[i].p);
   }
 }
 

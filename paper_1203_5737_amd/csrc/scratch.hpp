@@ -16,9 +16,11 @@ namespace argcsr {
 // stream-ordered allocation needs no wait, but its hipFreeAsync takes 8 to
 // 16 us on the host, three times per conversion: without it the conversion of
 // the power-law matrix of 10^6 rows went from 210 to 184 us.)  The cache keeps
-// at most kKeepBytes and kKeepBlocks per device -- the scratch of a matrix of
-// 10^8 rows -- and frees the oldest blocks beyond that; when the device is out
-// of memory everything cached is freed and the allocation tried again.
+// at most kKeepBytes and kKeepBlocks per device -- the scratch of planning and
+// converting a matrix of about 9*10^7 rows, at 22 bytes a row and what the
+// fill's list of long tiles takes -- and frees the oldest blocks beyond that
+// (a larger matrix allocates again on each call); when the device is out of
+// memory everything cached is freed and the allocation tried again.
 class DeviceScratch {
  public:
   static constexpr size_t kKeepBytes = size_t(2) << 30;

@@ -71,7 +71,7 @@ hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* m) {
   return hipSuccess;
 }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
-hipError_t hipMalloc(void** p, size_t n) {
+static hipError_t hip_malloc(void** p, size_t n) {
   if (forbidden()) return hipErrorCapture;
   ++g_mallocs;
   if (g_malloc_result != hipSuccess) return g_malloc_result;
@@ -89,7 +89,7 @@ hipError_t hipFree(void* p) {
   std::free(p);
   return hipSuccess;
 }
-hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+static hipError_t hip_host_malloc(void** p, size_t n, unsigned) {
   if (forbidden()) return hipErrorCapture;
   *p = std::malloc(n);
   g_pinned[*p] = n;
@@ -117,7 +117,12 @@ using argcsr::Mailbox;
 #define CHECK(c) do { if (!(c)) { std::printf("line %d: %s\n", __LINE__, #c); std::exit(1); } } while (0)
 """
 
-SLOTS = r"""
+PLAIN = r"""
+hipError_t hipMalloc(void** p, size_t n) { return hip_malloc(p, n); }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned f) { return hip_host_malloc(p, n, f); }
+"""
+
+SLOTS = PLAIN + r"""
 int main() {
   hipStream_t s = reinterpret_cast<hipStream_t>(0x10);
   int64_t* slot;
@@ -161,7 +166,7 @@ int main() {
 """
 
 
-BLOCKS = r"""
+BLOCKS = PLAIN + r"""
 constexpr size_t kMB = size_t(1) << 20;
 static size_t live() {
   size_t n = 0;
@@ -262,6 +267,55 @@ int main() {
 }
 """
 
+# every allocation of host memory by the two files fails: nothing throws, in a
+# destructor or out of a call
+NO_HOST_MEMORY = r"""
+#include <new>
+static bool g_no_memory = false;
+void* operator new(size_t n) {
+  if (g_no_memory) throw std::bad_alloc();
+  return std::malloc(n);
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
+
+// the stand-in's own lists may allocate
+struct Allow {
+  bool was = g_no_memory;
+  Allow() { g_no_memory = false; }
+  ~Allow() { g_no_memory = was; }
+};
+hipError_t hipMalloc(void** p, size_t n) { Allow a; return hip_malloc(p, n); }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned f) { Allow a; return hip_host_malloc(p, n, f); }
+
+int main() {
+  hipStream_t s = reinterpret_cast<hipStream_t>(0x10);
+  g_no_memory = true;
+  bool ok = true;
+  for (int round = 0; round < 2; ++round) {
+    DeviceScratch b[DeviceScratch::kKeepBlocks + 4];
+    for (auto& x : b) {
+      ok = ok && x.alloc(5 << 20, s) == ARGCSR_OK;
+      x.idle();
+    }
+    Mailbox m[300];
+    for (auto& x : m) {
+      ok = ok && x.init(s) == ARGCSR_OK;
+      x.idle();
+    }
+    for (auto& x : b) x.release();
+    g_room = 0;                          // empties the cache
+    ok = ok && b[0].alloc(1 << 30, s) == ARGCSR_ENOMEM;
+    g_room = size_t(1) << 40;
+  }
+  g_no_memory = false;
+  CHECK(ok && g_dev.empty());
+  std::puts("ok");
+  std::fflush(stdout);
+  std::_Exit(0);
+}
+"""
+
 
 def run(tmp_path, main):
     (tmp_path / "hip").mkdir()
@@ -290,3 +344,8 @@ def test_device_scratch_cache(tmp_path):
     """Reuse, eviction by number and by size, lack of memory, other failures,
     and graph capture by this and by another thread."""
     run(tmp_path, BLOCKS)
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_no_host_allocation_throws(tmp_path):
+    run(tmp_path, NO_HOST_MEMORY)
