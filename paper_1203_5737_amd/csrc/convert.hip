@@ -23,6 +23,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstddef>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -51,8 +52,8 @@ constexpr size_t kMaxFillLds = size_t(64) << 10;
 constexpr int kLongSteps = 16;        // steps per LDS tile in fill_long_kernel
 constexpr int kLongGrid = 4096;       // one-wave workgroups of fill_long_kernel
 
-// Device-side state of one conversion, all zero at its start (but for
-// `groups`, which step 1 on the device fills in).
+// Device-side state of one conversion, all zero at its start but for
+// `groups`, which step 1 on the device writes.
 struct Status {
   GroupCount groups;                  // step 1's, when it runs on the device
   int32_t scans_done;                 // workgroups of offsets_kernel that have finished
@@ -60,6 +61,8 @@ struct Status {
   unsigned long long heavy;           // heavy groups of those
   unsigned long long long_tiles;      // and tiles of long groups (see fill_kernel)
 };
+static_assert(offsetof(Status, scans_done) == sizeof(GroupCount),
+              "step 1 clears what follows `groups`, and nothing of it");
 
 // Words the kernels hand to the host (a pinned slot, or device memory).
 constexpr int kBoxGroups = 0, kBoxSlots = 1, kBoxHeavy = 2, kBoxBadRowPtr = 3, kBoxBadColumn = 4,
@@ -710,8 +713,9 @@ int build_plan(int32_t n_rows, const int32_t* row_ptr, int32_t T, int32_t desire
   p->heavy_parts = share_slots + kChunkBlocks;
   auto* st = reinterpret_cast<Status*>(p->heavy_parts + 2 * kScanBlocks);
   rc = group_on_device(n_rows, row_ptr, T, desired, format, region_rows, regions, p->groups,
-                       &st->groups, reinterpret_cast<int32_t*>(st),
-                       int64_t(sizeof(Status) / sizeof(int32_t)), work.ptr(), s);
+                       &st->groups, &st->scans_done,
+                       int64_t((sizeof(Status) - offsetof(Status, scans_done)) / sizeof(int32_t)),
+                       work.ptr(), s);
   if (rc) return rc;
   launch_chunks(row_ptr, p->groups, 0, &st->groups, T, format, p->tm, share_slots, s);
   offsets_kernel<<<kScanBlocks, kScanBlock, 0, s>>>(p->groups, 0, &st->groups, T, share_slots,

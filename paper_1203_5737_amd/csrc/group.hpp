@@ -22,7 +22,8 @@ struct GroupCount {
 // first_row and size of every group (offset and chunk size 0), *count the
 // number of groups and whether row_ptr is malformed (the groups then still
 // cover the rows, each at most block_dim of them), and the `clear_words`
-// 32-bit words at `clear` are set to 0.  block_dim in [1, 1024].
+// 32-bit words at `clear`, which *count is none of, are set to 0.  block_dim
+// in [1, 1024].
 // format ARGCSR_FORMAT_RG: groups of block_dim rows (no nonzero budget);
 // region_desired (host, checked by the caller): a desiredChunkSize per region
 // of region_rows rows, taken from the region of a group's first row.
