@@ -230,11 +230,25 @@ int argcsr_plan_device_keep(int32_t n_rows, const int32_t* row_ptr, int32_t bloc
                             void* stream);
 
 /*
+ * argcsr_plan_keep -- argcsr_plan_device_keep for a caller who holds the row
+ * offsets on the host too: while the device works, the host copy is checked
+ * as argcsr_plan checks it (EINVAL when it does not start at 0 or decreases),
+ * and its last entry is compared with the device's (EINVAL).
+ *   row_ptr_host  host int32[n_rows+1], same content as row_ptr
+ *   other arguments as for argcsr_plan_device_keep
+ * Synchronous.  Errors: as argcsr_plan_device.
+ */
+int argcsr_plan_keep(int32_t n_rows, const int32_t* row_ptr_host, const int32_t* row_ptr,
+                     int32_t block_dim, int32_t desired_chunk_size, int32_t format,
+                     int32_t* n_groups, int64_t* n_slots, int32_t* n_heavy,
+                     argcsr_device_plan** plan, void* stream);
+
+/*
  * argcsr_convert_planned -- argcsr_convert of the planned matrix: copies the
  * plan's groups and threads mapping into out's buffers and runs step 4
  * (offsets, launch schedule, fill) only.  The result equals argcsr_convert's
  * byte for byte.
- *   plan     from argcsr_plan_device_keep on the same row_ptr
+ *   plan     from argcsr_plan_device_keep or argcsr_plan_keep on the same row_ptr
  *   out      as for argcsr_convert; n_rows, block_dim, desired_chunk_size,
  *            format, n_groups and n_slots must be the plan's (EINVAL
  *            otherwise); no region table

@@ -205,9 +205,11 @@ _DEVICE_GROUPING_ROWS = 8192
 
 
 def _groups_on_device(A: DeviceCsr) -> bool:
-    rp = A.row_ptr
+    rp, host = A.row_ptr, A.row_ptr_host
     return (A.n_rows >= _DEVICE_GROUPING_ROWS and rp.is_cuda and rp.dtype == torch.int32
-            and rp.is_contiguous() and rp.numel() == A.n_rows + 1)
+            and rp.is_contiguous() and rp.numel() == A.n_rows + 1
+            and isinstance(host, np.ndarray) and host.dtype == np.int32
+            and host.flags.c_contiguous and host.shape == (A.n_rows + 1,))
 
 
 def _check_device_row_ptr(rp: torch.Tensor) -> None:
@@ -215,15 +217,18 @@ def _check_device_row_ptr(rp: torch.Tensor) -> None:
         raise ValueError("row_ptr must be a contiguous int32 device tensor")
 
 
-def _plan_keep(A: DeviceCsr, block_dim, desired_chunk_size, fmt, stream):
-    """(plan handle, n_groups, n_slots, n_heavy) of argcsr_plan_device_keep."""
+def _plan_keep(A: DeviceCsr, block_dim, desired_chunk_size, fmt, stream, host_copy: bool):
+    """(plan handle, n_groups, n_slots, n_heavy) of argcsr_plan_device_keep,
+    or, with `host_copy`, of argcsr_plan_keep, which checks row_ptr_host too."""
     g, s, h = ctypes.c_int32(0), ctypes.c_int64(0), ctypes.c_int32(0)
     plan_h = ctypes.c_void_p(0)
-    check(lib().argcsr_plan_device_keep(A.n_rows, _ptr(A.row_ptr), int(block_dim),
-                                        int(desired_chunk_size), int(fmt), ctypes.byref(g),
-                                        ctypes.byref(s), ctypes.byref(h),
-                                        ctypes.byref(plan_h), _stream(stream)),
-          "argcsr_plan_device_keep")
+    rest = (_ptr(A.row_ptr), int(block_dim), int(desired_chunk_size), int(fmt), ctypes.byref(g),
+            ctypes.byref(s), ctypes.byref(h), ctypes.byref(plan_h), _stream(stream))
+    if host_copy:
+        check(lib().argcsr_plan_keep(A.n_rows, A.row_ptr_host.ctypes.data, *rest),
+              "argcsr_plan_keep")
+    else:
+        check(lib().argcsr_plan_device_keep(A.n_rows, *rest), "argcsr_plan_device_keep")
     return plan_h, g.value, s.value, h.value
 
 
@@ -238,8 +243,9 @@ def convert(A: DeviceCsr, block_dim: int = 64, desired_chunk_size: int = 1,
     kept on the device between sizing and conversion
     (argcsr_plan_device_keep + argcsr_convert_planned; `keep_plan` is
     accepted and changes nothing).  Without it step 1 of a large matrix runs
-    there all the same (see _groups_on_device) and that of a small one on the
-    host; the result is the same bytes.
+    there all the same (see _groups_on_device), the host copy being checked
+    meanwhile (argcsr_plan_keep), and that of a small one on the host; the
+    result is the same bytes.
     `region_desired` (with `region_rows`) gives ARG-CSR a desiredChunkSize
     per region of rows (argcsr_plan_regions; the sizes are planned on the
     host).  `noalloc` converts with argcsr_convert_noalloc (the library
@@ -257,11 +263,11 @@ def convert(A: DeviceCsr, block_dim: int = 64, desired_chunk_size: int = 1,
         G, S, H = plan_regions(A.row_ptr_host, block_dim, region_rows, regions)
     elif device_grouping:
         _check_device_row_ptr(A.row_ptr)
-        plan_h, G, S, H = _plan_keep(A, block_dim, desired_chunk_size, fmt, stream)
+        plan_h, G, S, H = _plan_keep(A, block_dim, desired_chunk_size, fmt, stream, False)
     else:
         if not noalloc and _groups_on_device(A):
             try:
-                plan_h, G, S, H = _plan_keep(A, block_dim, desired_chunk_size, fmt, stream)
+                plan_h, G, S, H = _plan_keep(A, block_dim, desired_chunk_size, fmt, stream, True)
             except ArgCsrError as e:
                 if e.code != _lib_mod.ENOMEM:        # no room for the plan: group on the host
                     raise

@@ -108,6 +108,9 @@ SIGNATURES = {
     "argcsr_plan_device_keep": (ctypes.c_int, [i32, vp, i32, i32, i32, ctypes.POINTER(i32),
                                                ctypes.POINTER(i64), ctypes.POINTER(i32),
                                                ctypes.POINTER(vp), vp]),
+    "argcsr_plan_keep": (ctypes.c_int, [i32, vp, vp, i32, i32, i32, ctypes.POINTER(i32),
+                                        ctypes.POINTER(i64), ctypes.POINTER(i32),
+                                        ctypes.POINTER(vp), vp]),
     "argcsr_convert_planned": (ctypes.c_int, [vp, i32, vp, vp, vp, ctypes.POINTER(MatrixDesc),
                                               vp]),
     "argcsr_device_plan_destroy": (ctypes.c_int, [vp]),

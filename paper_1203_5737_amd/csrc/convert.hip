@@ -693,9 +693,12 @@ struct ResultBox {
 };
 
 // Steps 1-3 of n_rows > 0 rows on the device, and the sizes of the result
-// (one wait for the stream).
+// (one wait for the stream).  A host copy of the row offsets, when given, is
+// checked while the device works: 10^6 rows take the host 37 us, the device 45
+// or more.
 int build_plan(int32_t n_rows, const int32_t* row_ptr, int32_t T, int32_t desired, int32_t format,
-               int32_t region_rows, const int32_t* regions, hipStream_t s, argcsr_device_plan* p) {
+               int32_t region_rows, const int32_t* regions, hipStream_t s, argcsr_device_plan* p,
+               const int32_t* row_ptr_host = nullptr) {
   const size_t groups_b = sizeof(argcsr_group_info) * size_t(n_rows);
   const size_t tm_b = (sizeof(int32_t) * size_t(n_rows) + 15) / 16 * 16;
   ResultBox box;
@@ -722,13 +725,18 @@ int build_plan(int32_t n_rows, const int32_t* row_ptr, int32_t T, int32_t desire
                                                     p->heavy_parts, p->heavy_parts + kScanBlocks, st,
                                                     row_ptr, n_rows, box.dev);
   ARGCSR_HIP(hipGetLastError());
+  const int host_rc = row_ptr_host ? check_row_ptr(n_rows, row_ptr_host) : ARGCSR_OK;
   rc = box.read(s);
   if (rc) return rc;
   p->block.idle();
   work.idle();
   box.idle();
+  if (host_rc) return host_rc;
   if (box.word[kBoxBadRowPtr])
     return fail(ARGCSR_EINVAL, "row_ptr does not start at 0 or decreases");
+  if (row_ptr_host && int64_t(row_ptr_host[n_rows]) != box.word[kBoxNnz])
+    return fail(ARGCSR_EINVAL, "row_ptr_host ends at %d, row_ptr at %lld", row_ptr_host[n_rows],
+                (long long)box.word[kBoxNnz]);
   p->n_rows = n_rows;
   p->block_dim = T;
   p->desired_chunk_size = format == ARGCSR_FORMAT_RG ? 0 : desired;
@@ -1014,7 +1022,8 @@ namespace {
 // Steps 1-3 from a device row_ptr into *p, and the sizes of the result.
 int plan_device_impl(int32_t n_rows, const int32_t* row_ptr, int32_t block_dim,
                      int32_t desired_chunk_size, int32_t format, int32_t* n_groups,
-                     int64_t* n_slots, int32_t* n_heavy, hipStream_t s, argcsr_device_plan* p) {
+                     int64_t* n_slots, int32_t* n_heavy, hipStream_t s, argcsr_device_plan* p,
+                     const int32_t* row_ptr_host = nullptr) {
   if (!n_groups || !n_slots) return fail(ARGCSR_EINVAL, "NULL output pointer");
   if (n_rows < 0) return fail(ARGCSR_EINVAL, "n_rows < 0");
   if (format != ARGCSR_FORMAT_ARG && format != ARGCSR_FORMAT_RG)
@@ -1026,7 +1035,7 @@ int plan_device_impl(int32_t n_rows, const int32_t* row_ptr, int32_t block_dim,
   if (n_rows > 0 && !row_ptr) return fail(ARGCSR_EINVAL, "row_ptr is NULL");
   if (n_rows > 0) {
     const int rc = build_plan(n_rows, row_ptr, block_dim, desired_chunk_size, format, 0, nullptr,
-                              s, p);
+                              s, p, row_ptr_host);
     if (rc) return rc;
   }
   *n_groups = p->n_groups;
@@ -1050,12 +1059,13 @@ extern "C" int argcsr_plan_device(int32_t n_rows, const int32_t* row_ptr, int32_
                                   &p);
 }
 
-extern "C" int argcsr_plan_device_keep(int32_t n_rows, const int32_t* row_ptr, int32_t block_dim,
-                                       int32_t desired_chunk_size, int32_t format,
-                                       int32_t* n_groups, int64_t* n_slots, int32_t* n_heavy,
-                                       argcsr_device_plan** plan, void* stream) {
-  using namespace argcsr;
-  clear_error();
+namespace argcsr {
+namespace {
+
+int plan_keep_impl(int32_t n_rows, const int32_t* row_ptr_host, const int32_t* row_ptr,
+                   int32_t block_dim, int32_t desired_chunk_size, int32_t format,
+                   int32_t* n_groups, int64_t* n_slots, int32_t* n_heavy,
+                   argcsr_device_plan** plan, hipStream_t s) {
   if (!plan) return fail(ARGCSR_EINVAL, "plan is NULL");
   *plan = nullptr;
   auto* p = new (std::nothrow) argcsr_device_plan();
@@ -1065,13 +1075,41 @@ extern "C" int argcsr_plan_device_keep(int32_t n_rows, const int32_t* row_ptr, i
   p->desired_chunk_size = format == ARGCSR_FORMAT_RG ? 0 : desired_chunk_size;
   p->format = format;
   const int rc = plan_device_impl(n_rows, row_ptr, block_dim, desired_chunk_size, format,
-                                  n_groups, n_slots, n_heavy, static_cast<hipStream_t>(stream), p);
+                                  n_groups, n_slots, n_heavy, s, p, row_ptr_host);
   if (rc) {
     delete p;
     return rc;
   }
   *plan = p;
   return ARGCSR_OK;
+}
+
+}  // namespace
+}  // namespace argcsr
+
+extern "C" int argcsr_plan_device_keep(int32_t n_rows, const int32_t* row_ptr, int32_t block_dim,
+                                       int32_t desired_chunk_size, int32_t format,
+                                       int32_t* n_groups, int64_t* n_slots, int32_t* n_heavy,
+                                       argcsr_device_plan** plan, void* stream) {
+  argcsr::clear_error();
+  return argcsr::plan_keep_impl(n_rows, nullptr, row_ptr, block_dim, desired_chunk_size, format,
+                                n_groups, n_slots, n_heavy, plan,
+                                static_cast<hipStream_t>(stream));
+}
+
+extern "C" int argcsr_plan_keep(int32_t n_rows, const int32_t* row_ptr_host,
+                                const int32_t* row_ptr, int32_t block_dim,
+                                int32_t desired_chunk_size, int32_t format, int32_t* n_groups,
+                                int64_t* n_slots, int32_t* n_heavy, argcsr_device_plan** plan,
+                                void* stream) {
+  using namespace argcsr;
+  clear_error();
+  if (n_rows > 0 && !row_ptr_host) {
+    if (plan) *plan = nullptr;
+    return fail(ARGCSR_EINVAL, "row_ptr_host is NULL");
+  }
+  return plan_keep_impl(n_rows, row_ptr_host, row_ptr, block_dim, desired_chunk_size, format,
+                        n_groups, n_slots, n_heavy, plan, static_cast<hipStream_t>(stream));
 }
 
 extern "C" int argcsr_convert_planned(const argcsr_device_plan* plan, int32_t n_cols,

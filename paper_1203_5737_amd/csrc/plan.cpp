@@ -3,6 +3,7 @@
 #include "plan.hpp"
 
 #include <algorithm>
+#include <exception>
 #include <thread>
 
 #include "common.hpp"
@@ -12,6 +13,56 @@ namespace argcsr {
 
 namespace {
 constexpr int32_t kMaxGroupRows = 1024;   // plan/convert accept block_dim <= 1024
+
+// Whether rp decreases somewhere in [first, last): no early exit, so that the
+// loop takes several rows at a time, eight where the processor has AVX2.
+#define ARGCSR_DECREASES                                               \
+  int32_t bad = 0;                                                     \
+  for (int64_t r = first; r < last; ++r) bad |= rp[r + 1] < rp[r];     \
+  return bad != 0;
+bool decreases_any(const int32_t* rp, int64_t first, int64_t last) { ARGCSR_DECREASES }
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+__attribute__((target("avx2"))) bool decreases_avx2(const int32_t* rp, int64_t first,
+                                                    int64_t last) {
+  ARGCSR_DECREASES
+}
+bool decreases(const int32_t* rp, int64_t first, int64_t last) {
+  static const bool avx2 = __builtin_cpu_supports("avx2");
+  return avx2 ? decreases_avx2(rp, first, last) : decreases_any(rp, first, last);
+}
+#else
+bool decreases(const int32_t* rp, int64_t first, int64_t last) {
+  return decreases_any(rp, first, last);
+}
+#endif
+
+// The same for all n rows, by several threads where they pay: 10^6 rows 37 us
+// with one, 26 with two; 4*10^6 rows 331 with one, 101 with four; 3*10^5 rows
+// 11 / 13.  (Without AVX2 10^6 rows take one thread 75 us.)
+bool any_decreases(const int32_t* rp, int32_t n) {
+  constexpr int kMost = 4;
+  constexpr int32_t kRowsEach = 1 << 20;
+  const int parts = int(std::min<int64_t>(kMost, 1 + int64_t(n) / kRowsEach));
+  bool bad[kMost] = {};
+  auto part = [&](int i) {
+    bad[i] = decreases(rp, int64_t(n) * i / parts, int64_t(n) * (i + 1) / parts);
+  };
+  std::thread helper[kMost];
+  for (int i = 1; i < parts; ++i) {
+    try {
+      helper[i] = std::thread(part, i);
+    } catch (const std::exception&) {       // no thread to be had
+      part(i);
+    }
+  }
+  part(0);
+  bool any = bad[0];
+  for (int i = 1; i < parts; ++i) {
+    if (helper[i].joinable()) helper[i].join();
+    any |= bad[i];
+  }
+  return any;
+}
 }  // namespace
 
 int check_row_ptr(int32_t n_rows, const int32_t* rp) {
@@ -19,6 +70,7 @@ int check_row_ptr(int32_t n_rows, const int32_t* rp) {
   if (n_rows > 0 && rp == nullptr) return fail(ARGCSR_EINVAL, "row_ptr is NULL");
   if (rp == nullptr) return ARGCSR_OK;
   if (rp[0] != 0) return fail(ARGCSR_EINVAL, "row_ptr[0] = %d, expected 0", rp[0]);
+  if (!any_decreases(rp, n_rows)) return ARGCSR_OK;
   for (int32_t r = 0; r < n_rows; ++r)
     if (rp[r + 1] < rp[r])
       return fail(ARGCSR_EINVAL, "row_ptr decreases at row %d", r);

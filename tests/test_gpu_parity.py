@@ -749,3 +749,46 @@ def test_full_stencil_all_dtypes(ac, stencil_full, T):
         announce(f"stencil T={T} dtype={dtype}: accumulation err {acc:.2e}, total {tot:.2e}")
         del M
     torch.cuda.empty_cache()
+
+
+# convert() does not need the host's row offsets of a large matrix for
+# grouping, but a malformed copy is refused as it is for a small one; 2.5*10^6
+# rows are checked by several threads
+@pytest.mark.parametrize("n", [500, 8192, 2_500_000])
+@pytest.mark.parametrize("where", ["first", "start", "middle", "end", "last"])
+def test_malformed_host_row_offsets_are_refused(ac, n, where):
+    L = np.random.default_rng(3).integers(1, 4, n)
+    rp = np.concatenate([[0], np.cumsum(L)]).astype(np.int32)
+    nnz = int(rp[-1])
+    dev = ac.DeviceCsr(n, 10, rp.copy(), torch.from_numpy(rp).to(DEV),
+                       torch.zeros(nnz, dtype=torch.int32, device=DEV),
+                       torch.ones(nnz, dtype=torch.float64, device=DEV))
+    good = ac.convert(dev, 64, 1)
+    r = {"first": 0, "start": 1, "middle": n // 2, "end": n - 1, "last": n}[where]
+    # not 0 first, or a decrease at r
+    dev.row_ptr_host[r] = 1 if where == "first" else rp[r - 1] - 1
+    with pytest.raises(ac.ArgCsrError) as e:
+        ac.convert(dev, 64, 1)
+    assert e.value.code == ac._lib.EINVAL
+    if where == "last" and ac._groups_on_device(dev):   # the copy of another matrix
+        dev.row_ptr_host[n] = rp[n] + 1
+        with pytest.raises(ac.ArgCsrError) as e:
+            ac.convert(dev, 64, 1)
+        assert e.value.code == ac._lib.EINVAL
+    dev.row_ptr_host[:] = rp
+    assert torch.equal(ac.convert(dev, 64, 1).columns, good.columns)
+
+
+def test_host_row_offsets_of_another_kind_are_taken_as_before(ac):
+    """A list, another integer type or a strided view: grouped on the host."""
+    n = 9000
+    A = csr_from_lengths(np.random.default_rng(4).integers(0, 9, n), 500, 4)
+    dev = ac.to_device_csr(A.rp, A.col, A.val, A.n_cols, DEV)
+    good = ac.convert(dev, 64, 1)
+    dev.row_ptr_host = np.repeat(A.rp, 2)[::2]
+    assert not ac._groups_on_device(dev)
+    assert ac.plan(dev.row_ptr_host, 64, 1) == (good.n_groups, good.n_slots, good.n_heavy)
+    dev.row_ptr_host = None
+    with pytest.raises(Exception):
+        ac.convert(dev, 64, 1)
+    assert torch.equal(ac.convert(dev, 64, 1, device_grouping=True).columns, good.columns)
