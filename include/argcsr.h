@@ -197,6 +197,15 @@ int argcsr_choose_region_desired(int32_t n_rows, const int32_t* row_ptr_host,
                                  int32_t* region_desired);
 
 /*
+ * argcsr_trim_scratch -- frees the device scratch that the library keeps on
+ * the current device between calls (planning, conversion and binning leave at
+ * most 2 GiB there; the library frees it by itself when one of its own
+ * allocations fails).  Scratch in use by other threads stays.
+ * Errors: EHIP.
+ */
+int argcsr_trim_scratch(void);
+
+/*
  * argcsr_plan_device -- the sizes argcsr_plan computes (same grouping rule,
  * same results), from a row_ptr that lives only in device memory: steps 1-2
  * of Sec. 3 run as HIP kernels on `stream` (step 1 from the

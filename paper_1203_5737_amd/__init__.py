@@ -255,54 +255,73 @@ def convert(A: DeviceCsr, block_dim: int = 64, desired_chunk_size: int = 1,
         raise ValueError("argcsr_convert_noalloc groups the rows on the host")
     if fmt == FORMAT_RG:
         desired_chunk_size = 0
-    regions = None
-    plan_h = None
+    how = (int(block_dim), int(desired_chunk_size), int(dtype), stream, schedule, int(fmt))
     if region_desired is not None:
         regions = np.ascontiguousarray(np.asarray(region_desired, dtype=np.int32))
-        desired_chunk_size = 0
-        G, S, H = plan_regions(A.row_ptr_host, block_dim, region_rows, regions)
-    elif device_grouping:
+        how = how[:1] + (0,) + how[2:]
+        sizes = plan_regions(A.row_ptr_host, block_dim, region_rows, regions)
+        return _convert_sized(A, how, sizes, None if device_grouping else A.row_ptr_host, None,
+                              noalloc, int(region_rows), regions)
+    if device_grouping:
         _check_device_row_ptr(A.row_ptr)
-        plan_h, G, S, H = _plan_keep(A, block_dim, desired_chunk_size, fmt, stream, False)
-    else:
-        if not noalloc and _groups_on_device(A):
-            try:
-                plan_h, G, S, H = _plan_keep(A, block_dim, desired_chunk_size, fmt, stream, True)
-            except ArgCsrError as e:
-                if e.code != _lib_mod.ENOMEM:        # no room for the plan: group on the host
-                    raise
-        if plan_h is None:
-            G, S, H = plan(A.row_ptr_host, block_dim, desired_chunk_size, fmt)
+        return _convert_planned(A, how, False)
+    if not noalloc and _groups_on_device(A):
+        try:
+            return _convert_planned(A, how, True)
+        except ArgCsrError as e:
+            if e.code != _lib_mod.ENOMEM:
+                raise
+        except torch.OutOfMemoryError:
+            pass
+        # no room for the plan, or beside it for the result: the scratch goes
+        # back to the device and the rows are grouped on the host
+        check(lib().argcsr_trim_scratch(), "argcsr_trim_scratch")
+    sizes = plan(A.row_ptr_host, block_dim, desired_chunk_size, fmt)
+    return _convert_sized(A, how, sizes, A.row_ptr_host, None, noalloc)
+
+
+def _convert_planned(A: DeviceCsr, how, host_copy: bool) -> ArgCsrMatrix:
+    """convert() by a device plan (see _plan_keep)."""
+    block_dim, desired_chunk_size, _, stream, _, fmt = how
+    plan_h, *sizes = _plan_keep(A, block_dim, desired_chunk_size, fmt, stream, host_copy)
     try:
-        dev = A.row_ptr.device
-        out = ArgCsrMatrix(
-            A.n_rows, A.n_cols, int(block_dim), int(desired_chunk_size), int(dtype), G, A.nnz, S,
-            torch.empty((G, 4), dtype=torch.int32, device=dev),
-            torch.empty(A.n_rows, dtype=torch.int32, device=dev),
-            torch.empty(S, dtype=torch.int32, device=dev),
-            torch.empty(S, dtype=_STORAGE[dtype], device=dev),
-            torch.empty(H, dtype=torch.int32, device=dev) if schedule else None,
-            H if schedule else 0, 0, int(fmt))
-        d = out.desc()
-        if schedule and H == 0:
-            d.heavy_groups = None
-        if regions is not None:
-            d.region_rows = int(region_rows)
-            d.region_desired = regions.ctypes.data_as(ctypes.c_void_p)
-        if plan_h is not None:
-            check(lib().argcsr_convert_planned(plan_h, A.n_cols, _ptr(A.row_ptr), _ptr(A.col),
-                                               _ptr(A.val), ctypes.byref(d), _stream(stream)),
-                  "argcsr_convert_planned")
-        else:
-            rp_host = (None if device_grouping
-                       else A.row_ptr_host.ctypes.data_as(ctypes.c_void_p))
-            fn, name = ((lib().argcsr_convert_noalloc, "argcsr_convert_noalloc") if noalloc
-                        else (lib().argcsr_convert, "argcsr_convert"))
-            check(fn(A.n_rows, A.n_cols, rp_host, _ptr(A.row_ptr), _ptr(A.col), _ptr(A.val),
-                     ctypes.byref(d), _stream(stream)), name)
+        return _convert_sized(A, how, sizes, None, plan_h, False)
     finally:
-        if plan_h is not None:
-            lib().argcsr_device_plan_destroy(plan_h)
+        lib().argcsr_device_plan_destroy(plan_h)
+
+
+def _convert_sized(A: DeviceCsr, how, sizes, rp_host, plan_h, noalloc: bool,
+                   region_rows: int = 0, regions=None) -> ArgCsrMatrix:
+    """Allocates the result of the planned sizes and converts into it: by the
+    device plan `plan_h`, or by argcsr_convert (argcsr_convert_noalloc) with
+    rp_host, None to group on the device."""
+    block_dim, desired_chunk_size, dtype, stream, schedule, fmt = how
+    G, S, H = sizes
+    dev = A.row_ptr.device
+    out = ArgCsrMatrix(
+        A.n_rows, A.n_cols, block_dim, desired_chunk_size, dtype, G, A.nnz, S,
+        torch.empty((G, 4), dtype=torch.int32, device=dev),
+        torch.empty(A.n_rows, dtype=torch.int32, device=dev),
+        torch.empty(S, dtype=torch.int32, device=dev),
+        torch.empty(S, dtype=_STORAGE[dtype], device=dev),
+        torch.empty(H, dtype=torch.int32, device=dev) if schedule else None,
+        H if schedule else 0, 0, fmt)
+    d = out.desc()
+    if schedule and H == 0:
+        d.heavy_groups = None
+    if regions is not None:
+        d.region_rows = region_rows
+        d.region_desired = regions.ctypes.data_as(ctypes.c_void_p)
+    if plan_h is not None:
+        check(lib().argcsr_convert_planned(plan_h, A.n_cols, _ptr(A.row_ptr), _ptr(A.col),
+                                           _ptr(A.val), ctypes.byref(d), _stream(stream)),
+              "argcsr_convert_planned")
+    else:
+        rp_host = None if rp_host is None else rp_host.ctypes.data_as(ctypes.c_void_p)
+        fn, name = ((lib().argcsr_convert_noalloc, "argcsr_convert_noalloc") if noalloc
+                    else (lib().argcsr_convert, "argcsr_convert"))
+        check(fn(A.n_rows, A.n_cols, rp_host, _ptr(A.row_ptr), _ptr(A.col), _ptr(A.val),
+                 ctypes.byref(d), _stream(stream)), name)
     out.nnz = int(d.nnz)
     out.heavy_chunk = int(d.heavy_chunk)
     if not schedule:

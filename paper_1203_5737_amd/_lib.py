@@ -102,6 +102,7 @@ SIGNATURES = {
     "argcsr_plan_regions": (ctypes.c_int, [i32, vp, i32, i32, vp, ctypes.POINTER(i32),
                                            ctypes.POINTER(i64), ctypes.POINTER(i32)]),
     "argcsr_choose_region_desired": (ctypes.c_int, [i32, vp, i32, i32, vp]),
+    "argcsr_trim_scratch": (ctypes.c_int, []),
     "argcsr_plan_device": (ctypes.c_int, [i32, vp, i32, i32, i32, ctypes.POINTER(i32),
                                           ctypes.POINTER(i64), ctypes.POINTER(i32), vp]),
     "argcsr_convert": (ctypes.c_int, [i32, i32, vp, vp, vp, vp, ctypes.POINTER(MatrixDesc), vp]),

@@ -40,7 +40,27 @@ size_t rounded(size_t bytes) {
   return (std::max<size_t>(bytes, 1) + step - 1) / step * step;
 }
 
+// Frees what a cache holds.
+void empty(Cache& c) {
+  Block drop[DeviceScratch::kKeepBlocks + 1];
+  int n_drop = 0;
+  {
+    std::lock_guard<std::mutex> lock(c.mu);
+    while (c.n > 0) drop[n_drop++] = c.take(c.n - 1);
+  }
+  const RelaxedCapture relaxed;
+  for (int i = 0; i < n_drop; ++i) (void)hipFree(drop[i].p);
+}
+
 }  // namespace
+
+int DeviceScratch::trim() {
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices)
+    return fail(ARGCSR_EHIP, "no current device");
+  empty(g_caches[dev]);
+  return ARGCSR_OK;
+}
 
 int DeviceScratch::alloc(size_t bytes, hipStream_t s) {
   release();
@@ -69,13 +89,7 @@ int DeviceScratch::alloc(size_t bytes, hipStream_t s) {
     const RelaxedCapture relaxed;
     hipError_t e = hipMalloc(&ptr_, want);
     if (e == hipErrorOutOfMemory) {
-      Block drop[DeviceScratch::kKeepBlocks + 1];
-      int n_drop = 0;
-      {
-        std::lock_guard<std::mutex> lock(c.mu);
-        while (c.n > 0) drop[n_drop++] = c.take(c.n - 1);
-      }
-      for (int i = 0; i < n_drop; ++i) (void)hipFree(drop[i].p);
+      empty(c);
       e = hipMalloc(&ptr_, want);
     }
     if (e != hipSuccess) {
@@ -122,3 +136,8 @@ void DeviceScratch::release() {
 }
 
 }  // namespace argcsr
+
+extern "C" int argcsr_trim_scratch(void) {
+  argcsr::clear_error();
+  return argcsr::DeviceScratch::trim();
+}

@@ -35,6 +35,8 @@ class DeviceScratch {
   // waits again before the block goes
   void idle() { idle_ = true; }
   void release();
+  // frees what the current device's cache holds (argcsr_trim_scratch)
+  static int trim();
 
  private:
   void* ptr_ = nullptr;

@@ -792,3 +792,57 @@ def test_host_row_offsets_of_another_kind_are_taken_as_before(ac):
     with pytest.raises(Exception):
         ac.convert(dev, 64, 1)
     assert torch.equal(ac.convert(dev, 64, 1, device_grouping=True).columns, good.columns)
+
+
+@pytest.mark.parametrize("short", ["plan", "result", "fill"])
+def test_conversion_without_room_for_the_plan(ac, monkeypatch, short):
+    """No memory for the device plan, or beside it for the result or for the
+    fill's scratch: the library's scratch goes back to the device and the
+    rows are grouped on the host, as they were before there was a plan.  A
+    conversion that asked for device grouping fails instead."""
+    from paper_1203_5737_amd import _lib
+    A = csr_from_lengths(np.random.default_rng(8).integers(0, 9, 30_000), 500, 8)
+    dev = ac.to_device_csr(A.rp, A.col, A.val, A.n_cols, DEV)
+    ref = oracle.convert(A.rp, A.col, A.val, 64, 1)
+    made = []
+
+    class NoRoom:
+        """The library, or torch, out of memory while a plan is about."""
+        def __getattr__(self, name):
+            if short == "plan" and name in ("argcsr_plan_keep", "argcsr_plan_device_keep"):
+                return lambda *a: _lib.ENOMEM
+            if short == "fill" and name == "argcsr_convert_planned":
+                return lambda *a: _lib.ENOMEM
+            made.append(name)
+            return getattr(real, name)
+    real = _lib.lib()
+    empty = torch.empty
+
+    def no_room(size, *a, **kw):
+        if "argcsr_convert_planned" not in made and made and made[-1].startswith("argcsr_plan_") \
+                and size == ref.columns.shape[0]:
+            raise torch.OutOfMemoryError("no room")
+        return empty(size, *a, **kw)
+    monkeypatch.setattr(ac, "lib", lambda: NoRoom())
+    if short == "result":
+        monkeypatch.setattr(torch, "empty", no_room)
+    M = ac.convert(dev, 64, 1)
+    assert "argcsr_trim_scratch" in made and "argcsr_convert" in made
+    got = (M.groups, M.threads_mapping, M.columns, M.values)
+    for g, w in zip(got, (ref.groups, ref.tm, ref.columns, ref.values)):
+        assert np.array_equal(g.cpu().numpy(), w)
+    made.clear()
+    with pytest.raises((ac.ArgCsrError, torch.OutOfMemoryError)):
+        ac.convert(dev, 64, 1, device_grouping=True)
+    assert "argcsr_convert" not in made
+
+
+def test_trimmed_scratch_goes_back_to_the_device(ac):
+    n = 3_000_000
+    rp = torch.arange(n + 1, dtype=torch.int32, device=DEV)
+    ac.plan_device(rp, 64, 1)
+    torch.cuda.synchronize()
+    kept = torch.cuda.mem_get_info()[0]
+    ac.check(ac._lib.lib().argcsr_trim_scratch(), "argcsr_trim_scratch")
+    assert torch.cuda.mem_get_info()[0] - kept >= 20 * n
+    assert ac.plan_device(rp, 64, 1)[0] == (n + 63) // 64

@@ -219,6 +219,15 @@ int main() {
     a.idle();
   }
   CHECK(g_dev.size() == 1);
+  {                                     // given back on request, what is in use is not
+    DeviceScratch a, b;
+    CHECK(a.alloc(64 * kMB, s) == ARGCSR_OK && b.alloc(64 * kMB, s) == ARGCSR_OK);
+    a.idle();
+    a.release();
+    CHECK(argcsr_trim_scratch() == ARGCSR_OK && g_dev.size() == 1 && g_dev.count(b.ptr()) == 1);
+    b.idle();
+  }
+  CHECK(g_dev.size() == 1);
   {                                     // any other failure is no lack of memory: the cache stays
     g_malloc_result = hipErrorUnknown;
     DeviceScratch a;
