@@ -22,18 +22,53 @@ namespace argcsr {
 namespace {
 
 constexpr int kCsrBlock = 256;
-// Elements of a row of bin 7 a lane loads at a time: 16 with up to kFewLongRows
-// of them, when the longest row's round trips are what the launch takes, else
-// 8, whose registers leave the CU more waves.  Power-law rows, us with 16 / 8:
-// FP32 2.4*10^5 rows (2300 of bin 7) 27.5 / 31.9, 4.5*10^5 (4200) 27 / 33, 10^6
-// (9400) 63.7 / 59.4; FP64 27.7 / 35.0, 37 / 39, 83.6 / 81.2.
-constexpr int32_t kFewLongRows = 4096;
+constexpr int kLongBatch = 8;     // elements of a row of bin 7 a lane loads at a time, or half
+
+// How the rows of bin 7 are read: those of up to `single` elements one element
+// a lane after the other, longer ones in batches.  A batch hides the chain of
+// column, x and sum, but many workgroups' batches queue their gathers in front
+// of each other's loads.  With `streamed` the elements pass by L2 and the
+// Infinity Cache.  us, three matrices in turn, FP32 but where marked:
+// * Up to kCachedBytes a matrix the Infinity Cache holds the elements: ordinary
+//   loads, and batches for the few longest rows alone, whose round trips the
+//   launch takes.  Batches for rows over 4096 / for all / for all and streamed:
+//   1000 rows of 3000 11.8 / 15.1 / 17.7, 4000 of 1000 20.4 / 21.3 / 26,
+//   power-law rows of 3*10^5 20.6 / 21.8 / 30, 10^6 54 / 54 / 59.5 (without
+//   batches 61).
+// * Beyond, they come from HBM and are streamed.  A lane's first element needs
+//   no batch, rows of 1024 just half a one: 70^3 rows of 125, singly / batches of
+//   8, 323 / 370, BF16 318 / 407; 10^5 rows of 1000, batches of 4 / 8, 535 / 611,
+//   FP64 589 / 659; 3*10^5 rows of 300, batches of 4 / singly, 533 / 582, FP64
+//   617 / 627, BF16 588 / 568.  Ordinary loads: 4000 rows of 400 beside 3*10^5 of
+//   27 93 against 79, but 96 MB of rows of 3000 63 against 74.
+// * Earlier where x does not fit the L2 beside them: power-law rows, streamed /
+//   not, FP64 8.5*10^5 (68 MB) 63.4 / 63.0, 10^6 (80 MB) 81.2 / 83.2, FP32
+//   1.5*10^6 (80 MB) 94 / 97.
+struct LongRows {
+  int32_t single;
+  bool streamed;
+};
+constexpr int64_t kCachedBytes = 100 * 1000 * 1000;
+constexpr int64_t kCachedBesideX = 75 * 1000 * 1000;
+constexpr int64_t kL2Bytes = int64_t(4) << 20;    // of an XCD
+constexpr LongRows long_rows(int64_t nnz, int32_t value_bytes, int32_t n_cols, int32_t x_bytes) {
+  const int64_t bytes = nnz * (int64_t(sizeof(int32_t)) + value_bytes);
+  const bool x_in_l2 = int64_t(n_cols) * x_bytes <= kL2Bytes;
+  if (bytes < (x_in_l2 ? kCachedBytes : kCachedBesideX)) return LongRows{4096, false};
+  return LongRows{value_bytes == 2 ? 512 : 256, true};
+}
 constexpr int kBins = ARGCSR_CSR_BINS;      // 8: widths 1, 2, 4, ..., 64, then a workgroup
+
+template <bool STREAMED, typename T>
+__device__ __forceinline__ T load_element(const T* p) {
+  if constexpr (STREAMED) return __builtin_nontemporal_load(p);
+  else return *p;
+}
 
 // sum plus fma(val, x[col], ...) over elements k, k + stride, ... below end, in that
 // order, U of them loaded at a time: a long row is not one chain of column,
 // x and sum after the other.
-template <int DT, int U>
+template <int DT, int U, bool STREAMED = false>
 __device__ __forceinline__ typename Val<DT>::acc strided_sum(
     int32_t k, int32_t end, int32_t stride, const int32_t* __restrict__ col,
     const typename Val<DT>::storage* __restrict__ val,
@@ -46,25 +81,25 @@ __device__ __forceinline__ typename Val<DT>::acc strided_sum(
     A xv[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      c[u] = col[k + u * stride];
-      v[u] = val[k + u * stride];
+      c[u] = load_element<STREAMED>(col + k + u * stride);
+      v[u] = load_element<STREAMED>(val + k + u * stride);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) xv[u] = x[c[u]];
 #pragma unroll
     for (int u = 0; u < U; ++u) sum = __builtin_fma(Vt::load(v[u]), xv[u], sum);
   }
-  for (; k < end; k += stride) sum = __builtin_fma(Vt::load(val[k]), x[col[k]], sum);
+  for (; k < end; k += stride)
+    sum = __builtin_fma(Vt::load(load_element<STREAMED>(val + k)),
+                        x[load_element<STREAMED>(col + k)], sum);
   return sum;
 }
 
 // As strided_sum over elements k0 + lane, + kCsrBlock, ... below end (k0 the same
 // for the wave), the elements left over from whole batches in one batch too:
-// one by one, their chains of column and x were most of a row of less than
-// U * kCsrBlock elements and half of one of 10^4.  Lanes past the end load the
-// row's last element and do not use it.  The elements are read once and by
-// this wave alone (non-temporal loads: L2 stays for x).
-template <int DT, int U>
+// one by one, their chains of column and x were half of a row of 10^4.  Lanes
+// past the end load the row's last element and do not use it.
+template <int DT, int U, bool STREAMED>
 __device__ __forceinline__ typename Val<DT>::acc long_row_sum(
     int32_t k0, int32_t end, const int32_t* __restrict__ col,
     const typename Val<DT>::storage* __restrict__ val,
@@ -79,8 +114,8 @@ __device__ __forceinline__ typename Val<DT>::acc long_row_sum(
   for (; end - k0 > (U - 1) * kCsrBlock + 63; k0 += U * kCsrBlock) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      c[u] = __builtin_nontemporal_load(col + k0 + lane + u * kCsrBlock);
-      v[u] = __builtin_nontemporal_load(val + k0 + lane + u * kCsrBlock);
+      c[u] = load_element<STREAMED>(col + k0 + lane + u * kCsrBlock);
+      v[u] = load_element<STREAMED>(val + k0 + lane + u * kCsrBlock);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) xv[u] = x[c[u]];
@@ -93,8 +128,8 @@ __device__ __forceinline__ typename Val<DT>::acc long_row_sum(
     v[u] = 0;
     if (end - k0 > u * kCsrBlock) {
       const int32_t k = min(k0 + lane + u * kCsrBlock, end - 1);
-      c[u] = __builtin_nontemporal_load(col + k);
-      v[u] = __builtin_nontemporal_load(val + k);
+      c[u] = load_element<STREAMED>(col + k);
+      v[u] = load_element<STREAMED>(val + k);
     }
   }
 #pragma unroll
@@ -216,12 +251,15 @@ __device__ __forceinline__ void binned_rows(const BinLaunch& bl, int k, int32_t 
 // Bound by the x gathers on power-law rows and by the CSR stream on regular
 // ones.  MI355X: power-law rows of 10^6 FP64 125 us -> 81 (long rows first and
 // loaded eight elements at a time a lane, regions, a workgroup per long row),
-// 27-point stencil 100^3 FP64 171 -> 105.
-template <int DT, int R, int L>
+// 27-point stencil 100^3 FP64 171 -> 105.  The code for bin 7 sets the
+// registers of every workgroup: with batches of 16 the other bins kept 5 waves
+// a SIMD of 8 (that stencil 138 us, in BF16 176 against 124).
+template <int DT, int R, bool STREAMED>
 __global__ __launch_bounds__(kCsrBlock) void csr_binned_kernel(
     BinLaunch bl, const int32_t* __restrict__ rows, const int32_t* __restrict__ rp,
     const int32_t* __restrict__ col, const typename Val<DT>::storage* __restrict__ val,
-    const typename Val<DT>::acc* __restrict__ x, typename Val<DT>::acc* __restrict__ y) {
+    const typename Val<DT>::acc* __restrict__ x, typename Val<DT>::acc* __restrict__ y,
+    int32_t single) {
   using A = typename Val<DT>::acc;
   constexpr int kBlockWaves = kCsrBlock / 64;
   int k = kBins - 1;
@@ -257,7 +295,13 @@ __global__ __launch_bounds__(kCsrBlock) void csr_binned_kernel(
   __shared__ A part[kBlockWaves];
   const int wv = wave_uniform(int(threadIdx.x >> 6));
   const int32_t row = rows[bl.row_start[k] + b];
-  A sum = long_row_sum<DT, L>(rp[row] + wv * 64, rp[row + 1], col, val, x);
+  const int32_t begin = rp[row], end = rp[row + 1];
+  const int32_t k0 = begin + wv * 64;
+  A sum = end - begin <= single
+              ? strided_sum<DT, 1, STREAMED>(k0 + lane_id(), end, kCsrBlock, col, val, x)
+          : end - begin <= kLongBatch / 2 * kCsrBlock
+              ? long_row_sum<DT, kLongBatch / 2, STREAMED>(k0, end, col, val, x)
+              : long_row_sum<DT, kLongBatch, STREAMED>(k0, end, col, val, x);
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
   if (lane_id() == 0) part[wv] = sum;
@@ -391,16 +435,19 @@ int team_rows(const int32_t* bin_start) {
 }
 
 template <int DT>
-void launch_binned(const BinLaunch& bl, int team, int32_t blocks, const int32_t* rows,
-                   const int32_t* rp, const int32_t* col, const void* val, const void* x, void* y,
-                   hipStream_t s) {
+void launch_binned(const BinLaunch& bl, int team, int32_t blocks, int64_t nnz, int32_t n_cols,
+                   const int32_t* rows, const int32_t* rp, const int32_t* col, const void* val,
+                   const void* x, void* y, hipStream_t s) {
   using Vt = Val<DT>;
-  const bool few = bl.blocks[kBins - 1] <= kFewLongRows;
-  auto* kern = team == 4 ? few ? &csr_binned_kernel<DT, 4, 16> : &csr_binned_kernel<DT, 4, 8>
-                         : few ? &csr_binned_kernel<DT, 1, 16> : &csr_binned_kernel<DT, 1, 8>;
+  const LongRows lr = long_rows(nnz, int32_t(sizeof(typename Vt::storage)), n_cols,
+                                int32_t(sizeof(typename Vt::acc)));
+  auto* kern = team == 4 ? lr.streamed ? &csr_binned_kernel<DT, 4, true>
+                                       : &csr_binned_kernel<DT, 4, false>
+                         : lr.streamed ? &csr_binned_kernel<DT, 1, true>
+                                       : &csr_binned_kernel<DT, 1, false>;
   kern<<<blocks, kCsrBlock, 0, s>>>(
       bl, rows, rp, col, static_cast<const typename Vt::storage*>(val),
-      static_cast<const typename Vt::acc*>(x), static_cast<typename Vt::acc*>(y));
+      static_cast<const typename Vt::acc*>(x), static_cast<typename Vt::acc*>(y), lr.single);
 }
 
 }  // namespace
@@ -490,11 +537,14 @@ extern "C" int argcsr_csr_spmv_binned(int32_t n_rows, int32_t n_cols, int64_t nn
   if (x == y) return fail(ARGCSR_EINVAL, "y must not alias x");
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int32_t nb = int32_t(grid);
+  auto go = [&](auto* launch) {
+    launch(bl, team, nb, nnz, n_cols, rows, row_ptr, col, val, x, y, s);
+  };
   switch (dtype) {
-    case ARGCSR_F64: launch_binned<ARGCSR_F64>(bl, team, nb, rows, row_ptr, col, val, x, y, s); break;
-    case ARGCSR_F32: launch_binned<ARGCSR_F32>(bl, team, nb, rows, row_ptr, col, val, x, y, s); break;
-    case ARGCSR_BF16: launch_binned<ARGCSR_BF16>(bl, team, nb, rows, row_ptr, col, val, x, y, s); break;
-    default: launch_binned<ARGCSR_F16>(bl, team, nb, rows, row_ptr, col, val, x, y, s); break;
+    case ARGCSR_F64: go(&launch_binned<ARGCSR_F64>); break;
+    case ARGCSR_F32: go(&launch_binned<ARGCSR_F32>); break;
+    case ARGCSR_BF16: go(&launch_binned<ARGCSR_BF16>); break;
+    default: go(&launch_binned<ARGCSR_F16>); break;
   }
   ARGCSR_HIP(hipGetLastError());
   return ARGCSR_OK;

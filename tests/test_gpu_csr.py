@@ -190,3 +190,33 @@ def test_binned_edge_cases(ac):
     bz.bin_start[8] = 299
     with pytest.raises(ac.ArgCsrError):
         ac.csr_spmv_binned(dz, torch.ones(10, dtype=torch.float64, device=DEV), bz)
+
+
+# how the rows of bin 7 are read: singly up to 4096 elements and in batches
+# above, in one launch (a matrix the Infinity Cache holds); from 100 MB of
+# elements on singly up to 256 (512 in 2-byte values), in batches of 4 up to
+# 1024 and of 8 above, streamed; from 75 MB on where x is over 4 MB
+@pytest.mark.parametrize("dtype,n_cols,mb", [
+    (0, 9000, 2), (0, 9000, 99), (0, 9000, 101), (0, 530_000, 74), (0, 530_000, 76),
+    (1, 9000, 99), (1, 9000, 101), (1, 1_060_000, 76), (2, 9000, 2), (2, 9000, 101)])
+def test_binned_long_row_paths(ac, dtype, n_cols, mb):
+    rng = np.random.default_rng(mb)
+    edges = np.array([65, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025, 2047, 2048, 2049, 4095,
+                      4096, 4097, 4096 + 255, 4096 + 256, 4096 + 257, 6143, 6144, 6145, 8191,
+                      8192, 8193])
+    elements = mb * 1_000_000 // (4 + [8, 4, 2, 2][dtype]) + 1
+    L = np.concatenate([edges, np.full((elements - edges.sum() - 600) // 2500, 2500),
+                        rng.integers(0, 65, 20)])
+    L = np.append(L, max(0, elements - L.sum())).astype(np.int64)
+    rng.shuffle(L)
+    A = synth.random_csr(L, n_cols, rng, rng)
+    x = rng.uniform(-1.0, 1.0, A.n_cols).astype(np.float32).astype(np.float64)
+    dev = ac.to_device_csr(A.rp, A.col, A.val, A.n_cols, DEV)
+    xd = torch.from_numpy(x).to(DEV, ac.vector_dtype(dtype))
+    vals = dev.val if dtype == 0 else stored_values(ac, A, dtype)
+    y = ac.csr_spmv_binned(dev, xd, ac.csr_bins(dev), values=vals, dtype=dtype)
+    yn = y.cpu().numpy().astype(np.float64)
+    if dtype == 0:
+        check_f64(A, x, yn)
+    else:
+        check_reduced(A, x, yn, dtype)

@@ -337,3 +337,20 @@ def test_built_library_has_no_packed_fp32(L, tmp_path):
         assert "s_endpgm" in asm or not asm.strip()
         hit = PACKED_FP32.search(asm)
         assert not hit, f"{o.name}: {hit.group(0)}"
+
+
+# -- registers ----------------------------------------------------------------
+
+@pytest.mark.skipif(not os.path.exists("/opt/rocm/bin/hipcc"), reason="needs hipcc")
+def test_binned_csr_keeps_its_occupancy(tmp_path):
+    """The binned CSR kernels hold the code of all bins: the long rows' must
+    not cost the short ones the CU's 8 waves a SIMD."""
+    from paper_1203_5737_amd import build
+    r = subprocess.run([build.HIPCC, *build.FLAGS, "--cuda-device-only", "-c",
+                        os.path.join(build.CSRC, "csr_spmv.hip"), "-o", str(tmp_path / "csr.o"),
+                        "-Rpass-analysis=kernel-resource-usage"], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    kernels = re.findall(r"Function Name: (\S+)(?s:.*?)Occupancy \[waves/SIMD\]: (\d+)", r.stderr)
+    binned = {name: int(w) for name, w in kernels if "csr_binned_kernel" in name}
+    assert len(binned) >= 8, r.stderr[-2000:]
+    assert set(binned.values()) == {8}, binned
