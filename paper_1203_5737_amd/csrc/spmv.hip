@@ -34,9 +34,12 @@ void launch(const argcsr_matrix* A, const void* x, void* y, hipStream_t s) {
   const int32_t n_heavy = sched ? A->n_heavy : 0;
   const int32_t heavy_chunk = sched ? A->heavy_chunk : INT32_MAX;
   const int blocks = n_heavy + (A->n_groups + kSpmvWaves - 1) / kSpmvWaves;
-  const bool serial = serial_gathers(int32_t(sizeof(typename Vt::storage)), A->block_dim,
-                                     A->n_slots, A->n_groups);
-  argcsr_spmv_kernel<DT, W, U><<<blocks, kSpmvWaves * 64, 0, s>>>(
+  constexpr int32_t kBytes = int32_t(sizeof(typename Vt::storage));
+  const bool serial = serial_gathers(kBytes, A->block_dim, A->n_slots, A->n_groups);
+  const bool wait = wait_for_mapping(kBytes, A->block_dim, A->n_rows, A->n_slots, A->n_groups,
+                                     n_heavy);
+  auto* kern = wait ? &argcsr_spmv_kernel<DT, W, U, true> : &argcsr_spmv_kernel<DT, W, U, false>;
+  kern<<<blocks, kSpmvWaves * 64, 0, s>>>(
       A->groups, A->n_groups, A->threads_mapping, A->columns,
       static_cast<const typename Vt::storage*>(A->values),
       static_cast<const typename Vt::acc*>(x), A->n_cols, static_cast<typename Vt::acc*>(y),

@@ -65,18 +65,26 @@ __device__ __forceinline__ argcsr_group_info load_group(const argcsr_group_info*
   return argcsr_group_info{first, size, offset, chunk};
 }
 
-// This lane's threads-mapping entries (rows l = 64*w + lane of the group).
-// Every lane loads, past the end of the group its last entry: a load under a
-// condition is waited for where the condition ends, before the chunk loads go
-// out, one round trip for each w.
-template <int W, bool STREAM = true>
+// This lane's threads-mapping entries (rows l = 64*w + lane of the group), 0
+// past its end.  Read by range-checked buffer loads, which need no condition:
+// a load under a condition is waited for where the condition ends, before the
+// chunk loads go out, one round trip for each w.  WAIT does just that (see
+// wait_for_mapping).
+template <int W, bool STREAM = true, bool WAIT = false>
 __device__ __forceinline__ void load_mapping(int32_t first, int32_t size,
                                              const int32_t* __restrict__ tm, int32_t (&tmv)[W]) {
+  constexpr int kNonTemporal = 2;                   // the load's cache policy
   const int lane = lane_id();
+  const __amdgpu_buffer_rsrc_t rows = buffer_rsrc(tm + first, uint32_t(size) * 4u);
 #pragma unroll
   for (int w = 0; w < W; ++w) {
     const int l = w * 64 + lane;
-    tmv[w] = load_matrix<STREAM>(tm + first + (l < size ? l : size - 1));
+    if constexpr (WAIT) {
+      tmv[w] = l < size ? load_matrix<STREAM>(tm + first + l) : 0;
+    } else {
+      tmv[w] = __builtin_amdgcn_raw_buffer_load_b32(rows, uint32_t(l) * 4u, 0,
+                                                    STREAM ? kNonTemporal : 0);
+    }
   }
 }
 
@@ -94,7 +102,7 @@ __device__ __forceinline__ void row_end_mask(const int32_t (&tmv)[W], int32_t* e
   wave_lds_sync();
 #pragma unroll
   for (int w = 0; w < W; ++w) {
-    const uint32_t e = uint32_t(tmv[w] - 1);        // past `size` the last row's again, or none
+    const uint32_t e = uint32_t(tmv[w] - 1);        // rows beyond `size` hold 0 -> skipped
     if (e < uint32_t(T)) ends[e] = 1;
   }
   wave_lds_sync();
@@ -252,7 +260,7 @@ __device__ __forceinline__ void row_sums(int32_t first, int32_t size, int32_t n_
 }
 
 // One whole group with the calling wave.
-template <int DT, int W, int U, bool STREAM = true>
+template <int DT, int W, int U, bool STREAM = true, bool WAIT = false>
 __device__ __forceinline__ void spmv_group(
     int32_t first, int32_t size, int32_t offset, int32_t c,
     const int32_t* __restrict__ tm, const int32_t* __restrict__ columns,
@@ -261,7 +269,7 @@ __device__ __forceinline__ void spmv_group(
     int32_t* ends) {
   using A = typename Val<DT>::acc;
   int32_t tmv[W];
-  load_mapping<W, STREAM>(first, size, tm, tmv);           // in flight with the first chunk loads
+  load_mapping<W, STREAM, WAIT>(first, size, tm, tmv);
   const int32_t n_mapped = tm[first + size - 1];    // chunks in use; the rest are free
   A acc[W];
   chunk_partials<DT, W, U, STREAM>(offset, 0, c, columns, values, gx, serial, acc);
@@ -286,15 +294,11 @@ __device__ __forceinline__ void spmv_group_split(
   const int32_t share = (c + kSpmvWaves - 1) / kSpmvWaves;
   const int32_t j0 = min(c, wv * share), j1 = min(c, j0 + share);
   int32_t tmv[W];
-  // under a condition, against load_mapping's way: with the waves of the heavy
-  // workgroups held back by it, power-law rows take less (FP32, T = 64, 2*10^5 /
-  // 3.3*10^5 / 7*10^5 rows 16.2 / 21.4 / 35.0 us, without 16.6 / 21.8 / 36.0; FP64,
-  // T = 128, 21.5 / 27.8 / 49.7, without 22.5 / 28.1 / 50.0)
-#pragma unroll
-  for (int w = 0; w < W; ++w) {
-    const int l = w * 64 + lane;
-    tmv[w] = l < size ? load_matrix<STREAM>(tm + first + l) : 0;
-  }
+  // waited for: with the waves of the heavy workgroups held back by it,
+  // power-law rows take less (FP32, T = 64, 2*10^5 / 3.3*10^5 / 7*10^5 rows 16.2 /
+  // 21.4 / 35.0 us, in flight 16.6 / 21.8 / 36.0; FP64, T = 128, 21.5 / 27.8 / 49.7
+  // and 22.5 / 28.1 / 50.0)
+  load_mapping<W, STREAM, true>(first, size, tm, tmv);
   A acc[W];
   chunk_partials<DT, W, U, STREAM>(offset, j0, j1, columns, values, gx, serial, acc);
   if (wv > 0) {
@@ -317,7 +321,7 @@ __device__ __forceinline__ void spmv_group_split(
 // Single-matrix launch: blocks [0, n_heavy) take one heavy group each (in
 // the order of `heavy`, dispatched first); the remaining blocks take
 // kSpmvWaves consecutive groups, one per wave, skipping heavy ones.
-template <int DT, int W, int U>
+template <int DT, int W, int U, bool WAIT>
 __global__ __launch_bounds__(kSpmvWaves * 64) void argcsr_spmv_kernel(
     const argcsr_group_info* __restrict__ groups, int32_t n_groups,
     const int32_t* __restrict__ tm, const int32_t* __restrict__ columns,
@@ -342,8 +346,8 @@ __global__ __launch_bounds__(kSpmvWaves * 64) void argcsr_spmv_kernel(
   if (g >= n_groups) return;
   const argcsr_group_info gi = load_group(groups + g);
   if (gi.chunk_size > heavy_chunk) return;          // processed by a heavy block
-  spmv_group<DT, W, U>(gi.first_row, gi.size, gi.offset, gi.chunk_size, tm, columns, values,
-                       gx, serial != 0, y, ends[wv]);
+  spmv_group<DT, W, U, true, WAIT>(gi.first_row, gi.size, gi.offset, gi.chunk_size, tm, columns,
+                                   values, gx, serial != 0, y, ends[wv]);
 }
 
 int check_matrix(const argcsr_matrix* A);

@@ -846,3 +846,26 @@ def test_trimmed_scratch_goes_back_to_the_device(ac):
     ac.check(ac._lib.lib().argcsr_trim_scratch(), "argcsr_trim_scratch")
     assert torch.cuda.mem_get_info()[0] - kept >= 20 * n
     assert ac.plan_device(rp, 64, 1)[0] == (n + 63) // 64
+
+
+# both ways of the threads mapping (waited for before the chunk loads, or in
+# flight with them): small and large matrices with heavy groups, and without
+# heavy groups irregular rows in short and long chunks and full groups, with
+# last groups of every size
+@pytest.mark.parametrize("dtype", [0, 1, 2, 3])
+@pytest.mark.parametrize("T", [64, 128, 256])
+def test_spmv_threads_mapping_both_ways(ac, dtype, T):
+    rng = np.random.default_rng(T + dtype)
+    cases = [(rng.integers(5, 51, n), D) for n, D in ((3001, 1), (3002, 8), (3003, 27))]
+    cases += [(np.full(40 * T + k, 5, np.int64), 5) for k in (0, 1, T - 1)]
+    heavy = np.clip(rng.zipf(2.0, 350_000), 1, 4000)      # about 2.6*10^6 slots
+    cases += [(heavy[:20_000], 1), (heavy, 1)]
+    for L, D in cases:
+        A = synth.random_csr(L.astype(np.int64), 30_000, rng, rng)
+        x = rng.uniform(-1, 1, A.n_cols)
+        M = ac.convert(ac.to_device_csr(A.rp, A.col, A.val, A.n_cols, DEV), T, D, dtype)
+        assert (M.n_heavy > 0) == (len(L) >= 20_000)
+        if dtype == 0:
+            check_f64(A, x, gpu_spmv(ac, M, x))
+        else:
+            check_reduced(A, x, gpu_spmv(ac, M, x.astype(np.float32)), dtype)
