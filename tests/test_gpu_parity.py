@@ -869,3 +869,74 @@ def test_spmv_threads_mapping_both_ways(ac, dtype, T):
             check_f64(A, x, gpu_spmv(ac, M, x))
         else:
             check_reduced(A, x, gpu_spmv(ac, M, x.astype(np.float32)), dtype)
+
+
+# argcsr_convert by itself, which convert() calls for small matrices, region
+# tables and argcsr_convert_noalloc only: step 1 from the host's row offsets,
+# and on the device without them, in both formats and above the size from
+# which convert() plans on the device
+@pytest.mark.parametrize("host", [True, False])
+@pytest.mark.parametrize("n", [700, 60_000, 200_000])
+def test_convert_call_groups_on_the_host_and_on_the_device(ac, host, n):
+    A, _ = powerlaw_sample(n, seed=n)
+    dev = ac.to_device_csr(A.rp, A.col, A.val, A.n_cols, DEV)
+    for T, D, dtype, fmt in [(64, 1, 0, 0), (128, 3, 1, 0), (1000, 1, 2, 0), (7, 2, 3, 0),
+                             (64, 0, 0, 1), (256, 0, 1, 1)]:
+        if fmt == ac.FORMAT_RG and n > 60_000:
+            continue
+        announce(f"argcsr_convert host={host} n={n} T={T} D={D} dtype={dtype} format={fmt}")
+        sizes = ac.plan(A.rp, T, D, fmt)
+        M = ac._convert_sized(dev, (T, D, dtype, None, True, fmt), sizes,
+                              dev.row_ptr_host if host else None, None, False)
+        ref = (oracle.rg_convert(A.rp, A.col, A.val, T, dtype) if fmt == ac.FORMAT_RG
+               else oracle.convert(A.rp, A.col, A.val, T, D, dtype))
+        assert np.array_equal(M.groups.cpu().numpy(), ref.groups)
+        assert np.array_equal(M.threads_mapping.cpu().numpy(), ref.tm)
+        assert np.array_equal(M.columns.cpu().numpy(), ref.columns)
+        bits = {8: (torch.int64, np.int64), 4: (torch.int32, np.int32),
+                2: (torch.int16, np.int16)}[M.values.element_size()]
+        assert np.array_equal(M.values.cpu().view(bits[0]).numpy(), ref.values.view(bits[1]))
+        heavy = np.nonzero(ref.groups[:, 3] > M.heavy_chunk)[0]
+        assert M.n_heavy == len(heavy)
+        if len(heavy):
+            assert np.array_equal(M.heavy_groups.cpu().numpy(), heavy)
+
+
+def test_conversions_of_all_kinds_on_several_streams(ac):
+    """Threads that convert matrices of different sizes, each on its own
+    stream, by a device plan, with and without the host's row offsets and by
+    argcsr_convert alone: scratch blocks and result slots of one are not
+    another's.  A call that fails is reported, and every result is compared."""
+    mats = [csr_from_lengths(np.random.default_rng(i).integers(0, 9 + 200 * (i == 2), n), 900, i)
+            for i, n in enumerate([20_000, 60_000, 9_000, 3_000])]
+    refs = [oracle.convert(A.rp, A.col, A.val, 64, 1) for A in mats]
+    bad, done = [], []
+
+    def work(i):
+        A, ref, stream = mats[i], refs[i], torch.cuda.Stream()
+        try:
+            with torch.cuda.stream(stream):
+                dev = ac.to_device_csr(A.rp, A.col, A.val, A.n_cols, DEV)
+                how = (64, 1, 0, None, True, ac.FORMAT_ARG)
+                for rep in range(12):
+                    M = (ac.convert(dev, 64, 1) if rep % 3 == 0 else
+                         ac.convert(dev, 64, 1, device_grouping=True) if rep % 3 == 1 else
+                         ac._convert_sized(dev, how, ac.plan(A.rp, 64, 1),
+                                           dev.row_ptr_host if rep % 2 else None, None, False))
+                    heavy = np.nonzero(ref.groups[:, 3] > M.heavy_chunk)[0]
+                    for got, want in ((M.groups, ref.groups), (M.threads_mapping, ref.tm),
+                                      (M.columns, ref.columns), (M.values, ref.values),
+                                      (M.heavy_groups, heavy)):
+                        if not np.array_equal(got.cpu().numpy(), want):
+                            bad.append((i, rep))
+                    done.append(i)
+        except Exception as e:  # noqa: BLE001 - reported below
+            bad.append((i, repr(e)))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(mats))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad, bad
+    assert len(done) == 12 * len(mats)
