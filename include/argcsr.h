@@ -282,6 +282,9 @@ int argcsr_device_plan_destroy(argcsr_device_plan* plan);
  * composing the maps of 4096-row blocks (from each row the path can enter a
  * block at to the row it enters the next one at).  Either way the result equals, byte for byte, the
  * sequential conversion the paper describes.
+ * From about 8192 rows on argcsr_plan_keep and argcsr_convert_planned are the
+ * faster way for a caller with both copies: the host scan of 10^6 rows takes
+ * longer than the whole conversion.
  *   row_ptr_host  host int32[n_rows+1] (same content as row_ptr), or NULL
  *   row_ptr       device int32[n_rows+1]
  *   col           device int32[nnz], 0 <= col < n_cols

@@ -79,7 +79,11 @@ int launch_staged(const argcsr_matrix* A, const void* x, void* y, hipStream_t s)
 //   BF16  W = 1:  5 52 / 12 / 8.5, 8 52 / 13 / 11.7, 4 55 / 13 / 9.1
 //         W = 2:  3 48 / 13 / 8.6, 2 47 / 15 / 8.0, 4 49 / 13 / 8.7
 //         W = 4:  2 47 / 17 / 8.9, 3 45 / 15 / 10.7, 4 51 / 17 / 10.2
-// FP32 orders them the same.
+// FP32 orders them the same.  With x gathered these steps take, where the plain
+// kernel's (8 / 4 / 2 for W = 1 / 2 / 4) and waits between the loads of a batch did
+// before: FP64 W = 1 121 / 24 / 13.6 (124 / 25 / 13.4), W = 2 118 / 23 / 12.6 (118 /
+// 35 / 15.3), W = 4 113 / 28 / 14.2 (120 / 49 / 17.1); BF16 W = 1 56 / 13 / 8.6 (89 /
+// 22 / 12.0), W = 2 55 / 14 / 8.7 (56 / 17 / 11.2), W = 4 56 / 21 / 9.7 (55 / 26 / 11.2).
 template <int DT, int W>
 constexpr int staged_steps() {
   if (sizeof(typename Val<DT>::acc) == 8) return W == 1 ? 8 : W == 2 ? 3 : 2;

@@ -147,10 +147,13 @@ __device__ __forceinline__ void window_starts(uint32_t b, int bit0, int prev, in
   }
 }
 
-// What bounds it: VALU issue, 514 instructions a wave in the count pass
-// and 790 with FILL, for reading the columns (4 bytes a slot), marking, scans
-// and lookup, and writing the positions (2 bytes a slot); the group's chain is
-// hidden by the other groups of a CU.  A
+// What takes the time: reading the columns (4 bytes a slot), marking, scans and
+// lookup, and writing the positions (2 bytes a slot); the group's chain is
+// hidden by the other groups of a CU.  The vector ALU issues for 26 of the
+// count pass's 36 us (514 instructions a wave) and 40 of the fill pass's 58
+// (790), yet fewer instructions per marked column took the same time: neither
+// issue nor the stream alone is the bound.  The fill finds the windows again
+// that the count found, which nothing carries over.  A
 // thread holds up to kHeldSlots columns in registers, so a group that fits
 // its workgroup's registers is read once; a longer one is read again (from
 // L2) in each of the three phases.  The bitmap covers 2^15 columns at a time

@@ -87,8 +87,11 @@ double model_us(int32_t dtype, int32_t n_rows, int32_t n_cols, int32_t G, int64_
 // kernel overlaps the members, so only throughput counts -- the bytes of the
 // member's slots and groups at a rate that falls with the block size (a
 // group's wave streams more slots per step) and a cost per group (the
-// kernel of that time handed out groups one by one).  The part that does not depend on the
-// choice (x gathers, y, the row offsets) is left out.
+// kernel of that time handed out groups one by one).  The part that does not
+// depend on the choice (x gathers, y, the row offsets) is left out.  With the
+// present kernel its choices are within 1 to 4% of the best of 48 others, one
+// (T, D) for all or one for each kind of member: 48 matrices FP32 164 us (163),
+// 256 838 (830), 48 in FP64 220 (213).
 constexpr double kMemberBytesPerUs[3] = {5.25e6, 4.9e6, 4.0e6};  // T = 64, 128, 256
 constexpr double kMemberUsPerGroup = 3.5e-4;
 
