@@ -29,12 +29,16 @@ constexpr int kLongBatch = 8;     // elements of a row of bin 7 a lane loads at 
 // column, x and sum, but many workgroups' batches queue their gathers in front
 // of each other's loads.  With `streamed` the elements pass by L2 and the
 // Infinity Cache.  us, three matrices in turn, FP32 but where marked:
-// * Up to kCachedBytes a matrix the Infinity Cache holds the elements: ordinary
-//   loads, and batches for the few longest rows alone, whose round trips the
-//   launch takes.  Batches for rows over 4096 / for all / for all and streamed:
-//   1000 rows of 3000 11.8 / 15.1 / 17.7, 4000 of 1000 20.4 / 21.3 / 26,
-//   power-law rows of 3*10^5 20.6 / 21.8 / 30, 10^6 54 / 54 / 59.5 (without
-//   batches 61).
+// * Up to kCachedBytes a matrix the Infinity Cache holds the elements from one
+//   product to the next: ordinary loads.  Where bin 7 holds nearly all of the
+//   matrix only rows over 4096 take batches: over 4096 / all / all streamed, 1000
+//   rows of 3000 11.8 / 15.1 / 17.7, 4000 of 1000 20.4 / 21.3 / 26.  Beside other
+//   rows, those over 1024, whose round trips the launch takes: over 4096 / over
+//   1024 / over 1024 streamed, power-law rows of 10^5 10.0 / 9.3 / 11.3, 3.3*10^5
+//   23.2 / 21.9 / 27.6, FP64 30 / 27.3 / 32.3, 10^6 54 / 54 / 59.1 (without
+//   batches 61).  With nothing in the caches: 16.9 / 14.5 / 14.7, 33.7 / 31.9 /
+//   32.6, FP64 41 / 37 / 34, 75.3 / 75.3 / 70.9, and 1000 rows of 3000, over 4096 /
+//   all streamed, 23.6 / 21.0: streamed loads would be the faster there.
 // * Beyond, they come from HBM and are streamed.  A lane's first element needs
 //   no batch, rows of 1024 just half a one: 70^3 rows of 125, singly / batches of
 //   8, 323 / 370, BF16 318 / 407; 10^5 rows of 1000, batches of 4 / 8, 535 / 611,
@@ -51,10 +55,11 @@ struct LongRows {
 constexpr int64_t kCachedBytes = 100 * 1000 * 1000;
 constexpr int64_t kCachedBesideX = 75 * 1000 * 1000;
 constexpr int64_t kL2Bytes = int64_t(4) << 20;    // of an XCD
-constexpr LongRows long_rows(int64_t nnz, int32_t value_bytes, int32_t n_cols, int32_t x_bytes) {
+constexpr LongRows long_rows(int64_t nnz, int64_t long_nnz, int32_t value_bytes, int32_t n_cols,
+                             int32_t x_bytes) {
   const int64_t bytes = nnz * (int64_t(sizeof(int32_t)) + value_bytes);
   const bool x_in_l2 = int64_t(n_cols) * x_bytes <= kL2Bytes;
-  if (bytes < (x_in_l2 ? kCachedBytes : kCachedBesideX)) return LongRows{4096, false};
+  if (bytes < (x_in_l2 ? kCachedBytes : kCachedBesideX)) return LongRows{long_nnz >= nnz - nnz / 8 ? 4096 : 1024, false};
   return LongRows{value_bytes == 2 ? 512 : 256, true};
 }
 constexpr int kBins = ARGCSR_CSR_BINS;      // 8: widths 1, 2, 4, ..., 64, then a workgroup
@@ -435,11 +440,11 @@ int team_rows(const int32_t* bin_start) {
 }
 
 template <int DT>
-void launch_binned(const BinLaunch& bl, int team, int32_t blocks, int64_t nnz, int32_t n_cols,
-                   const int32_t* rows, const int32_t* rp, const int32_t* col, const void* val,
+void launch_binned(const BinLaunch& bl, int team, int32_t blocks, int64_t nnz, int64_t long_nnz,
+                   int32_t n_cols, const int32_t* rows, const int32_t* rp, const int32_t* col, const void* val,
                    const void* x, void* y, hipStream_t s) {
   using Vt = Val<DT>;
-  const LongRows lr = long_rows(nnz, int32_t(sizeof(typename Vt::storage)), n_cols,
+  const LongRows lr = long_rows(nnz, long_nnz, int32_t(sizeof(typename Vt::storage)), n_cols,
                                 int32_t(sizeof(typename Vt::acc)));
   auto* kern = team == 4 ? lr.streamed ? &csr_binned_kernel<DT, 4, true>
                                        : &csr_binned_kernel<DT, 4, false>
@@ -514,12 +519,13 @@ extern "C" int argcsr_csr_spmv_binned(int32_t n_rows, int32_t n_cols, int64_t nn
   const int team = team_rows(bin_start);
   BinLaunch bl{};
   int64_t blocks = 0;                 // of the bins but the last
+  int64_t long_nnz = nnz;             // elements of the last bin, at least
   for (int k = 0; k < kBins; ++k) {
     bl.row_start[k] = bin_start[k];
     const int64_t cnt = bin_start[k + 1] - bin_start[k];
     const int64_t per = k < kBins - 1 ? team * (kCsrBlock >> k) : 1;   // rows per workgroup
     bl.blocks[k] = int32_t((cnt + per - 1) / per);
-    if (k < kBins - 1) blocks += bl.blocks[k];
+    if (k < kBins - 1) blocks += bl.blocks[k], long_nnz -= cnt << k;
   }
   bl.row_start[kBins] = bin_start[kBins];
   bl.long_blocks = (bl.blocks[kBins - 1] + kXcds - 1) / kXcds * kXcds;
@@ -538,7 +544,7 @@ extern "C" int argcsr_csr_spmv_binned(int32_t n_rows, int32_t n_cols, int64_t nn
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int32_t nb = int32_t(grid);
   auto go = [&](auto* launch) {
-    launch(bl, team, nb, nnz, n_cols, rows, row_ptr, col, val, x, y, s);
+    launch(bl, team, nb, nnz, long_nnz, n_cols, rows, row_ptr, col, val, x, y, s);
   };
   switch (dtype) {
     case ARGCSR_F64: go(&launch_binned<ARGCSR_F64>); break;

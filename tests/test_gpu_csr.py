@@ -192,21 +192,22 @@ def test_binned_edge_cases(ac):
         ac.csr_spmv_binned(dz, torch.ones(10, dtype=torch.float64, device=DEV), bz)
 
 
-# how the rows of bin 7 are read: singly up to 4096 elements and in batches
-# above, in one launch (a matrix the Infinity Cache holds); from 100 MB of
+# how the rows of bin 7 are read: singly up to 4096 elements (1024 beside other
+# rows) and in batches above, in one launch (a matrix the Infinity Cache holds); from 100 MB of
 # elements on singly up to 256 (512 in 2-byte values), in batches of 4 up to
 # 1024 and of 8 above, streamed; from 75 MB on where x is over 4 MB
-@pytest.mark.parametrize("dtype,n_cols,mb", [
-    (0, 9000, 2), (0, 9000, 99), (0, 9000, 101), (0, 530_000, 74), (0, 530_000, 76),
-    (1, 9000, 99), (1, 9000, 101), (1, 1_060_000, 76), (2, 9000, 2), (2, 9000, 101)])
-def test_binned_long_row_paths(ac, dtype, n_cols, mb):
+@pytest.mark.parametrize("dtype,n_cols,mb,beside", [
+    (0, 9000, 2, 0), (0, 9000, 99, 0), (0, 9000, 101, 0), (0, 530_000, 74, 0), (0, 530_000, 76, 0),
+    (1, 9000, 99, 0), (1, 9000, 101, 0), (1, 1_060_000, 76, 0), (2, 9000, 2, 0), (2, 9000, 101, 0),
+    (0, 9000, 3, 9000), (1, 9000, 2, 9000), (3, 9000, 2, 9000)])
+def test_binned_long_row_paths(ac, dtype, n_cols, mb, beside):
     rng = np.random.default_rng(mb)
     edges = np.array([65, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025, 2047, 2048, 2049, 4095,
                       4096, 4097, 4096 + 255, 4096 + 256, 4096 + 257, 6143, 6144, 6145, 8191,
                       8192, 8193])
     elements = mb * 1_000_000 // (4 + [8, 4, 2, 2][dtype]) + 1
     L = np.concatenate([edges, np.full((elements - edges.sum() - 600) // 2500, 2500),
-                        rng.integers(0, 65, 20)])
+                        rng.integers(0, 65, 20 + beside)])
     L = np.append(L, max(0, elements - L.sum())).astype(np.int64)
     rng.shuffle(L)
     A = synth.random_csr(L, n_cols, rng, rng)
